@@ -82,21 +82,27 @@ void drop_graph(sgn_batch* b) {
   b->gexec = nullptr;
 }
 
+// Tile height that the tile kernels run: FP64 32 x 24 tiles with a wall would need
+// more than 256 registers, so an FP64 ensemble runs 32 x 16 ones in their place.
+int tile_of(const sgn_batch* b) {
+  return b->path == SGN_PATH_FUSED && b->tile_y == 24 && b->dtype == SGN_F64 ? 16 : b->tile_y;
+}
+
 int work_key(const sgn_batch* b) { return b->path * 100 + b->tile_y; }
 
 int tile_width(const sgn_batch* b) {
-  return b->path == SGN_PATH_FUSED ? (b->tile_y == 8 ? sgn::StepGeom<8>::TX : sgn::StepGeom<16>::TX) : sgn::TILE_X;
+  return b->path == SGN_PATH_FUSED ? (tile_of(b) == 8 ? sgn::StepGeom<8>::TX : sgn::StepGeom<16>::TX) : sgn::TILE_X;
 }
 
 // (Re)build the work list and descriptors for the current path and tile height.
 sgn_status build_work(sgn_batch* b) {
   if (b->work_key == work_key(b) && b->d_work) return SGN_OK;
   std::vector<int> work;
-  const int tw = tile_width(b);
+  const int tw = tile_width(b), th = tile_of(b);
   for (int i = 0; i < b->n; ++i) {
     sgn::InstDesc& d = b->h_desc[i];
     d.ntx = (b->params[i].nx + tw - 1) / tw;
-    d.nty = (b->params[i].ny + b->tile_y - 1) / b->tile_y;
+    d.nty = (b->params[i].ny + th - 1) / th;
     d.tile_base = (int)work.size();
     for (int t = 0; t < d.ntx * d.nty; ++t) work.push_back(i);
   }
@@ -176,13 +182,13 @@ hipError_t launch_batch_step_t(const sgn_batch* b, hipStream_t s, int parity, in
 // One RK4 step of every instance from the buffer selected by parity into the other.
 hipError_t enqueue_batch_step(const sgn_batch* b, hipStream_t s, int parity) {
   if (b->path == SGN_PATH_FUSED) {
+    const int ty = tile_of(b), bpc = b->tile_y == 24 ? 0 : b->blocks_per_cu;
     if (b->dtype == SGN_F64)
-      return b->tile_y == 24   ? launch_batch_step_t<double, 24>(b, s, parity, b->blocks_per_cu)
-             : b->tile_y == 16 ? launch_batch_step_t<double, 16>(b, s, parity, b->blocks_per_cu)
-                               : launch_batch_step_t<double, 8>(b, s, parity, b->blocks_per_cu);
-    return b->tile_y == 24   ? launch_batch_step_t<float, 24>(b, s, parity, b->blocks_per_cu)
-           : b->tile_y == 16 ? launch_batch_step_t<float, 16>(b, s, parity, b->blocks_per_cu)
-                             : launch_batch_step_t<float, 8>(b, s, parity, b->blocks_per_cu);
+      return ty == 16 ? launch_batch_step_t<double, 16>(b, s, parity, bpc)
+                      : launch_batch_step_t<double, 8>(b, s, parity, bpc);
+    return ty == 24   ? launch_batch_step_t<float, 24>(b, s, parity, bpc)
+           : ty == 16 ? launch_batch_step_t<float, 16>(b, s, parity, bpc)
+                      : launch_batch_step_t<float, 8>(b, s, parity, bpc);
   }
   hipError_t e = launch_batch_pair(b, s, 1, parity);
   if (e) return e;

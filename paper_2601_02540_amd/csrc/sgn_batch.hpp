@@ -107,10 +107,10 @@ __device__ __forceinline__ void batch_step_item(StepSmem<T, TY, 1>& s, const Ins
   const double dt = d.dt;
   const T c6 = T(dt / 6.0), c3 = T(dt / 3.0), c2 = T(dt / 2.0), c1 = T(dt);
   switch (d.gc.bc_x * 2 + d.gc.bc_y) {
-    case 0: step_tile<T, 0, 0, false, TY, false>(s, d.gc, i0, j0, cur, b, oth, c6, c3, c2, c1, 0.0, dt, flags + inst, nullptr); break;
-    case 1: step_tile<T, 0, 1, false, TY, false>(s, d.gc, i0, j0, cur, b, oth, c6, c3, c2, c1, 0.0, dt, flags + inst, nullptr); break;
-    case 2: step_tile<T, 1, 0, false, TY, false>(s, d.gc, i0, j0, cur, b, oth, c6, c3, c2, c1, 0.0, dt, flags + inst, nullptr); break;
-    default: step_tile<T, 1, 1, false, TY, false>(s, d.gc, i0, j0, cur, b, oth, c6, c3, c2, c1, 0.0, dt, flags + inst, nullptr); break;
+    case 0: step_tile<T, 0, 0, false, TY, false, 1, EPI_NONE, RK_CLASSIC, sizeof(T) == 4>(s, d.gc, i0, j0, cur, b, oth, c6, c3, c2, c1, 0.0, dt, flags + inst, nullptr); break;
+    case 1: step_tile<T, 0, 1, false, TY, false, 1, EPI_NONE, RK_CLASSIC, sizeof(T) == 4>(s, d.gc, i0, j0, cur, b, oth, c6, c3, c2, c1, 0.0, dt, flags + inst, nullptr); break;
+    case 2: step_tile<T, 1, 0, false, TY, false, 1, EPI_NONE, RK_CLASSIC, sizeof(T) == 4>(s, d.gc, i0, j0, cur, b, oth, c6, c3, c2, c1, 0.0, dt, flags + inst, nullptr); break;
+    default: step_tile<T, 1, 1, false, TY, false, 1, EPI_NONE, RK_CLASSIC, sizeof(T) == 4>(s, d.gc, i0, j0, cur, b, oth, c6, c3, c2, c1, 0.0, dt, flags + inst, nullptr); break;
   }
 }
 

@@ -141,11 +141,11 @@ __global__ __launch_bounds__(STAGE_THREADS) void fsal_kernel(const GridConst gc,
     const size_t o = (size_t)gj * nx + gi;
     T v[5];
 #pragma unroll
-    for (int f = 0; f < 5; ++f) v[f] = ROLE == FS_S2 ? Yin[f * N + o] + cin * k1[f * N + o] : Yin[f * N + o];
+    for (int f = 0; f < 5; ++f) v[f] = ROLE == FS_S2 ? fused(cin, k1[f * N + o], Yin[f * N + o]) : Yin[f * N + o];
 #pragma unroll
     for (int f = 0; f < 5; ++f) s.f[f][rr][cc] = v[f];
     s.f[5][rr][cc] = a.b[o];
-    s.f[6][rr][cc] = recip_staged(v[0]);
+    s.f[6][rr][cc] = node_e(v[0], v[4], recip_staged(v[0]));
   }
 
   // own-node operands, fetched before the barrier
@@ -206,27 +206,28 @@ __global__ __launch_bounds__(STAGE_THREADS) void fsal_kernel(const GridConst gc,
     const Node<T> ym = lds_node(s, r + ay.om, cidx);
     const Node<T> yp = lds_node(s, r + ay.op, cidx);
     const Rates<T> kk =
-        split_form_rates<T, BCX, BCY>(c, xm, xp, ym, yp, T(ax.scale), T(ay.scale), g, lam, satx, saty);
+        split_form_rates<T, BCX, BCY>(c, recip_staged(c.h), xm, xp, ym, yp, T(ax.scale), T(ay.scale), g, lam, satx,
+                                      saty);
     const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
     const T yv[5] = {c.h, c.u, c.v, c.w, c.eta};
     const size_t o = (size_t)j * nx + i;
     if (ROLE == FS_S2) {
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        ynew[f * N + o] = pa[k][f] + c1a * pb[k][f] + cacc * kv[f];
-        Yout[f * N + o] = pa[k][f] + cy * kv[f];
+        ynew[f * N + o] = fused(cacc, kv[f], fused(c1a, pb[k][f], pa[k][f]));
+        Yout[f * N + o] = fused(cy, kv[f], pa[k][f]);
       }
     } else if (ROLE == FS_S3 || ROLE == FS_S4) {
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        ynew[f * N + o] = pb[k][f] + cacc * kv[f];
-        Yout[f * N + o] = pa[k][f] + cy * kv[f];
+        ynew[f * N + o] = fused(cacc, kv[f], pb[k][f]);
+        Yout[f * N + o] = fused(cy, kv[f], pa[k][f]);
       }
     } else if (ROLE == FS_S5) {
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        ynew[f * N + o] = pb[k][f] + cacc * kv[f];
-        a.e[f * N + o] = cacc * kv[f] - ce1 * pa[k][f];
+        ynew[f * N + o] = fused(cacc, kv[f], pb[k][f]);
+        a.e[f * N + o] = fused(-ce1, pa[k][f], cacc * kv[f]);
       }
     } else {
 #pragma unroll

@@ -62,19 +62,43 @@ struct StepGeom {
 // values near the x-walls with padded rows, a failure not explained by the
 // source; unpadded they agree bit for bit with the four-stage path.
 template <typename T, int TY, int PAD>
-struct StepSmem {
-  T f[7][StepGeom<TY>::RY][StepGeom<TY>::RX + PAD];  // h u v w eta b 1/h, then the current stage (b kept)
+struct StepSmem;
+
+typedef double sgn_d2 __attribute__((ext_vector_type(2)));
+typedef float sgn_f4 __attribute__((ext_vector_type(4)));
+
+template <int TY, int PAD>
+struct StepSmem<double, TY, PAD> {
+  static constexpr int RY = StepGeom<TY>::RY, P = StepGeom<TY>::RX + PAD;
+  sgn_d2 a[3][RY][P];  // (h, u), (v, w), (eta, e) of the current stage
+  double b[RY][P];
+  __device__ __forceinline__ Node<double> load(int r, int c) const {
+    const sgn_d2 x = a[0][r][c], y = a[1][r][c], z = a[2][r][c];
+    return Node<double>{x.x, x.y, y.x, y.y, z.x, b[r][c], z.y};
+  }
+  // everything but b (`bb`: the node's b, unused here)
+  __device__ __forceinline__ void store(int r, int c, const double (&y)[5], double e, double) {
+    a[0][r][c] = sgn_d2{y[0], y[1]};
+    a[1][r][c] = sgn_d2{y[2], y[3]};
+    a[2][r][c] = sgn_d2{y[4], e};
+  }
+  __device__ __forceinline__ void store_b(int r, int c, double bb) { b[r][c] = bb; }
 };
 
-// The node's values behind an empty asm statement: the compiler can no longer
-// identify them with the values they were copied from, so it neither merges
-// arithmetic on them with earlier arithmetic nor changes how that arithmetic
-// is fused.
-template <typename T>
-__device__ __forceinline__ Node<T> opaque_node(Node<T> n) {
-  asm volatile("" : "+v"(n.h), "+v"(n.u), "+v"(n.v), "+v"(n.w), "+v"(n.eta), "+v"(n.b), "+v"(n.ih));
-  return n;
-}
+template <int TY, int PAD>
+struct StepSmem<float, TY, PAD> {
+  static constexpr int RY = StepGeom<TY>::RY, P = StepGeom<TY>::RX + PAD;
+  sgn_f4 a[2][RY][P];  // (h, u, v, w), (eta, e, b, unused) of the current stage
+  __device__ __forceinline__ Node<float> load(int r, int c) const {
+    const sgn_f4 x = a[0][r][c], y = a[1][r][c];
+    return Node<float>{x.x, x.y, x.z, x.w, y.x, y.z, y.y};
+  }
+  __device__ __forceinline__ void store(int r, int c, const float (&y)[5], float e, float bb) {
+    a[0][r][c] = sgn_f4{y[0], y[1], y[2], y[3]};
+    a[1][r][c] = sgn_f4{y[4], e, bb, 0.0f};
+  }
+  __device__ __forceinline__ void store_b(int, int, float) {}
+};
 
 // Which Runge-Kutta method a step tile runs.  RK_CLASSIC: one classical RK4
 // step from q.  RK_FSAL: evaluations 2 to 5 of one attempt of the adaptive
@@ -143,6 +167,17 @@ __device__ __forceinline__ void ring_node(int m, int& r, int& c) {
   }
 }
 
+// KEEP: the owned nodes' current stage Y and its 1/h stay in registers from stage
+// to stage, so that LDS gives them only the nodes around the column of NO (one
+// above, one below, two beside each), two thirds of the reads.  Without KEEP they
+// read their centres back: where the registers would pass 256 (FP64 32 x 24 tiles
+// with a wall: 900 us at 4096^2 instead of 640; the adaptive attempt; the ensemble
+// kernels, which hold all four boundary variants).
+template <typename T, int TY, int BCX, int BCY, int RK>
+constexpr bool step_keeps() {
+  return sizeof(T) == 4 || (RK != RK_FSAL && (TY != 24 || (BCX == BC_PERIODIC && BCY == BC_PERIODIC)));
+}
+
 // One tile (origin i0, j0) of one RK4 step, executed by a whole workgroup.
 // SAVE (the adjoint's recomputation): also write the intermediate stages
 // Y2, Y3, Y4 of the owned nodes to ysave, three consecutive states.
@@ -155,7 +190,7 @@ __device__ __forceinline__ void ring_node(int m, int& r, int& c) {
 // output; c6 .. c1, t0, dt and flag are unused (the health of y_{n+1} is
 // checked by the attempt's FSAL evaluation).
 template <typename T, int BCX, int BCY, bool SRC, int TY, bool SAVE, int PAD, int EPI = EPI_NONE,
-          int RK = RK_CLASSIC>
+          int RK = RK_CLASSIC, bool KEEP = step_keeps<T, TY, BCX, BCY, RK>()>
 __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridConst& gc, int i0, int j0,
                                           const T* __restrict__ q, const T* __restrict__ bplane,
                                           T* __restrict__ qout, T c6, T c3, T c2, T c1, double t0, double dt,
@@ -166,7 +201,7 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
   static_assert(RK != RK_FSAL || (!SRC && !SAVE && EPI == EPI_NONE), "the FSAL tile has no extras");
   static_assert(RK != RK_RELAXED || (!SRC && !SAVE), "the relaxed tile has no source or stage saving");
   using G = StepGeom<TY>;
-  constexpr int TX = G::TX, NO = G::NO;
+  constexpr int TX = G::TX, NO = G::NO, NR = 2;
   constexpr int RX = G::RX;
   constexpr int REGION = G::RX * G::RY;
 
@@ -179,7 +214,7 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
   //    for: the step kernel reads little per unit of work, so its bandwidth
   //    is set by how many bytes each workgroup keeps in flight.
   constexpr int NF = RK == RK_FSAL ? 1 : 0;
-  T yown[NF ? NO : 1][5], yring[NF ? 2 : 1][5];  // RK_FSAL: y of the owned and ring nodes
+  T yown[NF ? NO : 1][5], yring[NF ? NR : 1][5];  // RK_FSAL: y of the owned and ring nodes
   {
     constexpr int ITER = (REGION + STAGE_THREADS - 1) / STAGE_THREADS;
     T v[ITER][6];
@@ -219,32 +254,34 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
         if constexpr (RK == RK_RELAXED) {
           const T gam = T(rx->rs[0]);
 #pragma unroll
-          for (int f = 0; f < 5; ++f) v[it][f] = v[it][f] + gam * (kst[it][f] - v[it][f]);
+          for (int f = 0; f < 5; ++f) v[it][f] = fused(gam, kst[it][f] - v[it][f], v[it][f]);
         }
-#pragma unroll
-        for (int f = 0; f < 6; ++f) s.f[f][rr][cc] = v[it][f];
-        if constexpr (RK != RK_FSAL) s.f[6][rr][cc] = recip_staged(v[it][0]);
+        s.store_b(rr, cc, v[it][5]);
+        const T y[5] = {v[it][0], v[it][1], v[it][2], v[it][3], v[it][4]};
+        s.store(rr, cc, y, RK == RK_FSAL ? T(0) : node_e(y[0], y[4], recip_staged(y[0])), v[it][5]);
       }
     }
     if constexpr (RK == RK_FSAL) {
       __syncthreads();
       // LDS holds y: the owned and ring nodes take their y from it (the ring's
       // periodic images and clamped wall copies included), then Y_2 =
-      // y + h c_2 k_1 and its 1/h replace it
+      // y + h c_2 k_1 and its e replace it
       const int lx_ = tid % TX, ly_ = NO * (tid / TX);
 #pragma unroll
       for (int k = 0; k < NO; ++k) {
-#pragma unroll
-        for (int f = 0; f < 5; ++f) yown[k][f] = s.f[f][ly_ + k + STEP_HALO][lx_ + STEP_HALO];
+        {
+          const Node<T> n = s.load(ly_ + k + STEP_HALO, lx_ + STEP_HALO);
+          yown[k][0] = n.h, yown[k][1] = n.u, yown[k][2] = n.v, yown[k][3] = n.w, yown[k][4] = n.eta;
+        }
       }
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
+      for (int k = 0; k < NR; ++k) {
         const int m = tid + k * STAGE_THREADS;
         if (m < G::RING3) {
           int r_, c_;
           ring_node<TY>(m, r_, c_);
-#pragma unroll
-          for (int f = 0; f < 5; ++f) yring[k][f] = s.f[f][r_ + STEP_HALO][c_ + STEP_HALO];
+          const Node<T> n = s.load(r_ + STEP_HALO, c_ + STEP_HALO);
+          yring[k][0] = n.h, yring[k][1] = n.u, yring[k][2] = n.v, yring[k][3] = n.w, yring[k][4] = n.eta;
         }
       }
       __syncthreads();
@@ -257,10 +294,9 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
           T y2[5];
 #pragma unroll
           for (int f = 0; f < 5; ++f) {
-            y2[f] = v[it][f] + fx->cin * kst[it][f];
-            s.f[f][rr][cc] = y2[f];
+            y2[f] = fused(fx->cin, kst[it][f], v[it][f]);
           }
-          s.f[6][rr][cc] = recip_staged(y2[0]);
+          s.store(rr, cc, y2, node_e(y2[0], y2[4], recip_staged(y2[0])), v[it][5]);
         }
       }
     }
@@ -277,10 +313,10 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
     const int j = j0 + ly0 + k;
     own_dom[k] = on_axis<BCX>(i, nx) && on_axis<BCY>(j, ny);
   }
-  int ring_r[2], ring_c[2];
-  bool ring_ok[2];
+  int ring_r[NR], ring_c[NR];
+  bool ring_ok[NR];
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < NR; ++k) {
     const int m = tid + k * STAGE_THREADS;
     ring_r[k] = 0;
     ring_c[k] = 0;
@@ -292,24 +328,27 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
   }
   __syncthreads();
 
-  T qo[NO][5], acc[NO][5], qr[2][5];
-  T k1o[NF ? NO : 1][5];  // RK_FSAL: k_1 of the owned nodes
+  // ihr: 1/h of the ring nodes' current stage
+  Node<T> Y[NO];
+  T ih[NO], ihr[NR];
+  T qo[NO][5], acc[NO][5], qr[NR][5];
+#pragma unroll
+  for (int k = 0; k < NO; ++k) {
+    if (KEEP) {
+      Y[k] = s.load(ly0 + k + STEP_HALO, lx + STEP_HALO);
+      ih[k] = recip_staged(Y[k].h);
+    }
+    if constexpr (RK == RK_FSAL) {
+#pragma unroll
+      for (int f = 0; f < 5; ++f) qo[k][f] = yown[k][f];
+    }
+  }
   if constexpr (RK == RK_FSAL) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < NR; ++k) {
       if (tid + k * STAGE_THREADS < G::RING3) {
 #pragma unroll
         for (int f = 0; f < 5; ++f) qr[k][f] = yring[k][f];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NO; ++k) {
-#pragma unroll
-      for (int f = 0; f < 5; ++f) qo[k][f] = yown[k][f];
-      if (own_dom[k]) {
-        const size_t ow = (size_t)wrap_or_clamp<BCY>(j0 + ly0 + k, ny) * nx + wrap_or_clamp<BCX>(i, nx);
-#pragma unroll
-        for (int f = 0; f < 5; ++f) k1o[k][f] = fx->k1[f * N + ow];
       }
     }
   }
@@ -329,67 +368,99 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
     }
     const double ts = t0 + (st == 1 ? 0.0 : (st == 4 ? dt : 0.5 * dt));
     const int ring_lim = st == 1 ? G::RING3 : (st == 2 ? G::RING2 : G::RING1);
-    T ro[NO][5], rr[2][5];
-    // Owned nodes.  Node k lies just above node k - 1 in y, so whenever node k
-    // is in the domain (then j0 + ly0 + k - 1 is neither the first row nor
-    // beyond the last) its lower y-neighbour is node k - 1's centre, and node
-    // 1's centre is node 0's upper y-neighbour: the pair reads 8 nodes from
-    // LDS, not 10, and three nodes read 12, not 15.
-    const auto finish = [&](int k, const Rates<T>& kk, const Node<T>& cn) {
+    // Owned nodes, upwards: node k's lower neighbour is node k - 1 (its stage
+    // before this evaluation replaced it), its upper neighbour node k + 1.
+    const AxisStencil<BCX> ax(i, nx, gc.inv2dx, gc.invdx);
+    Node<T> below, above;
+#pragma unroll
+    for (int k = 0; k < NO; ++k) {
+      __builtin_amdgcn_sched_barrier(0);
       const int j = j0 + ly0 + k;
-      const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
-      if constexpr (RK == RK_FSAL) {
+      const bool run = st < 4 ? own_dom[k] : (i < nx && j < ny);
+      if (!run) continue;
+      const int r = ly0 + k + STEP_HALO, c = lx + STEP_HALO;
+      const AxisStencil<BCY> ay(j, ny, gc.inv2dy, gc.invdy);
+      const Node<T> cn = KEEP ? Y[k] : (k == 0 ? s.load(r, c) : above);
+      const Node<T> xm = s.load(r, c + ax.om);
+      const Node<T> xp = s.load(r, c + ax.op);
+      Node<T> dn, up;
+      if (k == 0) {
+        dn = s.load(r + ay.om, c);
+      } else {
+        dn = below;  // j > 0 here
+      }
+      if (k == NO - 1 || !KEEP) {
+        up = s.load(r + ay.op, c);
+        above = up;
+      } else {
+        up = Y[k + 1];
+        if (BCY == BC_REFLECTING && j == ny - 1) up = cn;
+      }
+      below = cn;
+      const size_t o = (size_t)j * nx + i;
+      if constexpr (RK != RK_FSAL) {
         if (st == 1) {
+          qo[k][0] = cn.h;
+          qo[k][1] = cn.u;
+          qo[k][2] = cn.v;
+          qo[k][3] = cn.w;
+          qo[k][4] = cn.eta;
+          if constexpr (RK == RK_RELAXED) {
+            if (i < nx && j < ny) {
 #pragma unroll
-          for (int f = 0; f < 5; ++f) {
-            acc[k][f] = qo[k][f] + fx->c1a * k1o[k][f] + ca * kv[f];
-            ro[k][f] = qo[k][f] + cy * kv[f];
+              for (int f = 0; f < 5; ++f) rx->qbase[f * N + o] = qo[k][f];
+            }
           }
-        } else if (st < 4) {
-#pragma unroll
-          for (int f = 0; f < 5; ++f) {
-            acc[k][f] = acc[k][f] + ca * kv[f];
-            ro[k][f] = qo[k][f] + cy * kv[f];
-          }
-        }
-      } else if (st == 1) {
-        const T yv[5] = {cn.h, cn.u, cn.v, cn.w, cn.eta};
-#pragma unroll
-        for (int f = 0; f < 5; ++f) {
-          qo[k][f] = yv[f];
-          acc[k][f] = yv[f] + ca * kv[f];
-          ro[k][f] = yv[f] + cy * kv[f];
-        }
-        if constexpr (RK == RK_RELAXED) {
-          if (i < nx && j < ny) {
-            const size_t o = (size_t)j * nx + i;
-#pragma unroll
-            for (int f = 0; f < 5; ++f) rx->qbase[f * N + o] = yv[f];
-          }
-        }
-      } else if (st < 4) {
-#pragma unroll
-        for (int f = 0; f < 5; ++f) {
-          acc[k][f] = acc[k][f] + ca * kv[f];
-          ro[k][f] = qo[k][f] + cy * kv[f];
         }
       }
-      if (SAVE && st < 4 && i < nx && j < ny) {
-        T* ys = ysave + (size_t)(st - 1) * 5 * N + (size_t)j * nx + i;
+      T k1o[5];  // RK_FSAL: k_1 of the node, read (from L2) where it is used
+      if constexpr (RK == RK_FSAL) {
+        if (st == 1 || st == 4) {
+          const size_t ow = (size_t)wrap_or_clamp<BCY>(j, ny) * nx + wrap_or_clamp<BCX>(i, nx);
 #pragma unroll
-        for (int f = 0; f < 5; ++f) ys[f * N] = ro[k][f];
+          for (int f = 0; f < 5; ++f) k1o[f] = fx->k1[f * N + ow];
+        }
       }
-      if (st == 4) {
-        const size_t o = (size_t)j * nx + i;
+      const Rates<T> kk = node_rates<T, BCX, BCY, SRC>(cn, KEEP ? ih[k] : recip_staged(cn.h), xm, xp, dn, up, ax, ay, i,
+                                                       j, gc, ts);
+      const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
+      if (st < 4) {
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+          T a = qo[k][f];
+          if constexpr (RK == RK_FSAL) {
+            if (st == 1) a = fused(fx->c1a, k1o[f], a);
+          }
+          acc[k][f] = fused(ca, kv[f], st == 1 ? a : acc[k][f]);
+        }
+        Y[k].h = fused(cy, kv[0], qo[k][0]);
+        Y[k].u = fused(cy, kv[1], qo[k][1]);
+        Y[k].v = fused(cy, kv[2], qo[k][2]);
+        Y[k].w = fused(cy, kv[3], qo[k][3]);
+        Y[k].eta = fused(cy, kv[4], qo[k][4]);
+        Y[k].b = cn.b;
+        if (KEEP) {
+          ih[k] = recip_staged(Y[k].h);
+          Y[k].e = node_e(Y[k].h, Y[k].eta, ih[k]);
+        }
+        if (SAVE && i < nx && j < ny) {
+          T* ys = ysave + (size_t)(st - 1) * 5 * N + o;
+          ys[0] = Y[k].h;
+          ys[N] = Y[k].u;
+          ys[2 * N] = Y[k].v;
+          ys[3 * N] = Y[k].w;
+          ys[4 * N] = Y[k].eta;
+        }
+      } else {
         T nv[5];
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
-          nv[f] = acc[k][f] + ca * kv[f];
+          nv[f] = fused(ca, kv[f], acc[k][f]);
           qout[f * N + o] = nv[f];
         }
         if constexpr (RK == RK_FSAL) {
 #pragma unroll
-          for (int f = 0; f < 5; ++f) fx->e[f * N + o] = ca * kv[f] - fx->ce1 * k1o[k][f];
+          for (int f = 0; f < 5; ++f) fx->e[f * N + o] = fused(-fx->ce1, k1o[f], ca * kv[f]);
         } else {
           if (!(nv[0] > T(0))) health |= FLAG_NONPOS;
           const T sum = nv[0] + nv[1] + nv[2] + nv[3] + nv[4];
@@ -397,10 +468,9 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
         }
         if (EPI == EPI_TOTALS) {
           const double M = axis_weight(i, nx, gc.bc_x, gc.dx) * axis_weight(j, ny, gc.bc_y, gc.dy);
-          const double bb = (double)s.f[5][ly0 + k + STEP_HALO][lx + STEP_HALO];
           rsum[0].add(M * (double)nv[0]);
           rsum[1].add(M * energy_density((double)nv[0], (double)nv[1], (double)nv[2], (double)nv[3], (double)nv[4],
-                                         bb, gc.g, gc.lam));
+                                         (double)cn.b, gc.g, gc.lam));
         }
         if (EPI == EPI_RELAX) {
           double x[5], d[5];
@@ -410,74 +480,28 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
             d[f] = (double)nv[f] - x[f];
           }
           double sv, dsv;
-          relax_node_terms(x, d, (double)s.f[5][ly0 + k + STEP_HALO][lx + STEP_HALO], gc.g, gc.lam, 1.0, sv, dsv);
+          relax_node_terms(x, d, (double)cn.b, gc.g, gc.lam, 1.0, sv, dsv);
           const double M = axis_weight(i, nx, gc.bc_x, gc.dx) * axis_weight(j, ny, gc.bc_y, gc.dy);
           rsum[0].add(M * sv);
           rsum[1].add(M * dsv);
         }
       }
-    };
-    {
-      __builtin_amdgcn_sched_barrier(0);
-      const int j = j0 + ly0;
-      // node 1 in the domain implies node 0 in the domain
-      const bool run0 = st < 4 ? own_dom[0] : (i < nx && j < ny);
-      const bool run1 = st < 4 ? own_dom[1] : (i < nx && j + 1 < ny);
-      if (run0) {
-        const int r = ly0 + STEP_HALO, c = lx + STEP_HALO;
-        const AxisStencil<BCX> ax(i, nx, gc.inv2dx, gc.invdx);
-        const AxisStencil<BCY> ay0(j, ny, gc.inv2dy, gc.invdy);
-        const Node<T> c0 = lds_load<T>(s, r, c);
-        const Node<T> up = lds_load<T>(s, r + ay0.op, c);
-        {
-          const Node<T> xm = lds_load<T>(s, r, c + ax.om);
-          const Node<T> xp = lds_load<T>(s, r, c + ax.op);
-          const Node<T> dn = lds_load<T>(s, r + ay0.om, c);
-          finish(0, node_rates<T, BCX, BCY, SRC>(c0, xm, xp, dn, up, ax, ay0, i, j, gc, ts), c0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (run1) {
-          // Node 1 re-enters the shared nodes as opaque values: products of
-          // them formed for node 0 are formed again, rounded exactly as every
-          // other evaluation of the right-hand side rounds them.
-          const Node<T> c0n = opaque_node(c0), upn = opaque_node(up);
-          const AxisStencil<BCY> ay1(j + 1, ny, gc.inv2dy, gc.invdy);
-          const Node<T> xm = lds_load<T>(s, r + 1, c + ax.om);
-          const Node<T> xp = lds_load<T>(s, r + 1, c + ax.op);
-          const Node<T> up1 = lds_load<T>(s, r + 1 + ay1.op, c);
-          finish(1, node_rates<T, BCX, BCY, SRC>(upn, xm, xp, c0n, up1, ax, ay1, i, j + 1, gc, ts), upn);
-          if constexpr (NO == 3) {
-            __builtin_amdgcn_sched_barrier(0);
-            const bool run2 = st < 4 ? own_dom[2] : (i < nx && j + 2 < ny);
-            if (run2) {
-              // node 1's centre re-enters as an opaque value; node 2's own
-              // centre is read again (taking it from node 1's upper neighbour
-              // changes how node 1's arithmetic is fused)
-              const Node<T> c1n = opaque_node(upn);
-              const AxisStencil<BCY> ay2(j + 2, ny, gc.inv2dy, gc.invdy);
-              const Node<T> c2 = lds_load<T>(s, r + 2, c);
-              const Node<T> xm2 = lds_load<T>(s, r + 2, c + ax.om);
-              const Node<T> xp2 = lds_load<T>(s, r + 2, c + ax.op);
-              const Node<T> up2 = lds_load<T>(s, r + 2 + ay2.op, c);
-              finish(2, node_rates<T, BCX, BCY, SRC>(c2, xm2, xp2, c1n, up2, ax, ay2, i, j + 2, gc, ts), c2);
-            }
-          }
-        }
-      }
     }
     if (st == 4) break;
     // ring nodes inside this stage's region
+    T rr[NR][5], re[NR], rb[NR];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < NR; ++k) {
       __builtin_amdgcn_sched_barrier(0);
       const int m = tid + k * STAGE_THREADS;
       if (m >= ring_lim || !ring_ok[k]) continue;
-      Node<T> cn;
-      const Rates<T> kk = tile_eval<T, BCX, BCY, SRC>(s, ring_r[k] + STEP_HALO, ring_c[k] + STEP_HALO,
-                                                      i0 + ring_c[k], j0 + ring_r[k], gc, ts, cn);
-      const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
-      if constexpr (RK != RK_FSAL) {
-        if (st == 1) {
+      const int r = ring_r[k] + STEP_HALO, c = ring_c[k] + STEP_HALO;
+      const AxisStencil<BCX> axr(i0 + ring_c[k], nx, gc.inv2dx, gc.invdx);
+      const AxisStencil<BCY> ayr(j0 + ring_r[k], ny, gc.inv2dy, gc.invdy);
+      const Node<T> cn = s.load(r, c);
+      if (st == 1) {
+        if (KEEP) ihr[k] = recip_staged(cn.h);
+        if constexpr (RK != RK_FSAL) {
           qr[k][0] = cn.h;
           qr[k][1] = cn.u;
           qr[k][2] = cn.v;
@@ -485,8 +509,20 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
           qr[k][4] = cn.eta;
         }
       }
+      const Node<T> xm = s.load(r, c + axr.om);
+      const Node<T> xp = s.load(r, c + axr.op);
+      const Node<T> dn = s.load(r + ayr.om, c);
+      const Node<T> up = s.load(r + ayr.op, c);
+      const Rates<T> kk = node_rates<T, BCX, BCY, SRC>(cn, KEEP ? ihr[k] : recip_staged(cn.h), xm, xp, dn, up, axr,
+                                                       ayr, i0 + ring_c[k], j0 + ring_r[k], gc, ts);
+      const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
 #pragma unroll
-      for (int f = 0; f < 5; ++f) rr[k][f] = qr[k][f] + cy * kv[f];
+      for (int f = 0; f < 5; ++f) rr[k][f] = fused(cy, kv[f], qr[k][f]);
+      if (KEEP) {
+        ihr[k] = recip_staged(rr[k][0]);
+        re[k] = node_e(rr[k][0], rr[k][4], ihr[k]);
+      }
+      rb[k] = cn.b;
     }
     __syncthreads();
     // the stage just formed replaces the one read
@@ -494,18 +530,15 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
     for (int k = 0; k < NO; ++k) {
       if (!own_dom[k]) continue;
       const int r = ly0 + k + STEP_HALO, c = lx + STEP_HALO;
-#pragma unroll
-      for (int f = 0; f < 5; ++f) s.f[f][r][c] = ro[k][f];
-      s.f[6][r][c] = recip_staged(ro[k][0]);
+      const T y[5] = {Y[k].h, Y[k].u, Y[k].v, Y[k].w, Y[k].eta};
+      s.store(r, c, y, KEEP ? Y[k].e : node_e(y[0], y[4], recip_staged(y[0])), Y[k].b);
     }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < NR; ++k) {
       const int m = tid + k * STAGE_THREADS;
       if (m >= ring_lim || !ring_ok[k]) continue;
       const int r = ring_r[k] + STEP_HALO, c = ring_c[k] + STEP_HALO;
-#pragma unroll
-      for (int f = 0; f < 5; ++f) s.f[f][r][c] = rr[k][f];
-      s.f[6][r][c] = recip_staged(rr[k][0]);
+      s.store(r, c, rr[k], KEEP ? re[k] : node_e(rr[k][0], rr[k][4], recip_staged(rr[k][0])), rb[k]);
     }
     __syncthreads();
   }

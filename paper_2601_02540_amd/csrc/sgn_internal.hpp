@@ -105,12 +105,14 @@ hipError_t enqueue_pair_step(const sgn_ctx* c, hipStream_t s, void* cur, void* o
 // with `ysave` non-null the stage states Y2, Y3, Y4 go to three consecutive
 // state slots there; with `rpart` non-null each tile's epilogue sums `epi`
 // (sgn::EPI_RELAX: relaxation sums at gam = 1; sgn::EPI_TOTALS: mass and
-// energy of the new state) go to rpart[4 tile ..] (step_tiles(c) tiles).
+// energy of the new state) go to rpart[4 tile ..] (step_parts(c, epi) of them).
 // Neither with source terms, and not both.
 hipError_t enqueue_step_into(const sgn_ctx* c, hipStream_t s, const void* cur, void* oth, double dt, double t,
                              void* ysave, double* rpart = nullptr, int epi = 0);
-// Number of tiles of the step kernel in the current tile shape.
-int step_tiles(const sgn_ctx* c);
+// The tile shape a step kernel of this context runs (24: 32 x 24, ...).
+int tile_of(const sgn_ctx* c);
+// Number of epilogue sums (4 doubles each) a step with epilogue `epi` leaves.
+int step_parts(const sgn_ctx* c, int epi);
 // Makes c->tile_partials hold the epilogue sums of either tile shape
 // (synchronizes and drops the graphs that captured an older buffer).
 sgn_status ensure_tile_partials(sgn_ctx* c);

@@ -181,7 +181,11 @@ hipError_t launch_fused_ty(const sgn_ctx* c, hipStream_t s, const void* qin, voi
   } while (0)
 #define SGN_LAUNCH(BX, BY, S) SGN_LAUNCH_K(BX, BY, S, false, sgn::EPI_NONE)
   const int bx = c->p.bc_x, by = c->p.bc_y;
-  if (rpart && epi == sgn::EPI_RELAX) {  // relaxation sums (no source terms, no stage saving)
+  if constexpr (TY == 24 && sizeof(T) == 8) {  // periodic only (tile_of), no source, no stage saving
+    if (rpart && epi == sgn::EPI_RELAX) SGN_LAUNCH_K(0, 0, false, false, sgn::EPI_RELAX);
+    else if (rpart) SGN_LAUNCH_K(0, 0, false, false, sgn::EPI_TOTALS);
+    else SGN_LAUNCH(0, 0, false);
+  } else if (rpart && epi == sgn::EPI_RELAX) {  // relaxation sums (no source terms, no stage saving)
     if (bx == 0 && by == 0) SGN_LAUNCH_K(0, 0, false, false, sgn::EPI_RELAX);
     else if (bx == 0 && by == 1) SGN_LAUNCH_K(0, 1, false, false, sgn::EPI_RELAX);
     else if (bx == 1 && by == 0) SGN_LAUNCH_K(1, 0, false, false, sgn::EPI_RELAX);
@@ -222,7 +226,7 @@ hipError_t launch_fused_ty(const sgn_ctx* c, hipStream_t s, const void* qin, voi
 // every tile shape forms the same values.
 hipError_t launch_fused(const sgn_ctx* c, hipStream_t s, const void* qin, void* qout, double dt, double t0,
                         void* ysave = nullptr, double* rpart = nullptr, int epi = sgn::EPI_NONE) {
-  const int ty = c->step_tile == 24 && (ysave || c->p.source == SGN_SRC_MMS) ? 16 : c->step_tile;
+  const int ty = sgn_host::tile_of(c) == 24 && (ysave || c->p.source == SGN_SRC_MMS) ? 16 : sgn_host::tile_of(c);
   if (c->p.dtype == SGN_F64) {
     if (ty == 24) return launch_fused_ty<double, 24>(c, s, qin, qout, dt, t0, ysave, rpart, epi);
     if (ty == 16) return launch_fused_ty<double, 16>(c, s, qin, qout, dt, t0, ysave, rpart, epi);
@@ -365,8 +369,14 @@ hipError_t enqueue_step_into(const sgn_ctx* c, hipStream_t s, const void* cur, v
   return ::launch_fused(c, s, cur, oth, dt, t, ysave, rpart, epi);
 }
 
-int step_tiles(const sgn_ctx* c) {
-  const int ty = c->step_tile;
+int tile_of(const sgn_ctx* c) {
+  // FP64 32 x 24 tiles with a wall would need more than 256 registers
+  const bool wall = c->p.bc_x == SGN_REFLECTING || c->p.bc_y == SGN_REFLECTING;
+  return c->step_tile == 24 && c->p.dtype == SGN_F64 && wall ? 16 : c->step_tile;
+}
+
+int step_parts(const sgn_ctx* c, int) {
+  const int ty = tile_of(c);
   const int tx = ty == 8 ? sgn::StepGeom<8>::TX : sgn::StepGeom<16>::TX;
   return ((c->p.nx + tx - 1) / tx) * ((c->p.ny + ty - 1) / ty);
 }

@@ -7,7 +7,7 @@
 //   pair 2:  k3 = f(Yb) on the tile plus ring,  Ya = q + dt k3
 //            k4 = f(Ya) on the tile:  q_new = acc + dt/3 k3 + dt/6 k4
 // The intermediate stage Ya never leaves LDS.  A workgroup stages its
-// 64 x TY tile with a two-node halo of (h, u, v, w, eta, b, 1/h); after the
+// 64 x TY tile with a two-node halo of (h, u, v, w, eta, b, e); after the
 // first evaluation the intermediate values overwrite the input planes in place
 // (b is kept), and the second evaluation reads them.  HBM traffic per step is
 // 37 values per node instead of 84 for four separate stage kernels.
@@ -23,7 +23,7 @@ namespace sgn {
 
 template <typename T, int TY>
 struct PairSmem {
-  T f[7][TY + 4][TILE_X + 4];  // h u v w eta b 1/h  (later: the intermediate stage, b kept)
+  T f[7][TY + 4][TILE_X + 4];  // h u v w eta b e  (later: the intermediate stage, b kept)
 };
 
 template <int BC>
@@ -48,7 +48,7 @@ __device__ __forceinline__ bool on_axis(int g, int n) {
 }
 
 // The seven staged values of LDS position (r, c).  `Smem` holds the planes
-// h u v w eta b 1/h as f[7][rows][cols].
+// h u v w eta b e as f[7][rows][cols].
 template <typename T, class Smem>
 __device__ __forceinline__ Node<T> lds_load(const Smem& s, int r, int c) {
   Node<T> n;
@@ -58,17 +58,18 @@ __device__ __forceinline__ Node<T> lds_load(const Smem& s, int r, int c) {
   n.w = s.f[3][r][c];
   n.eta = s.f[4][r][c];
   n.b = s.f[5][r][c];
-  n.ih = s.f[6][r][c];
+  n.e = s.f[6][r][c];
   return n;
 }
 
-// Right-hand side at node (i, j) (unwrapped indices) from its value and its four
-// neighbours as the stencils ax, ay select them (closure rows included).
+// Right-hand side at node (i, j) (unwrapped indices) from its value, ih =
+// recip_staged of its depth and its four neighbours as the stencils ax, ay
+// select them (closure rows included).
 template <typename T, int BCX, int BCY, bool SRC>
-__device__ __forceinline__ Rates<T> node_rates(const Node<T>& center, const Node<T>& xm, const Node<T>& xp,
-                                               const Node<T>& ym, const Node<T>& yp, const AxisStencil<BCX>& ax,
-                                               const AxisStencil<BCY>& ay, int i, int j, const GridConst& gc,
-                                               double t) {
+__device__ __forceinline__ Rates<T> node_rates(const Node<T>& center, T ih, const Node<T>& xm,
+                                               const Node<T>& xp, const Node<T>& ym, const Node<T>& yp,
+                                               const AxisStencil<BCX>& ax, const AxisStencil<BCY>& ay, int i, int j,
+                                               const GridConst& gc, double t) {
   T satx = T(0), saty = T(0);
   if (BCX == BC_REFLECTING) {
     if (i == 0) satx = T(-2.0 * gc.invdx);
@@ -78,8 +79,8 @@ __device__ __forceinline__ Rates<T> node_rates(const Node<T>& center, const Node
     if (j == 0) saty = T(-2.0 * gc.invdy);
     if (j == gc.ny - 1) saty = T(2.0 * gc.invdy);
   }
-  Rates<T> k = split_form_rates<T, BCX, BCY>(center, xm, xp, ym, yp, T(ax.scale), T(ay.scale), T(gc.g), T(gc.lam),
-                                             satx, saty);
+  Rates<T> k = split_form_rates<T, BCX, BCY>(center, ih, xm, xp, ym, yp, T(ax.scale), T(ay.scale), T(gc.g),
+                                             T(gc.lam), satx, saty);
   if (SRC) {
     const int gi = wrap_or_clamp<BCX>(i, gc.nx), gj = wrap_or_clamp<BCY>(j, gc.ny);
     double S[5];
@@ -104,7 +105,7 @@ __device__ __forceinline__ Rates<T> tile_eval(const Smem& s, int r, int c, int i
   const Node<T> xp = lds_load<T>(s, r, c + ax.op);
   const Node<T> ym = lds_load<T>(s, r + ay.om, c);
   const Node<T> yp = lds_load<T>(s, r + ay.op, c);
-  return node_rates<T, BCX, BCY, SRC>(center, xm, xp, ym, yp, ax, ay, i, j, gc, t);
+  return node_rates<T, BCX, BCY, SRC>(center, recip_staged(center.h), xm, xp, ym, yp, ax, ay, i, j, gc, t);
 }
 
 // One tile (origin i0, j0) of a stage pair, executed by a whole workgroup.
@@ -142,13 +143,14 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
     const int gj = wrap_or_clamp<BCY>(j0 - 2 + rr, ny);
     const size_t o = (size_t)gj * nx + gi;
     const T h = Yin[o];
+    const T eta = Yin[4 * N + o];
     s.f[0][rr][cc] = h;
     s.f[1][rr][cc] = Yin[N + o];
     s.f[2][rr][cc] = Yin[2 * N + o];
     s.f[3][rr][cc] = Yin[3 * N + o];
-    s.f[4][rr][cc] = Yin[4 * N + o];
+    s.f[4][rr][cc] = eta;
     s.f[5][rr][cc] = bplane[o];
-    s.f[6][rr][cc] = recip_staged(h);
+    s.f[6][rr][cc] = node_e(h, eta, recip_staged(h));
   }
 
   // Own-node operands fetched before the barrier.
@@ -229,14 +231,14 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
         base[k][f] = yv[f];
-        accr[k][f] = yv[f] + c1_acc * kv[f];
-        mid[k][f] = yv[f] + c1_y * kv[f];
+        accr[k][f] = fused(c1_acc, kv[f], yv[f]);
+        mid[k][f] = fused(c1_y, kv[f], yv[f]);
       }
     } else {
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        accr[k][f] = accr[k][f] + c1_acc * kv[f];
-        mid[k][f] = base[k][f] + c1_y * kv[f];
+        accr[k][f] = fused(c1_acc, kv[f], accr[k][f]);
+        mid[k][f] = fused(c1_y, kv[f], base[k][f]);
       }
     }
   }
@@ -248,7 +250,7 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
     const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
     const T yv[5] = {cnode.h, cnode.u, cnode.v, cnode.w, cnode.eta};
 #pragma unroll
-    for (int f = 0; f < 5; ++f) ring_mid[f] = (PAIR == 1 ? yv[f] : ring_base[f]) + c1_y * kv[f];
+    for (int f = 0; f < 5; ++f) ring_mid[f] = fused(c1_y, kv[f], PAIR == 1 ? yv[f] : ring_base[f]);
   }
   __syncthreads();
 #pragma unroll
@@ -264,12 +266,12 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
     }
 #pragma unroll
     for (int f = 0; f < 5; ++f) s.f[f][r][c] = mid[k][f];
-    s.f[6][r][c] = recip_staged(mid[k][0]);
+    s.f[6][r][c] = node_e(mid[k][0], mid[k][4], recip_staged(mid[k][0]));
   }
   if (ring_valid) {
 #pragma unroll
     for (int f = 0; f < 5; ++f) s.f[f][ring_r][ring_c] = ring_mid[f];
-    s.f[6][ring_r][ring_c] = recip_staged(ring_mid[0]);
+    s.f[6][ring_r][ring_c] = node_e(ring_mid[0], ring_mid[4], recip_staged(ring_mid[0]));
   }
   __syncthreads();
 
@@ -288,15 +290,15 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
     if (PAIR == 1) {
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        acc_io[f * N + o] = accr[k][f] + c2_acc * kv[f];
-        yb_out[f * N + o] = base[k][f] + c2_y * kv[f];
+        acc_io[f * N + o] = fused(c2_acc, kv[f], accr[k][f]);
+        yb_out[f * N + o] = fused(c2_y, kv[f], base[k][f]);
       }
     } else {
       T nv[5];
       T* dst = SAVE ? qout : acc_io;
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        nv[f] = accr[k][f] + c2_acc * kv[f];
+        nv[f] = fused(c2_acc, kv[f], accr[k][f]);
         dst[f * N + o] = nv[f];
       }
       if (!(nv[0] > T(0))) health |= FLAG_NONPOS;

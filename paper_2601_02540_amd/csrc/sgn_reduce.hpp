@@ -29,7 +29,7 @@ enum : int {
 // of one node (Theorem 2's E, whose M-weighted sum is the total energy).
 __device__ __forceinline__ double energy_density(double h, double u, double v, double w, double eta, double b,
                                                  double g, double lam) {
-  const double rm1 = eta * (1.0 / h) - 1.0;
+  const double rm1 = (eta - h) * recip_staged(h);  // eta/h - 1 without cancellation
   const double e = w * w * (1.0 / 6.0) + 0.5 * g * (h + 2.0 * b) + lam * (1.0 / 6.0) * rm1 * rm1;
   return h * (0.5 * (u * u + v * v) + e);
 }

@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void relax_update(size_t n5, T* out, const T* 
   if (k >= n5) return;
   const T gam = T(rs[0]);
   const T x = q[k];
-  out[k] = x + gam * (qrk[k] - x);
+  out[k] = fused(gam, qrk[k] - x, x);
 }
 
 // One RK4 step of a relaxation run after its first: the step tile stages the

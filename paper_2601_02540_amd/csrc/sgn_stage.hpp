@@ -2,14 +2,12 @@
 //
 // One workgroup of 256 threads (four wave64s) owns a tile of 64 x TY nodes.
 // It stages the tile plus a one-node halo of the six input planes
-// (h, u, v, w, eta, b) and of 1/h in LDS, with the periodic wrap or the
-// reflecting clamp applied while loading.  Each thread then evaluates the
+// (h, u, v, w, eta, b) and of (eta - h)^2/h in LDS, with the periodic wrap or
+// the reflecting clamp applied while loading.  Each thread then evaluates the
 // split-form rates of eq. (sd_periodic_2D_SGN) / eq. (semi_2D) for TY/4 nodes
 // of one column, with the one-sided closure rows and the wall SATs of Remark
 // "Concrete SBP operators and SATs" resolved per node, and applies the stage
-// update in registers.  Products that are differentiated (h(h+b), u^2, hu,
-// huv, eta^2/h, huw, ...) are formed at the two neighbours from LDS values, so
-// only one reciprocal per node is computed.
+// update in registers.
 #pragma once
 
 #include "sgn_common.hpp"
@@ -46,14 +44,25 @@ struct AxisStencil {
   }
 };
 
+// A node as the right-hand side reads it: the state, the bottom and
+// e = (eta - h)^2 / h, the only quantity of a neighbour that needs a division
+// (formed once per node and stage, where the node is staged).
 template <typename T>
 struct Node {
-  T h, u, v, w, eta, b, ih;  // ih = 1/h
+  T h, u, v, w, eta, b, e;
 };
+
+// e of a staged node; ih = recip_staged(h).
+template <typename T>
+__device__ __forceinline__ T node_e(T h, T eta, T ih) {
+#pragma clang fp contract(off)
+  const T d = eta - h;
+  return (d * d) * ih;
+}
 
 template <typename T, int TY>
 struct StageSmem {
-  T f[7][TY + 2][TILE_X + 2];  // h u v w eta b 1/h
+  T f[7][TY + 2][TILE_X + 2];  // h u v w eta b e
 };
 
 template <typename T, int TY>
@@ -65,9 +74,12 @@ __device__ __forceinline__ Node<T> lds_node(const StageSmem<T, TY>& s, int r, in
   n.w = s.f[3][r][c];
   n.eta = s.f[4][r][c];
   n.b = s.f[5][r][c];
-  n.ih = s.f[6][r][c];
+  n.e = s.f[6][r][c];
   return n;
 }
+
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // Rates of the five evolved variables at one node given its value, its four
 // neighbours (already resolved for closures) and the derivative scales.
@@ -76,80 +88,114 @@ struct Rates {
   T h, u, v, w, eta;
 };
 
-// Every derivative along one axis at a node carries the same scale (1/(2d) on
-// interior and periodic rows, 1/d on a closure row), so the differences are
-// formed unscaled, the x- and y-terms of each rate are summed separately and
-// each sum is scaled once.  The wall SAT enters only on reflecting axes.
+// The terms of one axis at a node: n is the velocity along the axis, t the one
+// across.  With the sums over the two neighbours m = +, - written S(f_m) =
+// f_+ - f_- (one-sided rows name the node itself as a neighbour; S(1) = 0), the
+// split form of the axis is
+//   dR = S(n h_m + h n_m)                               D-part of h_t
+//   A2 = h S(n_m^2) - n^2 S(h_m) + n S(h_m n_m) - h n S(n_m)
+//      = h S(n_m) (n_+ + n_-) + n (S(Q_m) - dR)         Q_m = h_m n_m + h n
+//   Tf = S(h_m n_m f_m) - n f S(h_m) + h n S(f_m) - h f S(n_m)
+//      = S(Q_m f_m) - f dR                              f = t, w
+//   P  = S(h_m (h_m + b_m)) - (h + b) S(h_m) = S(h_m (zeta_m - zeta))
+//   relaxation, r = eta/h - 1: lambda/3 R - lambda r S(b_m) is twice
+//      lambda/6 (eta^2/h^2 S(h_m) - S(eta_m^2/h_m)) - lambda/3 r S(eta_m)
+//      - lambda/2 r S(b_m), with R = r^2 S(h_m) - (2 + 2 r) S(eta_m - h_m) - S(e_m)
+// A = 2 g P + A2 + lambda/3 R - lambda r S(b), so that h n_t = -s/2 A + (cross
+// axis); E = S(eta) + 3/2 S(b).  Each line is exact algebra on the printed
+// sums, with products shared between the rates and none formed twice per
+// neighbour; the small differences (S(h), S(n), zeta_m - zeta, eta - h) are
+// formed first, so a state at rest gives exact zeros.
+template <typename T>
+struct AxisTerms {
+  T dR, A, Tt, Tw, E;
+};
+
+template <typename T>
+__device__ __forceinline__ AxisTerms<T> axis_terms(T h, T n, T hn, T t, T w, T H, T r2, T c2, T lamr, T g2, T lam3,
+                                                   T mh, T mn, T mt, T mw, T meta, T mb, T me, T ph, T pn, T pt, T pw,
+                                                   T peta, T pb, T pe) {
+#pragma clang fp contract(off)
+  AxisTerms<T> o;
+  const T dh = ph - mh;
+  const T dn = pn - mn;
+  const T hdn = h * dn;
+  o.dR = fused(n, dh, hdn);
+  const T Qp = fused(ph, pn, hn);
+  const T Qm = fused(mh, mn, hn);
+  const T A2 = fused(hdn, pn + mn, n * ((Qp - Qm) - o.dR));
+  o.Tt = fused(Qp, pt, fused(-Qm, mt, -(t * o.dR)));
+  o.Tw = fused(Qp, pw, fused(-Qm, mw, -(w * o.dR)));
+  const T P = fused((ph + pb) - H, ph, -(((mh + mb) - H) * mh));
+  const T deta = peta - meta;
+  const T db = pb - mb;
+  const T R = fused(-c2, deta - dh, fused(r2, dh, me - pe));
+  o.A = fused(-lamr, db, fused(lam3, R, fused(g2, P, A2)));
+  o.E = fused(T(1.5), db, deta);
+  return o;
+}
+
+// What the axis terms and the rates share of a node's own values.
+template <typename T>
+struct CenterTerms {
+  T hu, hv, H, r2, c2, lamr;
+  __device__ __forceinline__ CenterTerms(const Node<T>& c, T ih, T lam) {
+#pragma clang fp contract(off)
+    hu = c.h * c.u;
+    hv = c.h * c.v;
+    H = c.h + c.b;
+    const T r = (c.eta - c.h) * ih;
+    r2 = r * r;
+    c2 = fused(T(2), r, T(2));
+    lamr = lam * r;
+  }
+};
+
+template <typename T>
+__device__ __forceinline__ AxisTerms<T> x_terms(const Node<T>& c, const CenterTerms<T>& t, const Node<T>& m,
+                                                const Node<T>& p, T g, T lam) {
+  return axis_terms<T>(c.h, c.u, t.hu, c.v, c.w, t.H, t.r2, t.c2, t.lamr, T(2) * g, lam * T(1.0 / 3.0), m.h, m.u, m.v,
+                       m.w, m.eta, m.b, m.e, p.h, p.u, p.v, p.w, p.eta, p.b, p.e);
+}
+
+template <typename T>
+__device__ __forceinline__ AxisTerms<T> y_terms(const Node<T>& c, const CenterTerms<T>& t, const Node<T>& m,
+                                                const Node<T>& p, T g, T lam) {
+  return axis_terms<T>(c.h, c.v, t.hv, c.u, c.w, t.H, t.r2, t.c2, t.lamr, T(2) * g, lam * T(1.0 / 3.0), m.h, m.v, m.u,
+                       m.w, m.eta, m.b, m.e, p.h, p.v, p.u, p.w, p.eta, p.b, p.e);
+}
+
+// The rates from the terms of the two axes.  Every derivative along one axis
+// at a node carries the same scale (1/(2d) on interior and periodic rows, 1/d on
+// a closure row), applied once per axis sum.  The wall SAT enters only on
+// reflecting axes.
 template <typename T, int BCX, int BCY>
-__device__ __forceinline__ Rates<T> split_form_rates(const Node<T>& c, const Node<T>& xm, const Node<T>& xp,
+__device__ __forceinline__ Rates<T> join_rates(const Node<T>& c, T ih, const CenterTerms<T>& t, const AxisTerms<T>& x,
+                                               const AxisTerms<T>& y, T sx, T sy, T satx_coef, T saty_coef) {
+#pragma clang fp contract(off)
+  const T hsx = T(0.5) * sx, hsy = T(0.5) * sy;
+  Rates<T> k;
+  k.h = fused(-sx, x.dR, -(sy * y.dR));
+  if (BCX == BC_REFLECTING) k.h = fused(satx_coef, t.hu, k.h);
+  if (BCY == BC_REFLECTING) k.h = fused(saty_coef, t.hv, k.h);
+  k.u = fused(-hsx, x.A, -(hsy * y.Tt)) * ih;
+  k.v = fused(-hsy, y.A, -(hsx * x.Tt)) * ih;
+  k.w = (fused(-hsx, x.Tw, -(hsy * y.Tw)) - t.lamr) * ih;
+  k.eta = fused(-(c.u * sx), x.E, fused(-(c.v * sy), y.E, c.w));
+  return k;
+}
+
+// Rates at node c; ih = recip_staged(c.h).  All multiply-adds are written out
+// and the compiler forms no others, so every kernel rounds an evaluation alike,
+// whatever surrounds it.
+template <typename T, int BCX, int BCY>
+__device__ __forceinline__ Rates<T> split_form_rates(const Node<T>& c, T ih, const Node<T>& xm, const Node<T>& xp,
                                                      const Node<T>& ym, const Node<T>& yp, T sx, T sy, T g, T lam,
                                                      T satx_coef, T saty_coef) {
-  const T half = T(0.5);
-  // x differences (12), unscaled
-  const T dxh = xp.h - xm.h;
-  const T dxu = xp.u - xm.u;
-  const T dxv = xp.v - xm.v;
-  const T dxw = xp.w - xm.w;
-  const T dxeta = xp.eta - xm.eta;
-  const T dxb = xp.b - xm.b;
-  const T dxhH = xp.h * (xp.h + xp.b) - xm.h * (xm.h + xm.b);
-  const T dxu2 = xp.u * xp.u - xm.u * xm.u;
-  const T xphu = xp.h * xp.u, xmhu = xm.h * xm.u;
-  const T dxhu = xphu - xmhu;
-  const T dxhuv = xphu * xp.v - xmhu * xm.v;
-  // D(eta^2/h) = D(h) + D((eta - h)(eta + h)/h): the second part is small
-  // (eta stays close to h), so it is formed without cancellation
-  const T dxe2c = (xp.eta - xp.h) * (xp.eta + xp.h) * xp.ih - (xm.eta - xm.h) * (xm.eta + xm.h) * xm.ih;
-  const T dxhuw = xphu * xp.w - xmhu * xm.w;
-  // y differences (12), unscaled
-  const T dyh = yp.h - ym.h;
-  const T dyu = yp.u - ym.u;
-  const T dyv = yp.v - ym.v;
-  const T dyw = yp.w - ym.w;
-  const T dyeta = yp.eta - ym.eta;
-  const T dyb = yp.b - ym.b;
-  const T dyhH = yp.h * (yp.h + yp.b) - ym.h * (ym.h + ym.b);
-  const T dyv2 = yp.v * yp.v - ym.v * ym.v;
-  const T yphv = yp.h * yp.v, ymhv = ym.h * ym.v;
-  const T dyhv = yphv - ymhv;
-  const T dyhuv = yphv * yp.u - ymhv * ym.u;
-  const T dye2c = (yp.eta - yp.h) * (yp.eta + yp.h) * yp.ih - (ym.eta - ym.h) * (ym.eta + ym.h) * ym.ih;
-  const T dyhvw = yphv * yp.w - ymhv * ym.w;
-
-  const T h = c.h, u = c.u, v = c.v, w = c.w, eta = c.eta;
-  const T H = h + c.b;
-  // r - 1 = (eta - h)/h and r^2 - 1 = (r - 1)(r + 1), formed from eta - h, so
-  // that a state at rest (eta = h) gives exactly zero relaxation terms
-  const T rm1 = (eta - h) * c.ih;
-  const T omr = -rm1;
-  const T r2m1 = rm1 * (rm1 + T(2));
-  const T hu = h * u, hv = h * v, uv = u * v, hw = h * w;
-  const T lam6 = lam * T(1.0 / 6.0), lam3 = lam * T(1.0 / 3.0), lam2 = lam * T(0.5);
-  const T hsx = half * sx, hsy = half * sy;
-
-  Rates<T> k;
-  k.h = -(sx * (u * dxh + h * dxu) + sy * (v * dyh + h * dyv));
-  if (BCX == BC_REFLECTING) k.h += satx_coef * hu;
-  if (BCY == BC_REFLECTING) k.h += saty_coef * hv;
-
-  // A = h u_t, B = h v_t (with the sign of the rates), C = the flux part of h w_t
-  // lambda/6 (r^2 D h - D(eta^2/h)) = lambda/6 ((r^2 - 1) D h - D((eta - h)(eta + h)/h))
-  const T Ax = g * (dxhH - H * dxh) + lam6 * (r2m1 * dxh - dxe2c) + lam3 * omr * dxeta + lam2 * omr * dxb;
-  const T Ax2 = h * dxu2 - u * u * dxh + u * dxhu - hu * dxu;
-  const T Ay2 = dyhuv - uv * dyh + hv * dyu - hu * dyv;
-  const T A = sx * Ax + hsx * Ax2 + hsy * Ay2;
-  const T By = g * (dyhH - H * dyh) + lam6 * (r2m1 * dyh - dye2c) + lam3 * omr * dyeta + lam2 * omr * dyb;
-  const T By2 = h * dyv2 - v * v * dyh + v * dyhv - hv * dyv;
-  const T Bx2 = dxhuv - uv * dxh + hu * dxv - hv * dxu;
-  const T B = sy * By + hsy * By2 + hsx * Bx2;
-  const T Cx = dxhuw + hu * dxw - u * w * dxh - hw * dxu;
-  const T Cy = dyhvw + hv * dyw - v * w * dyh - hw * dyv;
-  const T C = hsx * Cx + hsy * Cy;
-  k.u = -A * c.ih;
-  k.v = -B * c.ih;
-  k.w = (lam * omr - C) * c.ih;
-  k.eta = w - (sx * (u * dxeta + T(1.5) * u * dxb) + sy * (v * dyeta + T(1.5) * v * dyb));
-  return k;
+  const CenterTerms<T> t(c, ih, lam);
+  const AxisTerms<T> x = x_terms(c, t, xm, xp, g, lam);
+  const AxisTerms<T> y = y_terms(c, t, ym, yp, g, lam);
+  return join_rates<T, BCX, BCY>(c, ih, t, x, y, sx, sy, satx_coef, saty_coef);
 }
 
 template <typename T, int BCX, int BCY, int MODE, bool SRC, int TY>
@@ -196,13 +242,14 @@ __global__ __launch_bounds__(STAGE_THREADS) void stage_kernel(const GridConst gc
     }
     const size_t o = (size_t)gj * nx + gi;
     const T h = Y[o];
+    const T eta = Y[4 * N + o];
     s.f[0][rr][cc] = h;
     s.f[1][rr][cc] = Y[N + o];
     s.f[2][rr][cc] = Y[2 * N + o];
     s.f[3][rr][cc] = Y[3 * N + o];
-    s.f[4][rr][cc] = Y[4 * N + o];
+    s.f[4][rr][cc] = eta;
     s.f[5][rr][cc] = bplane[o];
-    s.f[6][rr][cc] = recip_staged(h);
+    s.f[6][rr][cc] = node_e(h, eta, recip_staged(h));
   }
 
   // Own-node operands of the stage update, fetched before the barrier so the
@@ -252,7 +299,8 @@ __global__ __launch_bounds__(STAGE_THREADS) void stage_kernel(const GridConst gc
     const Node<T> xp = lds_node(s, r, cidx + ax.op);
     const Node<T> ym = lds_node(s, r + ay.om, cidx);
     const Node<T> yp = lds_node(s, r + ay.op, cidx);
-    Rates<T> kk = split_form_rates<T, BCX, BCY>(c, xm, xp, ym, yp, T(ax.scale), T(ay.scale), g, lam, satx, saty);
+    Rates<T> kk = split_form_rates<T, BCX, BCY>(c, recip_staged(c.h), xm, xp, ym, yp, T(ax.scale), T(ay.scale), g, lam,
+                                                satx, saty);
     if (SRC) {
       double S[5];
       mms_source(gc.xmin + i * gc.dx, gc.ymin + j * gc.dy, t, gc.g, S);
@@ -271,20 +319,20 @@ __global__ __launch_bounds__(STAGE_THREADS) void stage_kernel(const GridConst gc
     } else if (MODE == MODE_FIRST) {
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        acc[f * N + o] = yv[f] + c_acc * kv[f];
-        out[f * N + o] = yv[f] + c_y * kv[f];
+        acc[f * N + o] = fused(c_acc, kv[f], yv[f]);
+        out[f * N + o] = fused(c_y, kv[f], yv[f]);
       }
     } else if (MODE == MODE_MID) {
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        acc[f * N + o] = pacc[k][f] + c_acc * kv[f];
-        out[f * N + o] = pre[k][f] + c_y * kv[f];
+        acc[f * N + o] = fused(c_acc, kv[f], pacc[k][f]);
+        out[f * N + o] = fused(c_y, kv[f], pre[k][f]);
       }
     } else {
       T nv[5];
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        nv[f] = pacc[k][f] + c_acc * kv[f];
+        nv[f] = fused(c_acc, kv[f], pacc[k][f]);
         out[f * N + o] = nv[f];
       }
       if (!(nv[0] > T(0))) health |= FLAG_NONPOS;

@@ -30,7 +30,7 @@ hipError_t enqueue_step_with_totals(const sgn_ctx* c, hipStream_t s, void* cur, 
                                     double* series) {
   hipError_t e = sgn_host::enqueue_step_into(c, s, cur, oth, dt, 0.0, nullptr, c->tile_partials, sgn::EPI_TOTALS);
   if (e) return e;
-  const int tiles = sgn_host::step_tiles(c);
+  const int tiles = sgn_host::step_parts(c, sgn::EPI_TOTALS);
   const int per_min = sgn::RED_THREADS;
   int nb = (tiles + per_min - 1) / per_min;
   if (nb > sgn::RED_MAX_BLOCKS) nb = sgn::RED_MAX_BLOCKS;

@@ -38,6 +38,17 @@ namespace sgn {
 enum : int { VJP_PLAIN = 0, VJP_S4 = 4, VJP_S3 = 3, VJP_S2 = 2, VJP_S1 = 1 };
 
 template <typename T>
+struct VNode {
+  T h, u, v, w, eta, b, ih;  // ih = 1/h
+};
+
+template <typename T>
+__device__ __forceinline__ VNode<T> opaque_vnode(VNode<T> n) {
+  asm volatile("" : "+v"(n.h), "+v"(n.u), "+v"(n.v), "+v"(n.w), "+v"(n.eta), "+v"(n.b), "+v"(n.ih));
+  return n;
+}
+
+template <typename T>
 struct Cot {
   T h, u, v, w, eta, b;
   __device__ __forceinline__ void zero() { h = u = v = w = eta = b = T(0); }
@@ -54,7 +65,7 @@ struct Cot {
 // Chain the derivative cotangents amounts a[0..11] of the x-quantities
 // (h u v w eta b h(h+b) u^2 hu huv eta^2/h huw) at node n.
 template <typename T>
-__device__ __forceinline__ Cot<T> chain_x(const Node<T>& n, const T (&a)[12]) {
+__device__ __forceinline__ Cot<T> chain_x(const VNode<T>& n, const T (&a)[12]) {
   Cot<T> c;
   const T e2 = n.eta * n.eta;
   c.h = a[0] + (T(2) * n.h + n.b) * a[6] + n.u * a[8] + n.u * n.v * a[9] - e2 * n.ih * n.ih * a[10] +
@@ -69,7 +80,7 @@ __device__ __forceinline__ Cot<T> chain_x(const Node<T>& n, const T (&a)[12]) {
 
 // Same for the y-quantities (h u v w eta b h(h+b) v^2 hv huv eta^2/h hvw).
 template <typename T>
-__device__ __forceinline__ Cot<T> chain_y(const Node<T>& n, const T (&a)[12]) {
+__device__ __forceinline__ Cot<T> chain_y(const VNode<T>& n, const T (&a)[12]) {
   Cot<T> c;
   const T e2 = n.eta * n.eta;
   c.h = a[0] + (T(2) * n.h + n.b) * a[6] + n.v * a[8] + n.u * n.v * a[9] - e2 * n.ih * n.ih * a[10] +
@@ -88,8 +99,8 @@ __device__ __forceinline__ Cot<T> chain_y(const Node<T>& n, const T (&a)[12]) {
 // itself (below), reach the node's own values only through the diagonal of
 // the operator, i.e. on the reflecting closure rows.
 template <typename T>
-__device__ __forceinline__ void split_form_reverse(const Node<T>& c, const Node<T>& xm, const Node<T>& xp,
-                                                   const Node<T>& ym, const Node<T>& yp, T sx, T sy, T g, T lam,
+__device__ __forceinline__ void split_form_reverse(const VNode<T>& c, const VNode<T>& xm, const VNode<T>& xp,
+                                                   const VNode<T>& ym, const VNode<T>& yp, T sx, T sy, T g, T lam,
                                                    T satx, T saty, const T (&kb)[5], Cot<T>& cen) {
   const T half = T(0.5);
   // forward values
@@ -232,7 +243,7 @@ struct Seed {
 // a node from its own state n and seed a: the factor of each D_x f in the
 // rates of eq. (sd_periodic_2D_SGN), times the seed of that rate.
 template <typename T>
-__device__ __forceinline__ void dbar_x(const Node<T>& n, const Seed<T>& a, T g, T lam, T (&q)[12]) {
+__device__ __forceinline__ void dbar_x(const VNode<T>& n, const Seed<T>& a, T g, T lam, T (&q)[12]) {
   const T half = T(0.5);
   const T ih = n.ih;
   const T Ab = -a.u * ih, Bb = -a.v * ih, Cb = -a.w * ih;
@@ -255,7 +266,7 @@ __device__ __forceinline__ void dbar_x(const Node<T>& n, const Seed<T>& a, T g, 
 
 // Same for the 12 y-quantities (h u v w eta b h(h+b) v^2 hv huv eta^2/h hvw).
 template <typename T>
-__device__ __forceinline__ void dbar_y(const Node<T>& n, const Seed<T>& a, T g, T lam, T (&q)[12]) {
+__device__ __forceinline__ void dbar_y(const VNode<T>& n, const Seed<T>& a, T g, T lam, T (&q)[12]) {
   const T half = T(0.5);
   const T ih = n.ih;
   const T Ab = -a.u * ih, Bb = -a.v * ih, Cb = -a.w * ih;
@@ -290,7 +301,7 @@ struct VjpSmem {
 // With SCALE, the seed planes hold unscaled values and the seeds are formed as
 // sc * plane here (the same product the role kernels store when staging).
 template <typename T, bool SCALE = false, class Smem>
-__device__ __forceinline__ void vjp_lds(const Smem& s, int r, int c, Node<T>& n, Seed<T>& a, T sc = T(1)) {
+__device__ __forceinline__ void vjp_lds(const Smem& s, int r, int c, VNode<T>& n, Seed<T>& a, T sc = T(1)) {
   n.h = s.f[0][r][c];
   n.u = s.f[1][r][c];
   n.v = s.f[2][r][c];
@@ -328,7 +339,7 @@ __device__ __forceinline__ Cot<T> vjp_node(const Smem& s, int r, int c, int i, i
     if (j == 0) saty = T(-2.0 * gc.invdy);
     if (j == ny - 1) saty = T(2.0 * gc.invdy);
   }
-  Node<T> nc, nxm, nxp, nym, nyp;
+  VNode<T> nc, nxm, nxp, nym, nyp;
   Seed<T> ac, axm, axp, aym, ayp;
   vjp_lds<T, SCALE>(s, r, c, nc, ac, sc);
   vjp_lds<T, SCALE>(s, r, c - 1, nxm, axm, sc);
@@ -338,21 +349,21 @@ __device__ __forceinline__ Cot<T> vjp_node(const Smem& s, int r, int c, int i, i
   // Opaque copies: where one thread evaluates neighbouring nodes, the compiler
   // would otherwise share loads and products between the evaluations and fuse
   // the arithmetic differently; every evaluation rounds as a lone one does.
-  nc = opaque_node(nc);
-  nxm = opaque_node(nxm);
-  nxp = opaque_node(nxp);
-  nym = opaque_node(nym);
-  nyp = opaque_node(nyp);
+  nc = opaque_vnode(nc);
+  nxm = opaque_vnode(nxm);
+  nxp = opaque_vnode(nxp);
+  nym = opaque_vnode(nym);
+  nyp = opaque_vnode(nyp);
   ac = opaque_seed(ac);
   axm = opaque_seed(axm);
   axp = opaque_seed(axp);
   aym = opaque_seed(aym);
   ayp = opaque_seed(ayp);
   // local part: reverse of this node's own rates (stencil neighbours with closures)
-  const Node<T>& sxm = ax.om == 0 ? nc : nxm;
-  const Node<T>& sxp = ax.op == 0 ? nc : nxp;
-  const Node<T>& sym = ay.om == 0 ? nc : nym;
-  const Node<T>& syp = ay.op == 0 ? nc : nyp;
+  const VNode<T>& sxm = ax.om == 0 ? nc : nxm;
+  const VNode<T>& sxp = ax.op == 0 ? nc : nxp;
+  const VNode<T>& sym = ay.om == 0 ? nc : nym;
+  const VNode<T>& syp = ay.op == 0 ? nc : nyp;
   const T kb[5] = {ac.h, ac.u, ac.v, ac.w, ac.eta};
   Cot<T> out;
   split_form_reverse<T>(nc, sxm, sxp, sym, syp, T(ax.scale), T(ay.scale), g, lam, satx, saty, kb, out);
