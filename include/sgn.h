@@ -96,17 +96,21 @@ typedef struct sgn_ctx sgn_ctx;
  *     stage stays in LDS.  37 values per node and step.
  *   SGN_PATH_STAGES: four kernels, one per stage.  84 values per node and step.
  *   On the fused and pair paths the state alternates between the caller's
- *   buffer and a context buffer, so steps go in twos; an odd final step runs on
- *   the four-stage path.
+ *   buffer and a context buffer, so steps go in twos.  On the fused path an odd
+ *   count begins with three steps by way of two context buffers, and a single
+ *   step is copied back; on the pair path an odd final step runs on the
+ *   four-stage path.
  * SGN_OPT_TILE_Y: 8, 16 or 24.  Tile height of the stage and pair kernels (64
  *   wide; default 8 for SGN_F64, 16 for SGN_F32) and of the step kernel's tile
  *   (8 selects 64 x 8, 16 selects 32 x 16, 24 selects 32 x 24: three owned
  *   nodes per thread and the fewest redundant ring evaluations; default 24
  *   when the grid holds at least 1024 tiles of 32 x 24, 16 otherwise).
  *   8 and 16 set both; 24 sets the step tile and height 16 for the stage and
- *   pair kernels.  With a 32 x 24 step tile, steps that save stage states or
- *   add source terms, and the adaptive pair's attempt kernel on grids with a
- *   wall, run 32 x 16 tiles.  Every tile shape forms the same values.
+ *   pair kernels.  With 24, grids of 2^20 nodes and more whose width suits it
+ *   step by strips of 56 columns, one wave each, instead of tiles (steps
+ *   without source terms); on tiles, steps that save stage states or add
+ *   source terms, FP64 steps on grids with a wall and the adaptive pair's
+ *   attempt kernel on such grids run 32 x 16.  Every shape forms the same values.
  * SGN_OPT_ADJOINT_STORE: bytes of device memory (>= 0; default 0) that
  *   sgn_gauge_loss_grad may fill with the states and stage states of the last
  *   steps of its forward rollout, so that its reverse sweep need not recompute
@@ -378,9 +382,11 @@ sgn_status sgn_batch_cfl_dt(sgn_batch* batch, double cfl, double* dt);
  * 16 in SGN_F32). */
 sgn_status sgn_batch_set_step_path(sgn_batch* batch, int32_t path);
 /* Tile height (8 or 16, and 24 on the fused path; there 8 selects 64 x 8
- * tiles, 16 selects 32 x 16 and 24 selects 32 x 24) and persistent
+ * tiles, 16 selects 32 x 16, and 24 selects 32 x 24 ones (FP64: 32 x 16) or, where
+ * the ensemble holds 2^20 nodes and more and their shapes suit it, strips of 56
+ * columns, one wave each) and persistent
  * workgroups per compute unit (1..16), or 0 for one workgroup per tile (the
- * default: no persistent loop, fewer registers; the only choice for 32 x 24,
+ * default: no persistent loop, fewer registers; the only choice for 24,
  * SGN_E_UNSUPPORTED otherwise). */
 sgn_status sgn_batch_set_tiling(sgn_batch* batch, int32_t tile_y, int32_t blocks_per_cu);
 /* Time every (tile height 8, 16 or 24 (fused path, one workgroup per tile),

@@ -8,6 +8,7 @@
 
 #include "sgn.h"
 #include "sgn_batch.hpp"
+#include "sgn_internal.hpp"
 #include "sgn_reduce.hpp"
 
 namespace {
@@ -35,7 +36,8 @@ struct sgn_batch {
   sgn::InstDesc* h_desc = nullptr;  // pinned staging
   int* d_work = nullptr;
   int nwork = 0;
-  int work_key = 0;  // path and tile height the work list was built for
+  int work_key = 0;    // path and tiling the work list was built for
+  bool march = false;  // its items are the march kernel's
   int* d_flags = nullptr;
   int* h_flags = nullptr;
   double* d_partials = nullptr;
@@ -82,6 +84,38 @@ void drop_graph(sgn_batch* b) {
   b->gexec = nullptr;
 }
 
+// Runs of rows of each instance when the fused path of tile height 24 is better run by the march kernel (the rule of
+// march_plan, summed over the instances), none otherwise.  The runs are as
+// short as one round of waves over all instances allows.
+std::vector<int> march_chunks(const sgn_batch* b) {
+  std::vector<int> chunks;
+  if (b->path != SGN_PATH_FUSED || b->tile_y != 24 || (int64_t)b->total < sgn_host::MARCH_MIN_NODES) return chunks;
+  const int64_t slots =
+      (int64_t)b->num_cus * 4 * (b->dtype == SGN_F64 ? sgn::march_waves<double>() : sgn::march_waves<float>());
+  std::vector<int64_t> strips(b->n);
+  int64_t rows = 0;
+  for (int i = 0; i < b->n; ++i) {
+    strips[i] = (b->params[i].nx + sgn::MARCH_COLS - 1) / sgn::MARCH_COLS;
+    rows += strips[i] * b->params[i].ny;
+  }
+  const auto tasks = [&](int64_t h) {
+    int64_t n = 0;
+    for (int i = 0; i < b->n; ++i) n += strips[i] * ((b->params[i].ny + h - 1) / h);
+    return n;
+  };
+  int64_t h = std::max<int64_t>(sgn_host::MARCH_MIN_HEIGHT, rows / slots);
+  // the ends of the instances leave a few runs short: grow the height until one round holds them
+  for (int64_t top = 2 * h; h < top && tasks(h) > slots;) h += std::max<int64_t>(1, h / 32);
+  int64_t march = 0, tile = 0;
+  for (int i = 0; i < b->n; ++i) {
+    chunks.push_back((int)std::max<int64_t>(1, (b->params[i].ny + h - 1) / h));
+    march += sgn_host::march_evals(strips[i], b->params[i].ny, chunks.back());
+    tile += sgn_host::tile_evals(b->params[i].nx, b->params[i].ny);
+  }
+  if (!sgn_host::march_pays(march, tile)) chunks.clear();
+  return chunks;
+}
+
 // Tile height that the tile kernels run: FP64 32 x 24 tiles with a wall would need
 // more than 256 registers, so an FP64 ensemble runs 32 x 16 ones in their place.
 int tile_of(const sgn_batch* b) {
@@ -99,10 +133,13 @@ sgn_status build_work(sgn_batch* b) {
   if (b->work_key == work_key(b) && b->d_work) return SGN_OK;
   std::vector<int> work;
   const int tw = tile_width(b), th = tile_of(b);
+  const std::vector<int> chunks = march_chunks(b);
+  // the pinned descriptors may still be read by an earlier asynchronous copy
+  BCHK(b, hipStreamSynchronize(b->stream));
   for (int i = 0; i < b->n; ++i) {
     sgn::InstDesc& d = b->h_desc[i];
-    d.ntx = (b->params[i].nx + tw - 1) / tw;
-    d.nty = (b->params[i].ny + th - 1) / th;
+    d.ntx = chunks.empty() ? (b->params[i].nx + tw - 1) / tw : (b->params[i].nx + sgn::MARCH_COLS - 1) / sgn::MARCH_COLS;
+    d.nty = chunks.empty() ? (b->params[i].ny + th - 1) / th : chunks[i];
     d.tile_base = (int)work.size();
     for (int t = 0; t < d.ntx * d.nty; ++t) work.push_back(i);
   }
@@ -111,6 +148,7 @@ sgn_status build_work(sgn_batch* b) {
   BCHK(b, hipMalloc((void**)&b->d_work, work.size() * sizeof(int)));
   BCHK(b, hipMemcpy(b->d_work, work.data(), work.size() * sizeof(int), hipMemcpyHostToDevice));
   b->nwork = (int)work.size();
+  b->march = !chunks.empty();
   b->work_key = work_key(b);
   b->desc_dirty = true;
   drop_graph(b);
@@ -168,28 +206,39 @@ hipError_t launch_batch_pair(const sgn_batch* b, hipStream_t s, int pair, int pa
 }
 
 template <typename T, int TY>
-hipError_t launch_batch_step_t(const sgn_batch* b, hipStream_t s, int parity, int bpc) {
+hipError_t launch_batch_step_t(const sgn_batch* b, hipStream_t s, int route, int bpc) {
   if (TY == 24 || bpc == 0) {  // one workgroup per 32 x 24 tile: no persistent instance of that shape
     hipLaunchKernelGGL((sgn::batch_step_kernel<T, TY, false>), dim3(b->nwork), dim3(sgn::STAGE_THREADS), 0, s,
-                       b->d_desc, b->d_work, b->nwork, parity, b->d_flags);
+                       b->d_desc, b->d_work, b->nwork, route, b->d_flags);
   } else if constexpr (TY != 24) {
     hipLaunchKernelGGL((sgn::batch_step_kernel<T, TY, true>), dim3(persistent_grid(b, bpc)), dim3(sgn::STAGE_THREADS),
-                       0, s, b->d_desc, b->d_work, b->nwork, parity, b->d_flags);
+                       0, s, b->d_desc, b->d_work, b->nwork, route, b->d_flags);
   }
   return hipGetLastError();
 }
 
-// One RK4 step of every instance from the buffer selected by parity into the other.
-hipError_t enqueue_batch_step(const sgn_batch* b, hipStream_t s, int parity) {
+template <typename T>
+hipError_t launch_batch_march(const sgn_batch* b, hipStream_t s, int route) {
+  hipLaunchKernelGGL((sgn::batch_march_kernel<T>), dim3(b->nwork), dim3(sgn::MARCH_LANES), 0, s, b->d_desc, b->d_work,
+                     b->nwork, route, b->d_flags);
+  return hipGetLastError();
+}
+
+// One RK4 step of every instance from one state buffer into another (`route`: BATCH_*; the pair path knows
+// the first two).
+hipError_t enqueue_batch_step(const sgn_batch* b, hipStream_t s, int route) {
   if (b->path == SGN_PATH_FUSED) {
+    if (b->march)
+      return b->dtype == SGN_F64 ? launch_batch_march<double>(b, s, route) : launch_batch_march<float>(b, s, route);
     const int ty = tile_of(b), bpc = b->tile_y == 24 ? 0 : b->blocks_per_cu;
     if (b->dtype == SGN_F64)
-      return ty == 16 ? launch_batch_step_t<double, 16>(b, s, parity, bpc)
-                      : launch_batch_step_t<double, 8>(b, s, parity, bpc);
-    return ty == 24   ? launch_batch_step_t<float, 24>(b, s, parity, bpc)
-           : ty == 16 ? launch_batch_step_t<float, 16>(b, s, parity, bpc)
-                      : launch_batch_step_t<float, 8>(b, s, parity, bpc);
+      return ty == 16 ? launch_batch_step_t<double, 16>(b, s, route, bpc)
+                      : launch_batch_step_t<double, 8>(b, s, route, bpc);
+    return ty == 24   ? launch_batch_step_t<float, 24>(b, s, route, bpc)
+           : ty == 16 ? launch_batch_step_t<float, 16>(b, s, route, bpc)
+                      : launch_batch_step_t<float, 8>(b, s, route, bpc);
   }
+  const int parity = route;
   hipError_t e = launch_batch_pair(b, s, 1, parity);
   if (e) return e;
   return launch_batch_pair(b, s, 2, parity);
@@ -399,6 +448,21 @@ sgn_status sgn_batch_step(sgn_batch* b, const double* dt, int64_t nsteps) {
   if ((st = build_work(b))) return st;
   if ((st = push_desc(b))) return st;
   int64_t left = nsteps;
+  if (b->path == SGN_PATH_FUSED && (left & 1)) {  // an odd count begins with three steps, or is one and a copy
+    BCHK(b, enqueue_batch_step(b, b->stream, sgn::BATCH_Q_ACC));
+    if (left == 1) {
+      const dim3 grid(64, (unsigned)b->n);
+      if (b->dtype == SGN_F64)
+        hipLaunchKernelGGL(sgn::batch_copy_kernel<double>, grid, dim3(256), 0, b->stream, b->d_desc);
+      else
+        hipLaunchKernelGGL(sgn::batch_copy_kernel<float>, grid, dim3(256), 0, b->stream, b->d_desc);
+      BCHK(b, hipGetLastError());
+      return SGN_OK;
+    }
+    BCHK(b, enqueue_batch_step(b, b->stream, sgn::BATCH_ACC_YB));
+    BCHK(b, enqueue_batch_step(b, b->stream, sgn::BATCH_YB_Q));
+    left -= 3;
+  }
   const int64_t per_graph = 2 * BATCH_GRAPH_DOUBLE_STEPS;
   if (left >= per_graph) {
     if (!b->gexec || b->g_key != work_key(b) || b->g_bpc != b->blocks_per_cu) {

@@ -57,6 +57,7 @@ struct sgn_ctx {
   hipStream_t stream = nullptr;
   hipStream_t cap_stream = nullptr;
   int device = 0;
+  int num_cus = 256;
   size_t N = 0;
   size_t esize = 0;
   void* b = nullptr;
@@ -74,7 +75,7 @@ struct sgn_ctx {
   bool b_set = false;
   int step_path = SGN_PATH_FUSED;
   int tile_y = 8;     // stage and pair kernels
-  int step_tile = 16;  // step kernel: 16 selects 32 x 16, 8 selects 64 x 8
+  int step_tile = 16;  // step kernel: 24 the march kernel's strips or 32 x 24 tiles, 16 32 x 16, 8 64 x 8
   sgn_host::GraphCache graphs[2];
   sgn_host::GraphCache relax_graph;   // relaxation steps (sgn_step_relaxation)
   sgn_host::GraphCache totals_graph;  // steps with recorded totals (sgn_step_totals)
@@ -89,6 +90,36 @@ struct sgn_ctx {
 };
 
 namespace sgn_host {
+
+// How the march kernel cuts a grid: strips of MARCH_COLS columns, each cut into
+// `chunks` runs of rows (wall_chunks: the strips at reflecting walls in x);
+// tasks = 0: the grid runs the tile kernel instead.
+struct MarchPlan {
+  int strips = 0, chunks = 0, wall_chunks = 0, tasks = 0;
+};
+// One round of waves (as many as the GPU holds at once) covers the grid, in
+// runs of at least MARCH_MIN_HEIGHT rows (12 evaluations of the rows around a
+// run against 4 per row of it).  Below MARCH_MIN_NODES the strips are too few or
+// too short: FP64 512^2 takes 31 us in runs of 8 rows and 14.5 us on tiles, 1024^2
+// 41 us against 43, 2048^2 136 against 155.
+constexpr int64_t MARCH_MIN_NODES = (int64_t)1 << 20;
+constexpr int MARCH_MIN_HEIGHT = 8;
+// Evaluations per step in waves of 64: a strip's rows and those around its runs
+// against a tile's owned and ring nodes (32 x 24 tiles: 60 waves in four stages).
+// The march kernel runs one in 0.78 of the tile kernel's time (4096^2: FP64 466
+// against 602 us, FP32 257 against 324, about 1.31e6 of them either way), so it is
+// taken where it does not need 1.25 times as many: not where a last strip of a few
+// columns leaves most of its lanes idle.
+inline bool march_pays(int64_t march_evals, int64_t tile_evals) { return 4 * march_evals < 5 * tile_evals; }
+inline int64_t march_evals(int64_t strips, int64_t ny, int64_t chunks) { return strips * (4 * ny + 12 * chunks); }
+inline int64_t tile_evals(int64_t nx, int64_t ny) { return 60 * ((nx + 31) / 32) * ((ny + 23) / 24); }
+MarchPlan march_plan(const sgn_ctx* c);
+// One step by the march kernel; ysave and rpart as for enqueue_step_into (rpart:
+// mass and energy of the new state per task).
+hipError_t launch_march(const sgn_ctx* c, hipStream_t s, const MarchPlan& m, const void* qin, void* qout, double dt,
+                        void* ysave, double* rpart);
+// The tile shape a step kernel of this context runs (24: 32 x 24, ...).
+int tile_of(const sgn_ctx* c);
 
 sgn_status fail(sgn_ctx* c, sgn_status st, const std::string& msg);
 sgn_status hip_fail(sgn_ctx* c, hipError_t e, const char* what);
@@ -109,8 +140,6 @@ hipError_t enqueue_pair_step(const sgn_ctx* c, hipStream_t s, void* cur, void* o
 // Neither with source terms, and not both.
 hipError_t enqueue_step_into(const sgn_ctx* c, hipStream_t s, const void* cur, void* oth, double dt, double t,
                              void* ysave, double* rpart = nullptr, int epi = 0);
-// The tile shape a step kernel of this context runs (24: 32 x 24, ...).
-int tile_of(const sgn_ctx* c);
 // Number of epilogue sums (4 doubles each) a step with epilogue `epi` leaves.
 int step_parts(const sgn_ctx* c, int epi);
 // Makes c->tile_partials hold the epilogue sums of either tile shape

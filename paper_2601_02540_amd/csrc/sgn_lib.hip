@@ -218,7 +218,8 @@ hipError_t launch_fused_ty(const sgn_ctx* c, hipStream_t s, const void* qin, voi
   return hipGetLastError();
 }
 
-// One RK4 step in one kernel, from state buffer `qin` into `qout` (distinct);
+// One RK4 step in one kernel, from state buffer `qin` into `qout` (distinct), by
+// the march kernel where march_plan finds it the better one, else by tiles;
 // with `ysave`, also the stage states Y2, Y3, Y4 (three consecutive states);
 // with `rpart`, also the epilogue sums `epi` (sgn::EPI_*) of every tile.
 // Stage saving and source terms run on 32 x 16 tiles where the context's
@@ -226,6 +227,10 @@ hipError_t launch_fused_ty(const sgn_ctx* c, hipStream_t s, const void* qin, voi
 // every tile shape forms the same values.
 hipError_t launch_fused(const sgn_ctx* c, hipStream_t s, const void* qin, void* qout, double dt, double t0,
                         void* ysave = nullptr, double* rpart = nullptr, int epi = sgn::EPI_NONE) {
+  if (epi != sgn::EPI_RELAX) {
+    const sgn_host::MarchPlan m = sgn_host::march_plan(c);
+    if (m.tasks) return sgn_host::launch_march(c, s, m, qin, qout, dt, ysave, rpart);
+  }
   const int ty = sgn_host::tile_of(c) == 24 && (ysave || c->p.source == SGN_SRC_MMS) ? 16 : sgn_host::tile_of(c);
   if (c->p.dtype == SGN_F64) {
     if (ty == 24) return launch_fused_ty<double, 24>(c, s, qin, qout, dt, t0, ysave, rpart, epi);
@@ -279,6 +284,22 @@ hipError_t enqueue_double_step(const sgn_ctx* c, hipStream_t s, void* q, double 
 }
 
 bool double_steps(const sgn_ctx* c) { return c->step_path == SGN_PATH_PAIRS || c->step_path == SGN_PATH_FUSED; }
+
+// Three RK4 steps that leave the state in q on the fused path: q -> acc -> ya -> q.
+hipError_t enqueue_triple_step(const sgn_ctx* c, hipStream_t s, void* q, double dt, double t) {
+  hipError_t e = launch_fused(c, s, q, c->acc, dt, t);
+  if (!e) e = launch_fused(c, s, c->acc, c->ya, dt, t + dt);
+  if (!e) e = launch_fused(c, s, c->ya, q, dt, t + 2.0 * dt);
+  return e;
+}
+
+// One RK4 step in place on the fused path: the step kernel into acc and a copy
+// (21 values per node; the four stage kernels move 84).
+hipError_t enqueue_single_step(const sgn_ctx* c, hipStream_t s, void* q, double dt, double t) {
+  hipError_t e = launch_fused(c, s, q, c->acc, dt, t);
+  if (e) return e;
+  return hipMemcpyAsync(q, c->acc, 5 * c->N * c->esize, hipMemcpyDeviceToDevice, s);
+}
 
 // Enqueues `steps` RK4 steps on the context's step path (an even count on the
 // pair and fused paths).
@@ -375,7 +396,11 @@ int tile_of(const sgn_ctx* c) {
   return c->step_tile == 24 && c->p.dtype == SGN_F64 && wall ? 16 : c->step_tile;
 }
 
-int step_parts(const sgn_ctx* c, int) {
+int step_parts(const sgn_ctx* c, int epi) {
+  if (epi != sgn::EPI_RELAX) {
+    const MarchPlan m = march_plan(c);
+    if (m.tasks) return m.tasks;
+  }
   const int ty = tile_of(c);
   const int tx = ty == 8 ? sgn::StepGeom<8>::TX : sgn::StepGeom<16>::TX;
   return ((c->p.nx + tx - 1) / tx) * ((c->p.ny + ty - 1) / ty);
@@ -384,7 +409,9 @@ int step_parts(const sgn_ctx* c, int) {
 sgn_status ensure_tile_partials(sgn_ctx* c) {
   // room for the largest tile count of the tile shapes (32 x 24 has the fewest tiles)
   const size_t nx = (size_t)c->p.nx, ny = (size_t)c->p.ny;
-  const size_t tiles = std::max(((nx + 31) / 32) * ((ny + 15) / 16), ((nx + 63) / 64) * ((ny + 7) / 8));
+  // and for the march kernel's runs
+  const size_t tiles = std::max({((nx + 31) / 32) * ((ny + 15) / 16), ((nx + 63) / 64) * ((ny + 7) / 8),
+                                 (size_t)step_parts(c, sgn::EPI_TOTALS)});
   if (c->tile_partials_cap >= 4 * tiles) return SGN_OK;
   SGN_HIPCHK(c, hipStreamSynchronize(c->stream));  // earlier steps may still write the old buffer
   if (c->tile_partials) (void)hipFree(c->tile_partials);
@@ -500,6 +527,10 @@ sgn_status sgn_create(const sgn_params* p, void* stream, sgn_ctx** out) {
     delete c;
     return hip_fail(nullptr, e, "hipGetDevice");
   }
+  if ((e = hipDeviceGetAttribute(&c->num_cus, hipDeviceAttributeMultiprocessorCount, c->device)) != hipSuccess) {
+    delete c;
+    return hip_fail(nullptr, e, "hipDeviceGetAttribute");
+  }
   c->gc = sgn_host::grid_const(*p);
 
   const size_t plane = N * c->esize;
@@ -601,14 +632,31 @@ sgn_status sgn_step(sgn_ctx* c, void* q, double dt, int64_t nsteps, double t0) {
   if (!std::isfinite(t0)) return fail(c, SGN_E_ARG, "t0 must be finite");
   if (nsteps == 0) return SGN_OK;
   if (c->p.source != SGN_SRC_NONE) {
-    // Stage times matter: launch directly (pairs of steps, then a single one).
+    // Stage times matter: launch directly (an odd count on the fused path begins
+    // with three steps or is a single one; else pairs of steps, then a single one).
     int64_t s = 0;
+    if (c->step_path == SGN_PATH_FUSED && (nsteps & 1)) {
+      if (nsteps == 1) {
+        HIPCHK(c, enqueue_single_step(c, c->stream, q, dt, t0));
+        return SGN_OK;
+      }
+      HIPCHK(c, enqueue_triple_step(c, c->stream, q, dt, t0));
+      s = 3;
+    }
     if (double_steps(c))
       for (; s + 1 < nsteps; s += 2) HIPCHK(c, enqueue_double_step(c, c->stream, q, dt, t0 + (double)s * dt));
     for (; s < nsteps; ++s) HIPCHK(c, enqueue_step(c, c->stream, q, dt, t0 + (double)s * dt));
     return SGN_OK;
   }
   int64_t left = nsteps;
+  if (c->step_path == SGN_PATH_FUSED && (left & 1)) {
+    if (left == 1) {
+      HIPCHK(c, enqueue_single_step(c, c->stream, q, dt, 0.0));
+      return SGN_OK;
+    }
+    HIPCHK(c, enqueue_triple_step(c, c->stream, q, dt, 0.0));
+    left -= 3;
+  }
   if (left >= GRAPH_STEPS) {
     hipGraphExec_t ge;
     if ((st = get_graph(c, 0, q, dt, GRAPH_STEPS, &ge))) return st;
@@ -620,7 +668,7 @@ sgn_status sgn_step(sgn_ctx* c, void* q, double dt, int64_t nsteps, double t0) {
     if ((st = get_graph(c, 1, q, dt, small, &g1))) return st;
     for (; left >= small; left -= small) HIPCHK(c, hipGraphLaunch(g1, c->stream));
   }
-  // An odd final step on the pair or fused path runs as four single-stage kernels in place.
+  // An odd final step on the pair path runs as four single-stage kernels in place.
   if (left > 0) HIPCHK(c, enqueue_step(c, c->stream, q, dt, 0.0));
   return SGN_OK;
 }
@@ -632,7 +680,9 @@ sgn_status sgn_prepare_step(sgn_ctx* c, void* q, double dt, int64_t nsteps) {
   if (!(std::isfinite(dt) && dt > 0.0)) return fail(c, SGN_E_ARG, "dt must be finite and > 0");
   if (nsteps < 0) return fail(c, SGN_E_ARG, "nsteps must be >= 0");
   if (nsteps == 0 || c->p.source != SGN_SRC_NONE) return SGN_OK;
-  // the same split as sgn_step: 8-step replays, then 1- or 2-step replays
+  // the same split as sgn_step: an odd count of fused steps begins with three (or
+  // is one) launched directly; 8-step replays, then 1- or 2-step replays
+  if (c->step_path == SGN_PATH_FUSED && (nsteps & 1)) nsteps -= nsteps == 1 ? 1 : 3;
   hipGraphExec_t ge;
   if (nsteps >= GRAPH_STEPS && (st = get_graph(c, 0, q, dt, GRAPH_STEPS, &ge))) return st;
   const int small = double_steps(c) ? 2 : 1;

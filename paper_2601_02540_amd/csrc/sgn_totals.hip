@@ -42,14 +42,24 @@ hipError_t enqueue_step_with_totals(const sgn_ctx* c, hipStream_t s, void* cur, 
   return hipGetLastError();
 }
 
-// `steps` steps starting from the caller's buffer q (the state ends in q when
-// steps is even, in the scratch buffer otherwise).
-hipError_t enqueue_steps_with_totals(const sgn_ctx* c, hipStream_t s, void* q, double dt, int steps, int first,
-                                     double* series) {
+// `steps` steps of the state in q, which ends in q: in twos by way of acc, an
+// odd count >= 3 beginning with three by way of acc and ya, a single one copied back.
+hipError_t enqueue_steps_with_totals(const sgn_ctx* c, hipStream_t s, void* q, double dt, int steps, double* series) {
   hipError_t e = hipSuccess;
-  for (int k = 0; k < steps && e == hipSuccess; ++k) {
-    const bool from_q = ((first + k) % 2) == 0;
-    e = enqueue_step_with_totals(c, s, from_q ? q : c->acc, from_q ? c->acc : q, dt, series);
+  int k = 0;
+  if (steps & 1) {
+    e = enqueue_step_with_totals(c, s, q, c->acc, dt, series);
+    if (steps == 1) {
+      if (!e) e = hipMemcpyAsync(q, c->acc, 5 * c->N * c->esize, hipMemcpyDeviceToDevice, s);
+      return e;
+    }
+    if (!e) e = enqueue_step_with_totals(c, s, c->acc, c->ya, dt, series);
+    if (!e) e = enqueue_step_with_totals(c, s, c->ya, q, dt, series);
+    k = 3;
+  }
+  for (; k < steps && e == hipSuccess; k += 2) {
+    e = enqueue_step_with_totals(c, s, q, c->acc, dt, series);
+    if (!e) e = enqueue_step_with_totals(c, s, c->acc, q, dt, series);
   }
   return e;
 }
@@ -84,7 +94,7 @@ sgn_status sgn_step_totals(sgn_ctx* c, void* q, double dt, int64_t nsteps, doubl
       g = sgn_host::GraphCache{};
       c->totals_series = nullptr;
       HIPCHK(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-      hipError_t le = enqueue_steps_with_totals(c, c->cap_stream, q, dt, TOTALS_GRAPH_STEPS, 0, series);
+      hipError_t le = enqueue_steps_with_totals(c, c->cap_stream, q, dt, TOTALS_GRAPH_STEPS, series);
       hipGraph_t graph = nullptr;
       hipError_t ce = hipStreamEndCapture(c->cap_stream, &graph);
       if (le != hipSuccess) {
@@ -107,11 +117,7 @@ sgn_status sgn_step_totals(sgn_ctx* c, void* q, double dt, int64_t nsteps, doubl
     }
     for (; left >= TOTALS_GRAPH_STEPS; left -= TOTALS_GRAPH_STEPS) HIPCHK(c, hipGraphLaunch(g.exec, c->stream));
   }
-  if (left > 0) {
-    HIPCHK(c, enqueue_steps_with_totals(c, c->stream, q, dt, (int)left, 0, series));
-    if (left % 2)  // the state is in the scratch buffer
-      HIPCHK(c, hipMemcpyAsync(q, c->acc, 5 * c->N * c->esize, hipMemcpyDeviceToDevice, c->stream));
-  }
+  if (left > 0) HIPCHK(c, enqueue_steps_with_totals(c, c->stream, q, dt, (int)left, series));
   return SGN_OK;
 }
 
