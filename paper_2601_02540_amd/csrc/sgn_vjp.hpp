@@ -2,26 +2,30 @@
 // (discrete adjoint of eq. (sd_periodic_2D_SGN) / eq. (semi_2D)) and of the
 // classical RK4 stages.
 //
-// Reverse of one node c.  Given the cotangent kb of the five rates at c, the
-// reverse of split_form_rates yields cotangents of the node's own raw values
-// and of the 24 derivative values D_x f(c), D_y f(c).  A derivative
-// D f(c) = s (f(c+op) - f(c+om)) sends +s Dbar to the node c+op and -s Dbar
-// to c+om (a one-sided closure row sends one of them to c itself); at the
-// receiving node the product f (h(h+b), u^2, hu, huv, eta^2/h, ...) is chained
-// back to that node's raw values.  The cotangent of node d is the sum of what
-// d and its four neighbours send to it -- the transpose of the stencil.
-//
-// The cotangent a derivative D f(c) sends out, Dbar_f(c), depends only on node
-// c's own state and rate cotangent (it is the factor multiplying D f in the
-// rates, times the seed), not on any derivative.  The kernel therefore works
-// in gather form, like the forward stencil: node d evaluates Dbar_f at its
-// neighbours from their LDS values and applies the transposed operator column
-//   (D^T Dbar)(d) = D[d-1][d] Dbar(d-1) + D[d][d] Dbar(d) + D[d+1][d] Dbar(d+1)
-// (AxisTranspose below, closure rows included), then chains the amounts back
-// through the products at d.  No value crosses threads except through LDS.
-// The diagonal D[d][d] vanishes except on the first and last row of a
-// reflecting axis, so only those nodes evaluate their own Dbar; the reverse of
-// a node's own rates (split_form_reverse) therefore stops at its raw values.
+// The rates at a node c are sums over the neighbours m that its difference
+// operators name,
+//   a(c) . k(c) = sum_m w(c, m) G(c; m) + (terms of c alone),
+// with w = +-1/(2d) on interior and periodic rows and +-1/d on a reflecting closure
+// row, where c itself is one of the two (AxisStencil).  The cotangent of node d
+// gathers, for each neighbour m, the derivative of G(d; m) by d's values as the
+// centre and the derivative of G(m; d) by d's values as the neighbour, the latter
+// with the transposed weight (AxisTranspose); on a closure row m may be d.  G is
+// the printed split form term by term (n the velocity along the axis, t the one
+// across, r = eta/h - 1, an = a_n/h and so on for t and w):
+//   G(c; m) = -ah (n h_m + h n_m) - ae n (eta_m + 3/2 b_m)
+//     - an/2 [2g h_m (h_m + b_m - h - b) + h n_m^2 - n^2 h_m + n h_m n_m - h n n_m
+//             + lam/3 ((1 + r)^2 h_m - eta_m^2/h_m) - 2 lam/3 r eta_m - lam r b_m]
+//     - at/2 [h_m n_m t_m - n t h_m + h n t_m - h t n_m] - aw/2 [the same with w]
+// so that its derivatives share their factors: with Q = h n + h_m n_m and the
+// differences of the two neighbours' values, a node takes about 330 operations;
+// forming the cotangents of the 24 derivative values of every neighbour first and
+// chaining them back took 700.  The pair kernels were bound by that arithmetic,
+// then by waiting on the sums they wrote between their two evaluations: 1500 x 900
+// FP32 with walls 81 and 78 us, with this form 63 and 62, with the sums in
+// registers 54 and 52 (28 and 33 values a node: 2.8 and 3.4 TB/s).  Differences of
+// seeds and of r are formed before they are scaled by lambda: in FP32 the reverse
+// step's error against 64 bits fell from 7e-6 to 5e-7.
+// No value crosses threads except through LDS.
 #pragma once
 
 #include "sgn_fused.hpp"
@@ -37,360 +41,247 @@ namespace sgn {
 // and every role but PLAIN adds the bathymetry cotangent into Bb.
 enum : int { VJP_PLAIN = 0, VJP_S4 = 4, VJP_S3 = 3, VJP_S2 = 2, VJP_S1 = 1 };
 
+// A node as the reverse reads it: its state, the bottom, r = eta/h - 1 and the seed
+// of its rates, those of u, v and w times 1/(2h).
 template <typename T>
 struct VNode {
-  T h, u, v, w, eta, b, ih;  // ih = 1/h
+  T h, u, v, w, eta, r, b, ah, au, av, aw, ae;
 };
-
-template <typename T>
-__device__ __forceinline__ VNode<T> opaque_vnode(VNode<T> n) {
-  asm volatile("" : "+v"(n.h), "+v"(n.u), "+v"(n.v), "+v"(n.w), "+v"(n.eta), "+v"(n.b), "+v"(n.ih));
-  return n;
-}
 
 template <typename T>
 struct Cot {
   T h, u, v, w, eta, b;
-  __device__ __forceinline__ void zero() { h = u = v = w = eta = b = T(0); }
-  __device__ __forceinline__ void add(const Cot& o) {
-    h += o.h;
-    u += o.u;
-    v += o.v;
-    w += o.w;
-    eta += o.eta;
-    b += o.b;
-  }
 };
 
-// Chain the derivative cotangents amounts a[0..11] of the x-quantities
-// (h u v w eta b h(h+b) u^2 hu huv eta^2/h huw) at node n.
-template <typename T>
-__device__ __forceinline__ Cot<T> chain_x(const VNode<T>& n, const T (&a)[12]) {
-  Cot<T> c;
-  const T e2 = n.eta * n.eta;
-  c.h = a[0] + (T(2) * n.h + n.b) * a[6] + n.u * a[8] + n.u * n.v * a[9] - e2 * n.ih * n.ih * a[10] +
-        n.u * n.w * a[11];
-  c.u = a[1] + T(2) * n.u * a[7] + n.h * a[8] + n.h * n.v * a[9] + n.h * n.w * a[11];
-  c.v = a[2] + n.h * n.u * a[9];
-  c.w = a[3] + n.h * n.u * a[11];
-  c.eta = a[4] + T(2) * n.eta * n.ih * a[10];
-  c.b = a[5] + n.h * a[6];
-  return c;
-}
-
-// Same for the y-quantities (h u v w eta b h(h+b) v^2 hv huv eta^2/h hvw).
-template <typename T>
-__device__ __forceinline__ Cot<T> chain_y(const VNode<T>& n, const T (&a)[12]) {
-  Cot<T> c;
-  const T e2 = n.eta * n.eta;
-  c.h = a[0] + (T(2) * n.h + n.b) * a[6] + n.v * a[8] + n.u * n.v * a[9] - e2 * n.ih * n.ih * a[10] +
-        n.v * n.w * a[11];
-  c.u = a[1] + n.h * n.v * a[9];
-  c.v = a[2] + T(2) * n.v * a[7] + n.h * a[8] + n.h * n.u * a[9] + n.h * n.w * a[11];
-  c.w = a[3] + n.h * n.v * a[11];
-  c.eta = a[4] + T(2) * n.eta * n.ih * a[10];
-  c.b = a[5] + n.h * a[6];
-  return c;
-}
-
-// Reverse of split_form_rates at one node, through the node's own values: the
-// cotangent of the node's raw values (center) from the seed kb of its rates.
-// The cotangents of the node's derivative values, dbar_x and dbar_y of the node
-// itself (below), reach the node's own values only through the diagonal of
-// the operator, i.e. on the reflecting closure rows.
-template <typename T>
-__device__ __forceinline__ void split_form_reverse(const VNode<T>& c, const VNode<T>& xm, const VNode<T>& xp,
-                                                   const VNode<T>& ym, const VNode<T>& yp, T sx, T sy, T g, T lam,
-                                                   T satx, T saty, const T (&kb)[5], Cot<T>& cen) {
-  const T half = T(0.5);
-  // forward values
-  const T Dxh = sx * (xp.h - xm.h), Dxu = sx * (xp.u - xm.u), Dxv = sx * (xp.v - xm.v), Dxw = sx * (xp.w - xm.w);
-  const T Dxeta = sx * (xp.eta - xm.eta), Dxb = sx * (xp.b - xm.b);
-  const T DxhH = sx * (xp.h * (xp.h + xp.b) - xm.h * (xm.h + xm.b));
-  const T Dxu2 = sx * (xp.u * xp.u - xm.u * xm.u);
-  const T xphu = xp.h * xp.u, xmhu = xm.h * xm.u;
-  const T Dxhu = sx * (xphu - xmhu);
-  const T Dxhuv = sx * (xphu * xp.v - xmhu * xm.v);
-  const T Dxe2h = sx * (xp.eta * xp.eta * xp.ih - xm.eta * xm.eta * xm.ih);
-  const T Dxhuw = sx * (xphu * xp.w - xmhu * xm.w);
-  const T Dyh = sy * (yp.h - ym.h), Dyu = sy * (yp.u - ym.u), Dyv = sy * (yp.v - ym.v), Dyw = sy * (yp.w - ym.w);
-  const T Dyeta = sy * (yp.eta - ym.eta), Dyb = sy * (yp.b - ym.b);
-  const T DyhH = sy * (yp.h * (yp.h + yp.b) - ym.h * (ym.h + ym.b));
-  const T Dyv2 = sy * (yp.v * yp.v - ym.v * ym.v);
-  const T yphv = yp.h * yp.v, ymhv = ym.h * ym.v;
-  const T Dyhv = sy * (yphv - ymhv);
-  const T Dyhuv = sy * (yphv * yp.u - ymhv * ym.u);
-  const T Dye2h = sy * (yp.eta * yp.eta * yp.ih - ym.eta * ym.eta * ym.ih);
-  const T Dyhvw = sy * (yphv * yp.w - ymhv * ym.w);
-  const T h = c.h, u = c.u, v = c.v, w = c.w, eta = c.eta, ih = c.ih;
-  const T H = h + c.b;
-  const T r = eta * ih;
-  const T omr = T(1) - r;
-  const T hu = h * u, hv = h * v, uv = u * v, hw = h * w, uw = u * w, vw = v * w;
-  const T lam6 = lam * T(1.0 / 6.0), lam3 = lam * T(1.0 / 3.0), lam2 = lam * T(0.5);
-  const T A = g * (DxhH - H * Dxh) +
-              half * (h * Dxu2 - u * u * Dxh + u * Dxhu - hu * Dxu + Dyhuv - uv * Dyh + hv * Dyu - hu * Dyv) +
-              lam6 * (r * r * Dxh - Dxe2h) + lam3 * omr * Dxeta + lam2 * omr * Dxb;
-  const T B = g * (DyhH - H * Dyh) +
-              half * (h * Dyv2 - v * v * Dyh + v * Dyhv - hv * Dyv + Dxhuv - uv * Dxh + hu * Dxv - hv * Dxu) +
-              lam6 * (r * r * Dyh - Dye2h) + lam3 * omr * Dyeta + lam2 * omr * Dyb;
-  const T C = half * (Dxhuw + hu * Dxw - u * w * Dxh - hw * Dxu + Dyhvw + hv * Dyw - v * w * Dyh - hw * Dyv);
-
-  const T ah = kb[0], au = kb[1], av = kb[2], aw = kb[3], ae = kb[4];
-  const T Ab = -au * ih, Bb = -av * ih, Cb = -aw * ih;
-  T ihb = -au * A - av * B + aw * (lam * omr - C);
-  T omrb = lam * aw * ih;
-  T hb, ub, vb, wb, etab, Hb, hub, hvb, uvb, hwb, uwb, vwb, rb;
-  // k_eta = w - (u Dxeta + v Dyeta + 3/2 (u Dxb + v Dyb))
-  wb = ae;
-  ub = -ae * (Dxeta + T(1.5) * Dxb);
-  vb = -ae * (Dyeta + T(1.5) * Dyb);
-  // k_h = -(u Dxh + h Dxu + v Dyh + h Dyv) + satx hu + saty hv
-  ub += -ah * Dxh;
-  hb = -ah * (Dxu + Dyv);
-  vb += -ah * Dyh;
-  hub = ah * satx;
-  hvb = ah * saty;
-  // A
-  Hb = -g * Ab * Dxh;
-  hb += half * Ab * Dxu2;
-  ub += -Ab * u * Dxh;
-  ub += half * Ab * Dxhu;
-  hub += -half * Ab * Dxu;
-  uvb = -half * Ab * Dyh;
-  hvb += half * Ab * Dyu;
-  hub += -half * Ab * Dyv;
-  rb = lam3 * Ab * r * Dxh;
-  omrb += lam3 * Ab * Dxeta + lam2 * Ab * Dxb;
-  // B
-  Hb += -g * Bb * Dyh;
-  hb += half * Bb * Dyv2;
-  vb += -Bb * v * Dyh;
-  vb += half * Bb * Dyhv;
-  hvb += -half * Bb * Dyv;
-  uvb += -half * Bb * Dxh;
-  hub += half * Bb * Dxv;
-  hvb += -half * Bb * Dxu;
-  rb += lam3 * Bb * r * Dyh;
-  omrb += lam3 * Bb * Dyeta + lam2 * Bb * Dyb;
-  // C
-  hub += half * Cb * Dxw;
-  uwb = -half * Cb * Dxh;
-  hwb = -half * Cb * Dxu;
-  hvb += half * Cb * Dyw;
-  vwb = -half * Cb * Dyh;
-  hwb += -half * Cb * Dyv;
-  // center products
-  rb += -omrb;
-  hb += Hb;
-  T bb = Hb;
-  hb += u * hub;
-  ub += h * hub;
-  hb += v * hvb;
-  vb += h * hvb;
-  ub += v * uvb;
-  vb += u * uvb;
-  hb += w * hwb;
-  wb += h * hwb;
-  ub += w * uwb;
-  wb += u * uwb;
-  vb += w * vwb;
-  wb += v * vwb;
-  etab = rb * ih;
-  ihb += rb * eta;
-  hb += -ih * ih * ihb;
-  cen.h = hb;
-  cen.u = ub;
-  cen.v = vb;
-  cen.w = wb;
-  cen.eta = etab;
-  cen.b = bb;
-}
-
-// Column d of the 1D operator: weights of Dbar(d-1), Dbar(d), Dbar(d+1) in
-// (D^T Dbar)(d).  Interior/periodic rows are (-1, 0, 1)/(2 delta); the
-// reflecting first and last rows are (-2, 2)/(2 delta) (n >= 4 assumed).
+// Column d of the 1D operator: weights of the lower and the upper neighbour that
+// row d names (itself on a closure row) in (D^T Dbar)(d).  Interior/periodic
+// rows are (-1, 0, 1)/(2 delta); the reflecting first and last rows are (-2, 2)/(2
+// delta) (n >= 4 assumed).
 template <typename T, int BC>
 struct AxisTranspose {
-  T wl, wc, wr;
+  T wm, wp;
   __device__ __forceinline__ AxisTranspose(int i, int n, double inv2d, double invd) {
-    wl = T(inv2d);
-    wc = T(0);
-    wr = T(-inv2d);
+    wm = T(inv2d);
+    wp = T(-inv2d);
     if (BC == BC_REFLECTING) {
-      if (i == 0) {
-        wl = T(0);
-        wc = T(-invd);
-      } else if (i == 1) {
-        wl = T(invd);
-      }
-      if (i == n - 1) {
-        wr = T(0);
-        wc = T(invd);
-      } else if (i == n - 2) {
-        wr = T(-invd);
-      }
+      if (i == 0) wm = T(-invd);
+      if (i == 1) wm = T(invd);
+      if (i == n - 1) wp = T(invd);
+      if (i == n - 2) wp = T(-invd);
     }
   }
 };
 
-template <typename T>
-struct Seed {
-  T h, u, v, w, eta;  // cotangent of the five rates at one node
+// Planes of 16-byte vectors (128-bit LDS reads move twice the bytes per clock).
+// Parts of a vector are stored through pointers of their own type: an element
+// assignment would store the whole vector, and other threads write the rest.
+typedef float sgn_f2 __attribute__((ext_vector_type(2)));
+template <typename T, int H, int W>
+struct VjpSmem;
+
+template <int H, int W>
+struct VjpSmem<double, H, W> {
+  sgn_d2 hu[H][W], vw[H][W], er[H][W], bs[H][W], uv[H][W], we[H][W];
+  __device__ __forceinline__ VNode<double> load(int r, int c) const {
+    const sgn_d2 p = hu[r][c], q = vw[r][c], e = er[r][c], b = bs[r][c], x = uv[r][c], y = we[r][c];
+    return VNode<double>{p.x, p.y, q.x, q.y, e.x, e.y, b.x, b.y, x.x, x.y, y.x, y.y};
+  }
+  __device__ __forceinline__ void store_state(int r, int c, const double (&y)[5], double rr) {
+    hu[r][c] = sgn_d2{y[0], y[1]};
+    vw[r][c] = sgn_d2{y[2], y[3]};
+    er[r][c] = sgn_d2{y[4], rr};
+  }
+  __device__ __forceinline__ void store_b(int r, int c, double b) { ((double*)&bs[r][c])[0] = b; }
+  __device__ __forceinline__ void store_seed(int r, int c, const double (&a)[5]) {
+    ((double*)&bs[r][c])[1] = a[0];
+    uv[r][c] = sgn_d2{a[1], a[2]};
+    we[r][c] = sgn_d2{a[3], a[4]};
+  }
+  __device__ __forceinline__ void copy_seed(int r, int c, int r2, int c2) {
+    ((double*)&bs[r][c])[1] = bs[r2][c2].y;
+    uv[r][c] = uv[r2][c2];
+    we[r][c] = we[r2][c2];
+  }
 };
 
-// Dbar of the 12 x-quantities (h u v w eta b h(h+b) u^2 hu huv eta^2/h huw) at
-// a node from its own state n and seed a: the factor of each D_x f in the
-// rates of eq. (sd_periodic_2D_SGN), times the seed of that rate.
-template <typename T>
-__device__ __forceinline__ void dbar_x(const VNode<T>& n, const Seed<T>& a, T g, T lam, T (&q)[12]) {
-  const T half = T(0.5);
-  const T ih = n.ih;
-  const T Ab = -a.u * ih, Bb = -a.v * ih, Cb = -a.w * ih;
-  const T H = n.h + n.b, r = n.eta * ih, omr = T(1) - r;
-  const T hu = n.h * n.u, hv = n.h * n.v, hw = n.h * n.w;
-  q[0] = -g * Ab * H - half * Ab * n.u * n.u + lam * T(1.0 / 6.0) * Ab * r * r - half * Bb * n.u * n.v -
-         half * Cb * n.u * n.w - a.h * n.u;
-  q[1] = -half * Ab * hu - half * Bb * hv - half * Cb * hw - a.h * n.h;
-  q[2] = half * Bb * hu;
-  q[3] = half * Cb * hu;
-  q[4] = lam * T(1.0 / 3.0) * Ab * omr - a.eta * n.u;
-  q[5] = lam * T(0.5) * Ab * omr - T(1.5) * a.eta * n.u;
-  q[6] = g * Ab;
-  q[7] = half * Ab * n.h;
-  q[8] = half * Ab * n.u;
-  q[9] = half * Bb;
-  q[10] = -lam * T(1.0 / 6.0) * Ab;
-  q[11] = half * Cb;
-}
-
-// Same for the 12 y-quantities (h u v w eta b h(h+b) v^2 hv huv eta^2/h hvw).
-template <typename T>
-__device__ __forceinline__ void dbar_y(const VNode<T>& n, const Seed<T>& a, T g, T lam, T (&q)[12]) {
-  const T half = T(0.5);
-  const T ih = n.ih;
-  const T Ab = -a.u * ih, Bb = -a.v * ih, Cb = -a.w * ih;
-  const T H = n.h + n.b, r = n.eta * ih, omr = T(1) - r;
-  const T hu = n.h * n.u, hv = n.h * n.v, hw = n.h * n.w;
-  q[0] = -g * Bb * H - half * Bb * n.v * n.v + lam * T(1.0 / 6.0) * Bb * r * r - half * Ab * n.u * n.v -
-         half * Cb * n.v * n.w - a.h * n.v;
-  q[1] = half * Ab * hv;
-  q[2] = -half * Bb * hv - half * Ab * hu - half * Cb * hw - a.h * n.h;
-  q[3] = half * Cb * hv;
-  q[4] = lam * T(1.0 / 3.0) * Bb * omr - a.eta * n.v;
-  q[5] = lam * T(0.5) * Bb * omr - T(1.5) * a.eta * n.v;
-  q[6] = g * Bb;
-  q[7] = half * Bb * n.h;
-  q[8] = half * Bb * n.v;
-  q[9] = half * Ab;
-  q[10] = -lam * T(1.0 / 6.0) * Bb;
-  q[11] = half * Cb;
-}
-
-template <typename T>
-__device__ __forceinline__ Seed<T> opaque_seed(Seed<T> a) {
-  asm volatile("" : "+v"(a.h), "+v"(a.u), "+v"(a.v), "+v"(a.w), "+v"(a.eta));
-  return a;
-}
-
-template <typename T, int TY>
-struct VjpSmem {
-  T f[12][TY + 2][TILE_X + 2];  // h u v w eta b 1/h | seeds of h u v w eta
+template <int H, int W>
+struct VjpSmem<float, H, W> {
+  sgn_f4 y4[H][W], eb[H][W], a4[H][W];
+  __device__ __forceinline__ VNode<float> load(int r, int c) const {
+    const sgn_f4 p = y4[r][c], q = eb[r][c], a = a4[r][c];
+    return VNode<float>{p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w, a.x, a.y, a.z, a.w};
+  }
+  __device__ __forceinline__ void store_state(int r, int c, const float (&y)[5], float rr) {
+    y4[r][c] = sgn_f4{y[0], y[1], y[2], y[3]};
+    ((sgn_f2*)&eb[r][c])[0] = sgn_f2{y[4], rr};
+  }
+  __device__ __forceinline__ void store_b(int r, int c, float b) { ((float*)&eb[r][c])[2] = b; }
+  __device__ __forceinline__ void store_seed(int r, int c, const float (&a)[5]) {
+    ((float*)&eb[r][c])[3] = a[0];
+    a4[r][c] = sgn_f4{a[1], a[2], a[3], a[4]};
+  }
+  __device__ __forceinline__ void copy_seed(int r, int c, int r2, int c2) {
+    ((float*)&eb[r][c])[3] = eb[r2][c2].w;
+    a4[r][c] = a4[r2][c2];
+  }
 };
 
-// With SCALE, the seed planes hold unscaled values and the seeds are formed as
-// sc * plane here (the same product the role kernels store when staging).
-template <typename T, bool SCALE = false, class Smem>
-__device__ __forceinline__ void vjp_lds(const Smem& s, int r, int c, VNode<T>& n, Seed<T>& a, T sc = T(1)) {
-  n.h = s.f[0][r][c];
-  n.u = s.f[1][r][c];
-  n.v = s.f[2][r][c];
-  n.w = s.f[3][r][c];
-  n.eta = s.f[4][r][c];
-  n.b = s.f[5][r][c];
-  n.ih = s.f[6][r][c];
-  a.h = SCALE ? sc * s.f[7][r][c] : s.f[7][r][c];
-  a.u = SCALE ? sc * s.f[8][r][c] : s.f[8][r][c];
-  a.v = SCALE ? sc * s.f[9][r][c] : s.f[9][r][c];
-  a.w = SCALE ? sc * s.f[10][r][c] : s.f[10][r][c];
-  a.eta = SCALE ? sc * s.f[11][r][c] : s.f[11][r][c];
+// Seeds as they are staged, from the cotangent k of the five rates; ih = 1/h.
+template <typename T>
+__device__ __forceinline__ void staged_seed(const T (&k)[5], T ih, T (&a)[5]) {
+#pragma clang fp contract(off)
+  const T hih = T(0.5) * ih;
+  a[0] = k[0];
+  a[1] = k[1] * hih;
+  a[2] = k[2] * hih;
+  a[3] = k[3] * hih;
+  a[4] = k[4];
 }
 
-// Cotangent of the raw values of node (i, j), in the domain: the reverse of
-// its own rates plus what its neighbours' derivatives send it (the gathered
-// transpose), from a staging s that holds Y, b, 1/h and the seeds (planes
-// 0..11) around the node's position (r, c).
-template <typename T, int BCX, int BCY, bool SCALE = false, class Smem>
-__device__ __forceinline__ Cot<T> vjp_node(const Smem& s, int r, int c, int i, int j, const GridConst& gc,
-                                           T sc = T(1)) {
+// The values of a node by axis (n along, t across) and the products its own
+// derivatives share.
+template <typename T>
+struct VAxisNode {
+  T n, t, an, at;
+};
+template <typename T>
+__device__ __forceinline__ VAxisNode<T> along_x(const VNode<T>& c) {
+  return VAxisNode<T>{c.u, c.v, c.au, c.av};
+}
+template <typename T>
+__device__ __forceinline__ VAxisNode<T> along_y(const VNode<T>& c) {
+  return VAxisNode<T>{c.v, c.u, c.av, c.au};
+}
+
+// What one axis gives: the cotangents of the node's values (r: through r, the
+// centre's only) and the sums A, Tt, Tw of the rates h n_t, h t_t and h w_t along it
+// (twice the negative of their part, times the scale s).
+template <typename T>
+struct VAxis {
+  T h, n, t, w, eta, b, r, A, Tt, Tw;
+};
+
+template <typename T>
+__device__ __forceinline__ VAxis<T> axis_reverse(const VNode<T>& c, const VAxisNode<T>& ca, const VNode<T>& m,
+                                                 const VAxisNode<T>& ma, const VNode<T>& p, const VAxisNode<T>& pa,
+                                                 T s, T wm, T wp, T g2, T lam) {
+#pragma clang fp contract(off)
+  const T lam3 = lam * T(1.0 / 3.0);
+  const T h = c.h, n = ca.n, t = ca.t, w = c.w;
+  const T H = h + c.b, hn = h * n, r2 = c.r * c.r, rho = T(1) + c.r;
+  VAxis<T> o;
+  // the centre's part: differences of the two neighbours
+  const T dh = p.h - m.h, dn = pa.n - ma.n, dt = pa.t - ma.t, dw = p.w - m.w, deta = p.eta - m.eta, db = p.b - m.b;
+  const T sn = pa.n + ma.n;
+  const T hdn = h * dn, ndh = n * dh;
+  const T dR = ndh + hdn;
+  const T Qp = fused(p.h, pa.n, hn), Qm = fused(m.h, ma.n, hn);
+  const T X = (Qp - Qm) - dR;
+  const T zp = (p.h + p.b) - H, zm = (m.h + m.b) - H;
+  o.Tt = fused(Qp, pa.t, fused(-Qm, ma.t, -(t * dR)));
+  o.Tw = fused(Qp, p.w, fused(-Qm, m.w, -(w * dR)));
+  const T P = fused(zp, p.h, -(zm * m.h));
+  const T ddh = deta - dh;
+  const T R = fused(T(-2) * rho, ddh, fused(r2, dh, fused(m.r * m.r, m.h, -((p.r * p.r) * p.h))));
+  o.A = fused(-(lam * c.r), db, fused(lam3, R, fused(g2, P, fused(hdn, sn, n * X))));
+  const T gdh = (g2 * ca.an) * dh;
+  const T cn = -fused(c.ah, dh,
+                      fused(ca.an, X - ndh,
+                            fused(ca.at, fused(h, dt, -(t * dh)),
+                                  fused(c.aw, fused(h, dw, -(w * dh)), c.ae * fused(T(1.5), db, deta)))));
+  const T ch = gdh - fused(c.ah, dn,
+                           fused(ca.an * dn, sn - n,
+                                 fused(ca.at, fused(n, dt, -(t * dn)), c.aw * fused(n, dw, -(w * dn)))));
+  o.r = (s * (lam * ca.an)) * fused(T(2.0 / 3.0), fused(-c.r, dh, ddh), db);
+  o.n = s * cn;
+  o.h = s * ch;
+  o.t = s * (ca.at * dR);
+  o.w = s * (c.aw * dR);
+  o.b = s * gdh;
+  // the neighbours' rates, in which this node is the neighbour
+  const T ht = h * t, hw = h * w, nt = n * t, nw = n * w, n2 = n + n;
+  const auto side = [&](const VNode<T>& q, const VAxisNode<T>& qa, T Q, T z, T wt, T x2) {
+#pragma clang fp contract(off)
+    const T x1 = wt * q.ah, x3 = wt * qa.at, x4 = wt * q.aw;
+    o.t = fused(-x3, Q, o.t);
+    o.w = fused(-x4, Q, o.w);
+    const T fn = fused(q.h, n2, qa.n * (h - q.h));  // 2 h_m n + n_m (h - h_m)
+    o.n = fused(-x1, q.h, fused(-x2, fn, fused(-x3, fused(-q.h, qa.t, ht), fused(-x4, fused(-q.h, q.w, hw), o.n))));
+    const T fh = fused(-g2, z, qa.n * (n - qa.n));  // and 2g h of the sum below
+    o.h = fused(-x1, qa.n, fused(-x2, fh, fused(-x3, fused(-qa.n, qa.t, nt), fused(-x4, fused(-qa.n, q.w, nw), o.h))));
+  };
+  // The terms that carry g or lambda and this node's values take the difference
+  // of the neighbours' seeds first:
+  //   h: 2g h + lam/3 ((1 + r)^2 + 1 + 2 r_m + r_m^2),  eta: -2 lam/3 (1 + r + r_m),
+  //   b: 2g h - lam r_m,  times -x2 each
+  const T x2m = wm * ma.an, x2p = wp * pa.an;
+  side(m, ma, Qm, zm, wm, x2m);
+  side(p, pa, Qp, zp, wp, x2p);
+  const T x2 = x2m + x2p, tm = x2m * m.r, tp = x2p * p.r;
+  const T xr = tm + tp, xrr = fused(tm, m.r, tp * p.r);
+  const T x5 = fused(wm * m.ae, ma.n, (wp * p.ae) * pa.n);
+  const T g2h = g2 * h;
+  o.h = fused(-lam3, fused(T(2), xr, xrr), fused(-fused(lam3, fused(rho, rho, T(1)), g2h), x2, o.h));
+  o.eta = fused(T(2) * lam3, fused(rho, x2, xr), -x5);
+  o.b = fused(lam, xr, fused(-g2h, x2, fused(T(-1.5), x5, o.b)));
+  return o;
+}
+
+// Cotangent of the raw values of node (i, j), in the domain, from a staging s
+// around the node's position (r, c).  All multiply-adds are written out and no
+// others are formed, so every kernel rounds it alike.
+template <typename T, int BCX, int BCY, class Smem>
+__device__ __forceinline__ Cot<T> vjp_node(const Smem& s, int r, int c, int i, int j, const GridConst& gc) {
+#pragma clang fp contract(off)
   const int nx = gc.nx, ny = gc.ny;
-  const T g = T(gc.g), lam = T(gc.lam);
+  const T g2 = T(2) * T(gc.g), lam = T(gc.lam);
   const AxisStencil<BCX> ax(i, nx, gc.inv2dx, gc.invdx);
-  const AxisTranspose<T, BCX> tx_(i, nx, gc.inv2dx, gc.invdx);
-  T satx = T(0);
-  if (BCX == BC_REFLECTING) {
-    if (i == 0) satx = T(-2.0 * gc.invdx);
-    if (i == nx - 1) satx = T(2.0 * gc.invdx);
-  }
+  const AxisTranspose<T, BCX> tx(i, nx, gc.inv2dx, gc.invdx);
   const AxisStencil<BCY> ay(j, ny, gc.inv2dy, gc.invdy);
-  const AxisTranspose<T, BCY> ty_(j, ny, gc.inv2dy, gc.invdy);
-  T saty = T(0);
-  if (BCY == BC_REFLECTING) {
-    if (j == 0) saty = T(-2.0 * gc.invdy);
-    if (j == ny - 1) saty = T(2.0 * gc.invdy);
+  const AxisTranspose<T, BCY> ty(j, ny, gc.inv2dy, gc.invdy);
+  const VNode<T> cn = s.load(r, c);
+  const VNode<T> xm = s.load(r, c + ax.om), xp = s.load(r, c + ax.op);
+  const T ih = recip_staged(cn.h);
+  const T sx = T(ax.scale), sy = T(ay.scale);
+  const VAxis<T> x = axis_reverse<T>(cn, along_x(cn), xm, along_x(xm), xp, along_x(xp), sx, tx.wm, tx.wp, g2, lam);
+  const VNode<T> ym = s.load(r + ay.om, c), yp = s.load(r + ay.op, c);
+  const VAxis<T> y = axis_reverse<T>(cn, along_y(cn), ym, along_y(ym), yp, along_y(yp), sy, ty.wm, ty.wp, g2, lam);
+  // through r = eta/h - 1 and the 1/h of the rates
+  const T xr = (x.r + y.r) - (T(2) * lam) * cn.aw;
+  const T kh = fused(cn.au, fused(sx, x.A, sy * y.Tt),
+                     fused(cn.av, fused(sy, y.A, sx * x.Tt),
+                           cn.aw * fused(sx, x.Tw, fused(sy, y.Tw, (T(2) * lam) * cn.r))));
+  Cot<T> o;
+  o.h = fused(ih, fused(-xr, T(1) + cn.r, kh), x.h + y.h);
+  o.u = x.n + y.t;
+  o.v = x.t + y.n;
+  o.w = (x.w + y.w) + cn.ae;
+  o.eta = fused(xr, ih, x.eta + y.eta);
+  o.b = x.b + y.b;
+  if (BCX == BC_REFLECTING && (i == 0 || i == nx - 1)) {  // the wall SAT ah satx h u
+    const T a = cn.ah * T(i == 0 ? -2.0 * gc.invdx : 2.0 * gc.invdx);
+    o.h = fused(a, cn.u, o.h);
+    o.u = fused(a, cn.h, o.u);
   }
-  VNode<T> nc, nxm, nxp, nym, nyp;
-  Seed<T> ac, axm, axp, aym, ayp;
-  vjp_lds<T, SCALE>(s, r, c, nc, ac, sc);
-  vjp_lds<T, SCALE>(s, r, c - 1, nxm, axm, sc);
-  vjp_lds<T, SCALE>(s, r, c + 1, nxp, axp, sc);
-  vjp_lds<T, SCALE>(s, r - 1, c, nym, aym, sc);
-  vjp_lds<T, SCALE>(s, r + 1, c, nyp, ayp, sc);
-  // Opaque copies: where one thread evaluates neighbouring nodes, the compiler
-  // would otherwise share loads and products between the evaluations and fuse
-  // the arithmetic differently; every evaluation rounds as a lone one does.
-  nc = opaque_vnode(nc);
-  nxm = opaque_vnode(nxm);
-  nxp = opaque_vnode(nxp);
-  nym = opaque_vnode(nym);
-  nyp = opaque_vnode(nyp);
-  ac = opaque_seed(ac);
-  axm = opaque_seed(axm);
-  axp = opaque_seed(axp);
-  aym = opaque_seed(aym);
-  ayp = opaque_seed(ayp);
-  // local part: reverse of this node's own rates (stencil neighbours with closures)
-  const VNode<T>& sxm = ax.om == 0 ? nc : nxm;
-  const VNode<T>& sxp = ax.op == 0 ? nc : nxp;
-  const VNode<T>& sym = ay.om == 0 ? nc : nym;
-  const VNode<T>& syp = ay.op == 0 ? nc : nyp;
-  const T kb[5] = {ac.h, ac.u, ac.v, ac.w, ac.eta};
-  Cot<T> out;
-  split_form_reverse<T>(nc, sxm, sxp, sym, syp, T(ax.scale), T(ay.scale), g, lam, satx, saty, kb, out);
-  // transpose part: Dbar of the neighbours, and of this node itself where
-  // the operator's diagonal is nonzero (the closure rows of a reflecting axis)
-  T qa[12], qb[12], amt[12];
-  dbar_x(nxm, axm, g, lam, qa);
-  dbar_x(nxp, axp, g, lam, qb);
-#pragma unroll
-  for (int m = 0; m < 12; ++m) amt[m] = tx_.wl * qa[m] + tx_.wr * qb[m];
-  if (BCX == BC_REFLECTING && (i == 0 || i == nx - 1)) {
-    dbar_x(nc, ac, g, lam, qa);
-#pragma unroll
-    for (int m = 0; m < 12; ++m) amt[m] += tx_.wc * qa[m];
-  }
-  out.add(chain_x(nc, amt));
-  dbar_y(nym, aym, g, lam, qa);
-  dbar_y(nyp, ayp, g, lam, qb);
-#pragma unroll
-  for (int m = 0; m < 12; ++m) amt[m] = ty_.wl * qa[m] + ty_.wr * qb[m];
   if (BCY == BC_REFLECTING && (j == 0 || j == ny - 1)) {
-    dbar_y(nc, ac, g, lam, qa);
-#pragma unroll
-    for (int m = 0; m < 12; ++m) amt[m] += ty_.wc * qa[m];
+    const T a = cn.ah * T(j == 0 ? -2.0 * gc.invdy : 2.0 * gc.invdy);
+    o.h = fused(a, cn.v, o.h);
+    o.v = fused(a, cn.h, o.v);
   }
-  out.add(chain_y(nc, amt));
-  return out;
+  return o;
+}
+
+// Stages a node: v = its state, b and the seed before its factor a.
+template <typename T, class Smem>
+__device__ __forceinline__ void stage_node(Smem& s, int r, int c, const T (&v)[11], T a) {
+  const T ih = recip_staged(v[0]);
+  const T y[5] = {v[0], v[1], v[2], v[3], v[4]};
+  const T k[5] = {a * v[6], a * v[7], a * v[8], a * v[9], a * v[10]};
+  T sd[5];
+  staged_seed(k, ih, sd);
+  s.store_state(r, c, y, (y[4] - y[0]) * ih);
+  s.store_b(r, c, v[5]);
+  s.store_seed(r, c, sd);
 }
 
 // One reverse-mode stage (role ROLE) on a 64 x TY tile per workgroup.
@@ -403,7 +294,7 @@ __global__ __launch_bounds__(STAGE_THREADS) void vjp_kernel(const GridConst gc, 
   constexpr int RPT = TY / THREAD_ROWS;
   constexpr int W = TILE_X + 2;
   constexpr int REGION = (TY + 2) * W;
-  __shared__ VjpSmem<T, TY> s;
+  __shared__ VjpSmem<T, TY + 2, W> s;
   const int nx = gc.nx, ny = gc.ny;
   const size_t N = (size_t)nx * (size_t)ny;
   const int ntx = (nx + TILE_X - 1) / TILE_X;
@@ -455,11 +346,7 @@ __global__ __launch_bounds__(STAGE_THREADS) void vjp_kernel(const GridConst gc, 
       if (idx < REGION) {
         const int rr = idx / W;
         const int cc = idx - rr * W;
-#pragma unroll
-        for (int f = 0; f < 6; ++f) s.f[f][rr][cc] = v[it][f];
-        s.f[6][rr][cc] = recip_staged(v[it][0]);
-#pragma unroll
-        for (int f = 0; f < 5; ++f) s.f[7 + f][rr][cc] = a_in * v[it][6 + f];
+        stage_node<T>(s, rr, cc, v[it], a_in);
       }
     }
   }
@@ -491,13 +378,13 @@ __global__ __launch_bounds__(STAGE_THREADS) void vjp_kernel(const GridConst gc, 
       if (ROLE == VJP_S4) {
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
-          Kout[f * N + od] = cq * qv[f] + cy * yb[f];
+          Kout[f * N + od] = fused(cq, qv[f], cy * yb[f]);
           Acc[f * N + od] = yb[f];
         }
       } else if (ROLE == VJP_S3 || ROLE == VJP_S2) {
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
-          Kout[f * N + od] = cq * qv[f] + cy * yb[f];
+          Kout[f * N + od] = fused(cq, qv[f], cy * yb[f]);
           Acc[f * N + od] = Acc[f * N + od] + yb[f];
         }
       } else {
@@ -517,33 +404,22 @@ __global__ __launch_bounds__(STAGE_THREADS) void vjp_kernel(const GridConst gc, 
 // YbarA gives the second evaluation's seed kbB = cqA qbar + cyA YbarA, which
 // replaces the first seed in LDS beside the second state YB (one-node halo),
 // and the second evaluation runs on the tile:
-//   PAIR 2: KinA = qbar, aA = dt/6 (the seed planes hold qbar itself and the
-//           seeds aA qbar are formed as they are read, so kbB takes qbar from
-//           LDS), YA = Y4, YB = Y3, (cqA, cyA) = (dt/3, dt),
+//   PAIR 2: KinA = qbar, aA = dt/6, YA = Y4, YB = Y3, (cqA, cyA) = (dt/3, dt),
 //           Kout = cqB qbar + cyB YbarB with (cqB, cyB) = (dt/3, dt/2),
-//           Acc = YbarA + YbarB (YbarA written after the first evaluation)
+//           Acc = YbarA + YbarB
 //   PAIR 1: KinA = the seed of S2, aA = 1, YA = Y2, YB = Y1 = q_n,
 //           (cqA, cyA) = (dt/6, dt/2), QbOut = qbar + (Acc + YbarA) + YbarB
 //           (a buffer other than Qb: neighbouring tiles still read qbar on
 //           their rings while this one writes)
-//   both:   bbar = (bbar + bbarA) + bbarB, the first sum written after the
-//           first evaluation.
-// Node by node this is the arithmetic of the two role kernels (the compiler
-// fuses the multiply-adds of the separately built kernels differently, so the
-// results agree to rounding), and the results do not depend on the tile
+//   both:   bbar = (bbar + bbarA) + bbarB.
+// YbarA and bbarA of the owned nodes stay in registers.  Node by node this is the
+// arithmetic of the two role kernels, and the results do not depend on the tile
 // shape.  Algorithmic traffic per node: 28 values for S4 + S3
-// (role kernels: 56) and 33 for S2 + S1 (61), plus the sums written between
-// the evaluations and read back (6 values each way, mostly served by L2); the
-// price is the ring of first evaluations (1 + 2 (TX + 2 + TY) / 512 of them
-// per owned node).
+// (role kernels: 56) and 33 for S2 + S1 (61); the price is the ring of first
+// evaluations (1 + 2 (TX + 2 + TY) / 512 of them per owned node).
 // The reverse kernels use the 512-node step tiles: 32 x 16 or 64 x 8.
 template <int TX>
 using VjpGeom = StepGeom<TX == 64 ? 8 : 16>;
-
-template <typename T, int TX>
-struct VjpPairSmem {
-  T f[12][VjpGeom<TX>::TY + 4][TX + 4];  // h u v w eta b 1/h | seeds of h u v w eta
-};
 
 template <typename T, int BCX, int BCY, int PAIR, int TX>
 __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridConst gc, const T* __restrict__ YA,
@@ -560,7 +436,7 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
   constexpr int H = 2;  // LDS position of tile node (0, 0)
   constexpr int RXA = TX + 2 * H, REGA = RXA * (TY + 2 * H);
   constexpr int RXB = TX + 2, REGB = RXB * (TY + 2);
-  __shared__ VjpPairSmem<T, TX> s;
+  __shared__ VjpSmem<T, TY + 2 * H, RXA> s;
   const int nx = gc.nx, ny = gc.ny;
   const size_t N = (size_t)nx * (size_t)ny;
   const int ntx = (nx + TX - 1) / TX;
@@ -594,11 +470,7 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
       if (idx < REGA) {
         const int rr = idx / RXA;
         const int cc = idx - rr * RXA;
-#pragma unroll
-        for (int f = 0; f < 6; ++f) s.f[f][rr][cc] = v[it][f];
-        s.f[6][rr][cc] = recip_staged(v[it][0]);
-#pragma unroll
-        for (int f = 0; f < 5; ++f) s.f[7 + f][rr][cc] = PAIR == 2 ? v[it][6 + f] : aA * v[it][6 + f];
+        stage_node<T>(s, rr, cc, v[it], aA);
       }
     }
   }
@@ -623,35 +495,21 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
     ev[q] = slot[q] && on_axis<BCX>(i0 + pc[q], nx) && on_axis<BCY>(j0 + pr[q], ny);
   __syncthreads();
 
-  // 2. First evaluation on the ring and the tile (periodic images of nodes
-  //    past a ragged edge included): the seeds of the second one.
-  //    The owned nodes' sums go to memory as the role kernels write them
-  //    (Acc, bbar; read back after the second evaluation, from L2).
-  T kbB[3][5];
+  // 2. First evaluation on the ring and the tile (periodic images of nodes past
+  //    a ragged edge included).
+  T ybA[3][5], bbA[3];
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     __builtin_amdgcn_sched_barrier(0);
     if (!ev[q]) continue;
     const int iw = wrap_or_clamp<BCX>(i0 + pc[q], nx), jw = wrap_or_clamp<BCY>(j0 + pr[q], ny);
-    const size_t o = (size_t)jw * nx + iw;
-    // PAIR 2: the seed planes hold qbar itself (KinA = qbar), scaled by aA as it is read
-    const Cot<T> out = vjp_node<T, BCX, BCY, PAIR == 2>(s, pr[q] + H, pc[q] + H, iw, jw, gc, aA);
-    const T yb[5] = {out.h, out.u, out.v, out.w, out.eta};
-#pragma unroll
-    for (int f = 0; f < 5; ++f)
-      kbB[q][f] = cqA * (PAIR == 2 ? s.f[7 + f][pr[q] + H][pc[q] + H] : Qb[f * N + o]) + cyA * yb[f];
-    if (q > 0 && i0 + pc[q] < nx && j0 + pr[q] < ny) {
-      if (PAIR == 2) {
-#pragma unroll
-        for (int f = 0; f < 5; ++f) Acc[f * N + o] = yb[f];
-      } else {
-#pragma unroll
-        for (int f = 0; f < 5; ++f) Acc[f * N + o] = Acc[f * N + o] + yb[f];
-      }
-      Bb[o] = Bb[o] + out.b;
-    }
+    const Cot<T> out = vjp_node<T, BCX, BCY>(s, pr[q] + H, pc[q] + H, iw, jw, gc);
+    ybA[q][0] = out.h, ybA[q][1] = out.u, ybA[q][2] = out.v, ybA[q][3] = out.w, ybA[q][4] = out.eta;
+    bbA[q] = out.b;
   }
-  // the second state, loaded while the other waves finish their evaluations
+  __builtin_amdgcn_sched_barrier(0);
+  // the second state, loaded while the other waves finish their evaluations,
+  // and the seeds of the second evaluation
   constexpr int ITB = (REGB + STAGE_THREADS - 1) / STAGE_THREADS;
   T w[ITB][5];
 #pragma unroll
@@ -665,6 +523,16 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
       for (int f = 0; f < 5; ++f) w[it][f] = YB[f * N + o];
     }
   }
+  T kbB[3][5];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    if (!ev[q]) continue;
+    const size_t o = (size_t)wrap_or_clamp<BCY>(j0 + pr[q], ny) * nx + wrap_or_clamp<BCX>(i0 + pc[q], nx);
+    T kb[5];
+#pragma unroll
+    for (int f = 0; f < 5; ++f) kb[f] = fused(cqA, Qb[f * N + o], cyA * ybA[q][f]);
+    staged_seed(kb, recip_staged(YB[o]), kbB[q]);
+  }
   __syncthreads();
 
   // 3. YB and its 1/h over the one-node halo (b stays), the new seeds on the
@@ -676,16 +544,13 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
     if (idx < REGB) {
       const int rr = idx / RXB + H - 1;
       const int cc = idx - (idx / RXB) * RXB + H - 1;
-#pragma unroll
-      for (int f = 0; f < 5; ++f) s.f[f][rr][cc] = w[it][f];
-      s.f[6][rr][cc] = recip_staged(w[it][0]);
+      s.store_state(rr, cc, w[it], (w[it][4] - w[it][0]) * recip_staged(w[it][0]));
     }
   }
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     if (!ev[q]) continue;
-#pragma unroll
-    for (int f = 0; f < 5; ++f) s.f[7 + f][pr[q] + H][pc[q] + H] = kbB[q][f];
+    s.store_seed(pr[q] + H, pc[q] + H, kbB[q]);
   }
   if (BCX == BC_REFLECTING || BCY == BC_REFLECTING) {
     __syncthreads();
@@ -695,8 +560,7 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
       // the reflecting axis clamps; on a periodic axis the position is its own
       const int ic = BCX == BC_REFLECTING ? wrap_or_clamp<BC_REFLECTING>(i0 + pc[q], nx) - i0 : pc[q];
       const int jc = BCY == BC_REFLECTING ? wrap_or_clamp<BC_REFLECTING>(j0 + pr[q], ny) - j0 : pr[q];
-#pragma unroll
-      for (int f = 0; f < 5; ++f) s.f[7 + f][pr[q] + H][pc[q] + H] = s.f[7 + f][jc + H][ic + H];
+      s.copy_seed(pr[q] + H, pc[q] + H, jc + H, ic + H);
     }
   }
   __syncthreads();
@@ -709,23 +573,27 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
     const int j = j0 + ly0 + k;
     if (i >= nx || j >= ny) continue;
     const size_t od = (size_t)j * nx + i;
-    T qv[5];
+    T qv[5], av[5];
 #pragma unroll
     for (int f = 0; f < 5; ++f) qv[f] = Qb[f * N + od];
+    if (PAIR == 1) {
+#pragma unroll
+      for (int f = 0; f < 5; ++f) av[f] = Acc[f * N + od];
+    }
     const T bv = Bb[od];
     const Cot<T> out = vjp_node<T, BCX, BCY>(s, ly0 + k + H, lx + H, i, j, gc);
     const T yb[5] = {out.h, out.u, out.v, out.w, out.eta};
     if (PAIR == 2) {
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        Kout[f * N + od] = cqB * qv[f] + cyB * yb[f];
-        Acc[f * N + od] = Acc[f * N + od] + yb[f];
+        Kout[f * N + od] = fused(cqB, qv[f], cyB * yb[f]);
+        Acc[f * N + od] = ybA[1 + k][f] + yb[f];
       }
     } else {
 #pragma unroll
-      for (int f = 0; f < 5; ++f) QbOut[f * N + od] = qv[f] + Acc[f * N + od] + yb[f];
+      for (int f = 0; f < 5; ++f) QbOut[f * N + od] = qv[f] + (av[f] + ybA[1 + k][f]) + yb[f];
     }
-    Bb[od] = bv + out.b;
+    Bb[od] = bv + bbA[1 + k] + out.b;
   }
 }
 
