@@ -221,12 +221,14 @@ __global__ __launch_bounds__(256) void surface_to_state(const T* __restrict__ ze
 }
 
 // zeta = h + b at the gauges, one row of the series.  Also the misfit against a
-// target row and the loss increment.  One block; thread t handles gauges t,
+// target row and the row's loss.  One block per row, the rows' states one after
+// the other in memory; thread t handles gauges t,
 // t + 256, ... and the loss increment is summed in a fixed tree order, so the
 // result is deterministic.
 // Gauge indices come from the caller: an index outside [0, N) is skipped and
 // raises FLAG_BADINDEX (reported as SGN_E_ARG by the next synchronizing call).
 constexpr int GAUGE_THREADS = 256;
+constexpr int MAX_GAUGES = 4096;
 
 template <typename T>
 __global__ __launch_bounds__(GAUGE_THREADS) void gauge_record(const T* __restrict__ q, const T* __restrict__ b,
@@ -236,6 +238,13 @@ __global__ __launch_bounds__(GAUGE_THREADS) void gauge_record(const T* __restric
                                                               double* __restrict__ misfit, double* __restrict__ loss,
                                                               int* __restrict__ flag) {
   __shared__ double part[GAUGE_THREADS];
+  const size_t row = blockIdx.x;
+  q += row * 5 * N;
+  if (series) series += row * ng;
+  if (target) {
+    target += row * ng;
+    misfit += row * ng;
+  }
   const int t = threadIdx.x;
   double acc = 0.0;
   for (int g = t; g < ng; g += GAUGE_THREADS) {
@@ -261,7 +270,23 @@ __global__ __launch_bounds__(GAUGE_THREADS) void gauge_record(const T* __restric
     if (t < w) part[t] += part[t + w];
     __syncthreads();
   }
-  if (t == 0) *loss += part[0];
+  if (t == 0) loss[row] = part[0];
+}
+
+// *loss = the rows' losses, added in row order.  One block.
+__global__ __launch_bounds__(GAUGE_THREADS) void loss_sum(const double* __restrict__ rows, int64_t n,
+                                                          double* __restrict__ loss) {
+  __shared__ double part[GAUGE_THREADS];
+  double sum = 0.0;
+  for (int64_t r0 = 0; r0 < n; r0 += GAUGE_THREADS) {
+    const int m = (int)(n - r0 < GAUGE_THREADS ? n - r0 : GAUGE_THREADS);
+    if ((int)threadIdx.x < m) part[threadIdx.x] = rows[r0 + threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int k = 0; k < m; ++k) sum += part[k];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *loss = sum;
 }
 
 // Adjoint seed of one misfit row: qbar_h += m and bbar += m at the gauges.
@@ -271,15 +296,26 @@ template <typename T>
 __global__ __launch_bounds__(GAUGE_THREADS) void gauge_seed(const int64_t* __restrict__ idx, int ng, size_t N,
                                                             const double* __restrict__ misfit, T* __restrict__ qbar,
                                                             T* __restrict__ bbar) {
+  __shared__ int64_t all[MAX_GAUGES];
   const int g = blockIdx.x * GAUGE_THREADS + threadIdx.x;
-  if (g >= ng) return;
-  const int64_t k = idx[g];
-  if (k < 0 || (size_t)k >= N) return;  // flagged by gauge_record
+  const int64_t k = g < ng ? idx[g] : -1;
+  const bool valid = k >= 0 && (size_t)k < N;  // others are flagged by gauge_record
+  T qa = T(0), ba = T(0);
+  double m = 0.0;
+  if (valid) {
+    qa = qbar[k];
+    ba = bbar[k];
+    m = misfit[g];
+  }
+  for (int e = threadIdx.x; e < ng; e += GAUGE_THREADS) all[e] = idx[e];
+  __syncthreads();
+  if (!valid) return;
   for (int e = 0; e < g; ++e)
-    if (idx[e] == k) return;
-  T qa = qbar[k], ba = bbar[k];
-  for (int e = g; e < ng; ++e) {
-    if (idx[e] != k) continue;
+    if (all[e] == k) return;
+  qa += T(m);
+  ba += T(m);
+  for (int e = g + 1; e < ng; ++e) {
+    if (all[e] != k) continue;
     qa += T(misfit[e]);
     ba += T(misfit[e]);
   }
@@ -316,13 +352,13 @@ hipError_t launch_surface(const sgn_ctx* c, const void* zeta0, void* q) {
   return hipGetLastError();
 }
 
-hipError_t launch_record(const sgn_ctx* c, const void* q, const int64_t* idx, int ng, double* series,
+hipError_t launch_record(const sgn_ctx* c, const void* q, int64_t rows, const int64_t* idx, int ng, double* series,
                          const double* target, double* misfit, double* loss) {
   if (c->p.dtype == SGN_F64)
-    hipLaunchKernelGGL(gauge_record<double>, dim3(1), dim3(GAUGE_THREADS), 0, c->stream, (const double*)q, (const double*)c->b, idx,
+    hipLaunchKernelGGL(gauge_record<double>, dim3((unsigned)rows), dim3(GAUGE_THREADS), 0, c->stream, (const double*)q, (const double*)c->b, idx,
                        ng, c->N, series, target, misfit, loss, c->flag);
   else
-    hipLaunchKernelGGL(gauge_record<float>, dim3(1), dim3(GAUGE_THREADS), 0, c->stream, (const float*)q, (const float*)c->b, idx,
+    hipLaunchKernelGGL(gauge_record<float>, dim3((unsigned)rows), dim3(GAUGE_THREADS), 0, c->stream, (const float*)q, (const float*)c->b, idx,
                        ng, c->N, series, target, misfit, loss, c->flag);
   return hipGetLastError();
 }
@@ -331,7 +367,7 @@ sgn_status gauge_args(sgn_ctx* c, const void* zeta0, int64_t nsteps, double dt, 
   sgn_status st = sgn_host::check_ctx(c, true);
   if (st) return st;
   if (!zeta0 || !idx) return fail(c, SGN_E_ARG, "zeta0 or gauge indices NULL");
-  if (ng <= 0 || ng > 4096) return fail(c, SGN_E_ARG, "need 1..4096 gauges");
+  if (ng <= 0 || ng > MAX_GAUGES) return fail(c, SGN_E_ARG, "need 1..4096 gauges");
   if (nsteps <= 0) return fail(c, SGN_E_ARG, "nsteps must be > 0");
   if (!(std::isfinite(dt) && dt > 0)) return fail(c, SGN_E_ARG, "dt must be finite and > 0");
   if (c->p.source != SGN_SRC_NONE) return fail(c, SGN_E_UNSUPPORTED, "rollouts are defined without source terms");
@@ -396,7 +432,7 @@ sgn_status sgn_gauge_series(sgn_ctx* c, const void* zeta0, int64_t nsteps, doubl
   for (int64_t n = 1; n <= nsteps; ++n) {
     HIPCHK(c, rollout_step(c, c->stream, cur, oth, dt));
     std::swap(cur, oth);
-    HIPCHK(c, launch_record(c, cur, gauge_idx, ngauges, series + (n - 1) * ngauges, nullptr, nullptr, nullptr));
+    HIPCHK(c, launch_record(c, cur, 1, gauge_idx, ngauges, series + (n - 1) * ngauges, nullptr, nullptr, nullptr));
   }
   return sgn_host::sync_results(c, 0);
 }
@@ -413,13 +449,18 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
   // T0 = nsteps - F are checkpointed every K steps and recomputed segment by
   // segment in the reverse sweep.
   const int64_t budget_states = c->adj_store_bytes / (int64_t)sb;
-  const int64_t F = budget_states >= 5 ? std::min<int64_t>(nsteps, (budget_states - 1) / 4) : 0;
-  const int64_t T0 = nsteps - F;
+  int64_t F = budget_states >= 5 ? std::min<int64_t>(nsteps, (budget_states - 1) / 4) : 0;
+  int64_t T0 = nsteps - F;
   int64_t K = 1, nseg = 0;
   if (T0 > 0) {
     K = checkpoint_every > 0 ? checkpoint_every : (int64_t)std::ceil(std::sqrt((double)T0));
     K = std::max<int64_t>(1, std::min<int64_t>(K, T0));
     nseg = (T0 + K - 1) / K;
+  }
+  if (F == 0) {  // the last segment's storage is free during the rollout: keep its steps too
+    F = T0 - (nseg - 1) * K;
+    T0 -= F;
+    --nseg;
   }
   const size_t slots = (size_t)std::max<int64_t>(T0 > 0 ? 4 * K + 1 : 0, F > 0 ? 4 * F + 1 : 0);
   auto& a = c->adj;
@@ -434,7 +475,7 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
     ok = ok && hipMalloc(&a.ckpt, (size_t)nseg * sb) == hipSuccess;
     if (ok) a.ckpt_slots = (size_t)nseg;
   }
-  const size_t mlen = (size_t)nsteps * (size_t)ngauges;
+  const size_t mlen = (size_t)nsteps * ((size_t)ngauges + 1);  // misfits, then a loss per step
   if (a.misfit_len < mlen) {
     if (a.misfit) (void)hipFree(a.misfit);
     a.misfit = nullptr;
@@ -450,9 +491,7 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
   hipStream_t s = c->stream;
   // 1. forward rollout: checkpoints every K steps over the first T0 steps, then
   //    the last F steps keeping every state and stage state (slot layout of a
-  //    segment: states 0..F at slots [0, F], stage triples from slot F+1);
-  //    misfits and loss throughout
-  HIPCHK(c, hipMemsetAsync(a.loss, 0, sizeof(double), s));
+  //    segment: states 0..F at slots [0, F], stage triples from slot F+1)
   HIPCHK(c, launch_surface(c, zeta0, a.state));
   void* cur = a.state;
   void* oth = c->acc;
@@ -468,8 +507,15 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
                                   slot(a.stages, (size_t)(k + 1), c), dt));
       cur = slot(a.stages, (size_t)(k + 1), c);
     }
-    HIPCHK(c, launch_record(c, cur, gauge_idx, ngauges, nullptr, target + n * ngauges, a.misfit + n * ngauges, a.loss));
   }
+  // The misfits and losses of a segment's steps, from its states in the slots: one
+  // launch a segment (one a step in the rollout took 5 us each, 5% of a gradient
+  // of 48 steps of 640 x 512).
+  double* const row_loss = a.misfit + (size_t)nsteps * (size_t)ngauges;
+  const auto record_segment = [&](int64_t n0, int64_t len) {
+    return launch_record(c, slot(a.stages, 1, c), len, gauge_idx, ngauges, nullptr, target + n0 * ngauges,
+                         a.misfit + n0 * ngauges, row_loss + n0);
+  };
   // 2. reverse sweep: the kept steps, then one segment at a time (recompute
   //    the segment keeping every state and stage state, then reverse its steps)
   HIPCHK(c, hipMemsetAsync(a.qbar, 0, sb, s));
@@ -490,6 +536,7 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
     if (out != a.qbar) std::swap(a.qbar, a.kb_b);  // both buffers belong to the context
     return SGN_OK;
   };
+  if (F > 0) HIPCHK(c, record_segment(T0, F));
   for (int64_t k = F - 1; k >= 0; --k)
     if ((st = reverse_from_slots(T0, F, k))) return st;
   for (int64_t seg = nseg - 1; seg >= 0; --seg) {
@@ -499,6 +546,7 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
     for (int64_t k = 0; k < len; ++k)
       HIPCHK(c, forward_step_keep(c, s, slot(a.stages, (size_t)k, c), slot(a.stages, (size_t)(len + 1 + 3 * k), c),
                                   slot(a.stages, (size_t)(k + 1), c), dt));
+    HIPCHK(c, record_segment(n0, len));
     for (int64_t k = len - 1; k >= 0; --k)
       if ((st = reverse_from_slots(n0, len, k))) return st;
   }
@@ -510,6 +558,8 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
   else
     hipLaunchKernelGGL(init_reverse<float>, grid, block, 0, s, (const float*)a.qbar, (const float*)grad_b,
                        (float*)grad_zeta0, (float*)grad_b, c->N);
+  HIPCHK(c, hipGetLastError());
+  hipLaunchKernelGGL(loss_sum, dim3(1), dim3(GAUGE_THREADS), 0, s, row_loss, nsteps, a.loss);
   HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipMemcpyAsync(c->host_result, a.loss, sizeof(double), hipMemcpyDeviceToHost, s));
   if ((st = sgn_host::sync_results(c, 0))) return st;
