@@ -119,7 +119,7 @@ enum : int { RK_CLASSIC = 0, RK_FSAL = 1, RK_RELAXED = 2 };
 template <typename T>
 struct RelaxIn {
   const T* ra;             // the previous step's RK4 result
-  const double* rs;        // rs[0] = gam of the previous step
+  const double* rs;        // gam of the previous step
   T* qbase;                // out: the relaxed state of the owned nodes
 };
 
@@ -354,10 +354,12 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
   }
   int health = 0;
   CSum rsum[2];
-  if (EPI != EPI_NONE) {
+  RelaxSums xsum;
+  if (EPI == EPI_TOTALS) {
     rsum[0].init();
     rsum[1].init();
   }
+  if (EPI == EPI_RELAX) xsum.init();
 #pragma unroll
   for (int st = 1; st <= 4; ++st) {
     T cy = st == 3 ? c1 : c2;             // Y_{st+1} = q + cy k_st
@@ -479,11 +481,8 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
             x[f] = (double)qo[k][f];
             d[f] = (double)nv[f] - x[f];
           }
-          double sv, dsv;
-          relax_node_terms(x, d, (double)cn.b, gc.g, gc.lam, 1.0, sv, dsv);
           const double M = axis_weight(i, nx, gc.bc_x, gc.dx) * axis_weight(j, ny, gc.bc_y, gc.dy);
-          rsum[0].add(M * sv);
-          rsum[1].add(M * dsv);
+          xsum.add(M, relax_node_terms(x, d, (double)cn.b, gc.g, gc.lam, 1.0));
         }
       }
     }
@@ -545,7 +544,13 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
   if constexpr (RK != RK_FSAL) {
     if (health) atomicOr(flag, health);
   }
-  if (EPI != EPI_NONE) {
+  if (EPI == EPI_RELAX) {
+    static_assert(sizeof(s) >= RELAX_LDS * sizeof(double), "the staging serves the reduction");
+    __syncthreads();  // of the staging, no longer read
+    block_merge(xsum, (double*)&s);
+    if (tid == 0) xsum.put(rpart);
+  }
+  if (EPI == EPI_TOTALS) {
     block_merge<2>(rsum);
     if (tid == 0) {
       rpart[0] = rsum[0].s;
@@ -556,7 +561,7 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
   }
 }
 
-// EPI != EPI_NONE: rpart holds 4 doubles per tile, in tile order.
+// EPI != EPI_NONE: rpart holds epi_part(EPI) doubles per tile, in tile order.
 template <typename T, int BCX, int BCY, bool SRC, int TY, bool SAVE = false, int EPI = EPI_NONE>
 __global__ __launch_bounds__(STAGE_THREADS) void step_kernel(const GridConst gc, const T* __restrict__ q,
                                                              const T* __restrict__ bplane, T* __restrict__ qout,
@@ -570,7 +575,7 @@ __global__ __launch_bounds__(STAGE_THREADS) void step_kernel(const GridConst gc,
   const int tile = xcd_tile(blockIdx.x, ntx * nty);
   step_tile<T, BCX, BCY, SRC, TY, SAVE, SRC ? 0 : 1, EPI>(s, gc, (tile % ntx) * TX, (tile / ntx) * TY, q, bplane,
                                                           qout, c6, c3, c2, c1, t0, dt, flag, ysave,
-                                                          EPI != EPI_NONE ? rpart + 4 * tile : nullptr);
+                                                          EPI != EPI_NONE ? rpart + epi_part(EPI) * tile : nullptr);
 }
 
 }  // namespace sgn

@@ -65,7 +65,7 @@ struct sgn_ctx {
   void* ya = nullptr;
   void* yb = nullptr;
   double* partials = nullptr;
-  double* tile_partials = nullptr;  // 4 doubles per step tile (the step kernel's epilogue sums)
+  double* tile_partials = nullptr;  // the epilogue sums of each step tile or run
   size_t tile_partials_cap = 0;     // doubles allocated there
   int* series_counter = nullptr;    // next slot of a recorded totals series (sgn_step_totals)
   double* result = nullptr;
@@ -136,13 +136,13 @@ hipError_t enqueue_pair_step(const sgn_ctx* c, hipStream_t s, void* cur, void* o
 // with `ysave` non-null the stage states Y2, Y3, Y4 go to three consecutive
 // state slots there; with `rpart` non-null each tile's epilogue sums `epi`
 // (sgn::EPI_RELAX: relaxation sums at gam = 1; sgn::EPI_TOTALS: mass and
-// energy of the new state) go to rpart[4 tile ..] (step_parts(c, epi) of them).
+// energy of the new state) go to rpart[epi_part(epi) tile ..] (step_parts(c, epi) of them).
 // Neither with source terms, and not both.
 hipError_t enqueue_step_into(const sgn_ctx* c, hipStream_t s, const void* cur, void* oth, double dt, double t,
                              void* ysave, double* rpart = nullptr, int epi = 0);
-// Number of epilogue sums (4 doubles each) a step with epilogue `epi` leaves.
+// Number of partial sums a step with epilogue `epi` leaves.
 int step_parts(const sgn_ctx* c, int epi);
-// Makes c->tile_partials hold the epilogue sums of either tile shape
+// Makes c->tile_partials hold the epilogue sums of every shape
 // (synchronizes and drops the graphs that captured an older buffer).
 sgn_status ensure_tile_partials(sgn_ctx* c);
 // Validation of sgn_params (the rules of sgn_create; failures leave their

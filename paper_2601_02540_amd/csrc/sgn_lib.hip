@@ -407,20 +407,21 @@ int step_parts(const sgn_ctx* c, int epi) {
 }
 
 sgn_status ensure_tile_partials(sgn_ctx* c) {
-  // room for the largest tile count of the tile shapes (32 x 24 has the fewest tiles)
+  // room for the largest tile count of the tile shapes (32 x 24 has the fewest tiles),
+  // for the march kernel's runs and for the blocks of a pass, at the size of the larger epilogue
   const size_t nx = (size_t)c->p.nx, ny = (size_t)c->p.ny;
-  // and for the march kernel's runs
-  const size_t tiles = std::max({((nx + 31) / 32) * ((ny + 15) / 16), ((nx + 63) / 64) * ((ny + 7) / 8),
-                                 (size_t)step_parts(c, sgn::EPI_TOTALS)});
-  if (c->tile_partials_cap >= 4 * tiles) return SGN_OK;
+  const size_t parts = std::max({((nx + 31) / 32) * ((ny + 15) / 16), ((nx + 63) / 64) * ((ny + 7) / 8),
+                                 (size_t)step_parts(c, sgn::EPI_TOTALS), std::min(ny, (size_t)sgn::RED_MAX_BLOCKS)});
+  const size_t need = sgn::RELAX_PART * parts;
+  if (c->tile_partials_cap >= need) return SGN_OK;
   SGN_HIPCHK(c, hipStreamSynchronize(c->stream));  // earlier steps may still write the old buffer
   if (c->tile_partials) (void)hipFree(c->tile_partials);
   c->tile_partials = nullptr;
   c->tile_partials_cap = 0;
   destroy_graphs(c);  // captured graphs hold the old address
-  if (hipMalloc((void**)&c->tile_partials, 4 * tiles * sizeof(double)) != hipSuccess)
+  if (hipMalloc((void**)&c->tile_partials, need * sizeof(double)) != hipSuccess)
     return fail(c, SGN_E_ALLOC, "per-tile partial sums");
-  c->tile_partials_cap = 4 * tiles;
+  c->tile_partials_cap = need;
   return SGN_OK;
 }
 

@@ -17,11 +17,11 @@ namespace sgn {
 constexpr int RED_THREADS = 256;
 constexpr int RED_MAX_BLOCKS = 1024;
 
-// Optional epilogue of the step tile: two compensated sums over the tile's
-// owned nodes, written as 4 doubles per tile (sum, error, sum, error).
+// Optional epilogue of the step tile: sums over the tile's owned nodes, written
+// per tile (EPI_TOTALS: two compensated sums as sum, error, sum, error).
 enum : int {
   EPI_NONE = 0,
-  EPI_RELAX = 1,   // M s(1) and M s'(1) of relaxation RK4 (relax_node_terms at gam = 1)
+  EPI_RELAX = 1,   // the relaxation sums at gam = 1 (RelaxSums; RELAX_PART doubles per tile)
   EPI_TOTALS = 2,  // M h and M E of the new state (mass and energy)
 };
 
@@ -38,8 +38,15 @@ __device__ __forceinline__ double energy_density(double h, double u, double v, d
 // density e and its derivative s'(gam), from the node's values x, increments d
 // and bottom b.  Each part of e is written out as a polynomial in gam (rational
 // for the lambda term), so the difference is never formed by subtraction.
-__device__ __forceinline__ void relax_node_terms(const double (&x)[5], const double (&dx)[5], double bb, double g,
-                                                 double lam, double gam, double& s, double& ds) {
+// Around gam the series of s goes on with (second coefficient c2 of the polynomial
+// parts) + t_2, t_3, t_4, ..., t_k = (-rho)^(k-1) t_1, where t_1 = dlam is the lambda
+// term's share of s' and rho = dh / (h + gam dh).
+struct RelaxTerms {
+  double s, ds, c2, dlam, rho;
+};
+__device__ __forceinline__ RelaxTerms relax_node_terms(const double (&x)[5], const double (&dx)[5], double bb,
+                                                       double g, double lam, double gam) {
+  RelaxTerms o;
   const double h = x[0], u = x[1], v = x[2], w = x[3], eta = x[4], b = bb;
   const double dh = dx[0], du = dx[1], dv = dx[2], dw = dx[3], deta = dx[4];
   const double H = h + gam * dh;
@@ -50,14 +57,18 @@ __device__ __forceinline__ void relax_node_terms(const double (&x)[5], const dou
   const double s_kin = 0.5 * (dh * (u * u + v * v) + H * (lin_uv + gam * sq_uv));
   const double s_w = (1.0 / 6.0) * (dh * w * w + H * (lin_w + gam * sq_w));
   const double s_pot = 0.5 * g * dh * (2.0 * h + 2.0 * b + gam * dh);
-  const double ihH2 = 1.0 / (h * H * H);  // one division for both lambda terms
+  const double hH = h * H;
+  const double ihH2 = recip_staged(hH * H);  // one reciprocal for both lambda terms and rho
   const double s_lam = (lam / 6.0) * (Nl * H) * ihH2;
   const double d_kin = 0.5 * (dh * (lin_uv + gam * sq_uv) + H * sq_uv);
   const double d_w = (1.0 / 6.0) * (dh * (lin_w + gam * sq_w) + H * sq_w);
   const double d_pot = 0.5 * g * dh * dh;
-  const double d_lam = (lam / 6.0) * (h * B * B * H - Nl * dh) * ihH2;
-  s = s_kin + s_w + s_pot + s_lam;
-  ds = d_kin + d_w + d_pot + d_lam;
+  o.dlam = (lam / 6.0) * (h * B * B * H - Nl * dh) * ihH2;
+  o.s = s_kin + s_w + s_pot + s_lam;
+  o.ds = d_kin + d_w + d_pot + o.dlam;
+  o.c2 = dh * (0.5 * sq_uv + (1.0 / 6.0) * sq_w);
+  o.rho = (dh * hH) * ihH2;
+  return o;
 }
 
 __device__ __forceinline__ void wave_merge(CSum& a) {
@@ -67,6 +78,109 @@ __device__ __forceinline__ void wave_merge(CSum& a) {
     const double c2 = __shfl_xor(a.c, off, 64);
     a.merge(s2, c2);
   }
+}
+
+// The M-weighted sums of relax_node_terms at gam = 1: s and s' compensated, the
+// next three coefficients of the series, sum M |t_5| and max |rho| (both for the
+// bound of what follows; a NaN stays in them).
+constexpr int RELAX_PART = 10;  // doubles a partial takes (one unused)
+constexpr int epi_part(int epi) { return epi == EPI_RELAX ? RELAX_PART : 4; }
+struct RelaxSums {
+  CSum s, ds;
+  double c2, c3, c4, rem, rho;
+  __device__ __forceinline__ void init() {
+    s.init();
+    ds.init();
+    c2 = c3 = c4 = rem = rho = 0.0;
+  }
+  __device__ __forceinline__ void add(double M, const RelaxTerms& t) {
+    s.add(M * t.s);
+    ds.add(M * t.ds);
+    const double mt2 = -t.rho * (M * t.dlam), mt3 = -t.rho * mt2, mt4 = -t.rho * mt3, mt5 = -t.rho * mt4;
+    c2 += M * t.c2 + mt2;
+    c3 += mt3;
+    c4 += mt4;
+    rem += fabs(mt5);
+    largest(fabs(t.rho));
+  }
+  __device__ __forceinline__ void largest(double r) { rho = (r > rho || r != r) ? r : rho; }
+  __device__ __forceinline__ void merge(const RelaxSums& o) {
+    s.merge(o.s.s, o.s.c);
+    ds.merge(o.ds.s, o.ds.c);
+    c2 += o.c2;
+    c3 += o.c3;
+    c4 += o.c4;
+    rem += o.rem;
+    largest(o.rho);
+  }
+  __device__ __forceinline__ void put(double* p) const {
+    p[0] = s.s, p[1] = s.c, p[2] = ds.s, p[3] = ds.c, p[4] = c2, p[5] = c3, p[6] = c4, p[7] = rem, p[8] = rho;
+    p[9] = 0.0;
+  }
+  __device__ __forceinline__ void get(const double* p) {
+    s.s = p[0], s.c = p[1], ds.s = p[2], ds.c = p[3], c2 = p[4], c3 = p[5], c4 = p[6], rem = p[7], rho = p[8];
+  }
+};
+
+// Reduces the sums over a block of RED_THREADS; thread 0 gets the result.  `sh`:
+// LDS for RELAX_LDS doubles that no thread reads or writes any more.  Half a wave
+// takes a quantity and merges the threads' values: shuffling all nine through
+// every wave cost the step tile's epilogue a tenth of the kernel.
+constexpr int RELAX_LDS = 9 * RED_THREADS;
+__device__ __forceinline__ void block_merge(RelaxSums& a, double* sh) {
+  const int t = threadIdx.x;
+  double p[RELAX_PART];
+  a.put(p);
+#pragma unroll
+  for (int k = 0; k < 9; ++k) sh[k * RED_THREADS + t] = p[k];
+  __syncthreads();
+  const int q = t / 32, r = t % 32;  // 0, 1: s and s'; 2 .. 5: c2, c3, c4, rem; 6: rho
+  CSum m;
+  m.init();
+  if (q < 2) {
+    const double *s0 = sh + 2 * q * RED_THREADS + r, *c0 = s0 + RED_THREADS;
+#pragma unroll
+    for (int k = 0; k < RED_THREADS; k += 32) m.merge(s0[k], c0[k]);
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) {
+      const double s2 = __shfl_xor(m.s, off, 64), c2 = __shfl_xor(m.c, off, 64);
+      m.merge(s2, c2);
+    }
+  } else if (q < 7) {
+    const double* s0 = sh + (2 + q) * RED_THREADS + r;
+    const bool most = q == 6;
+    const auto join = [&](double x) { m.s = most ? ((x > m.s || x != x) ? x : m.s) : m.s + x; };
+#pragma unroll
+    for (int k = 0; k < RED_THREADS; k += 32) join(s0[k]);
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) join(__shfl_xor(m.s, off, 64));
+  }
+  __syncthreads();
+  if (r == 0 && q < 7) {
+    if (q < 2) {
+      sh[2 * q] = m.s;
+      sh[2 * q + 1] = m.c;
+    } else {
+      sh[2 + q] = m.s;
+    }
+  }
+  __syncthreads();
+  if (t == 0) a.get(sh);
+}
+
+// True (for the whole block) in the last block of the grid to come here, which
+// then sees what the others' first threads wrote before.  The ticket is zero before and
+// after the kernel.
+__device__ __forceinline__ bool last_block(int* __restrict__ ticket) {
+  __shared__ int last;
+  if (threadIdx.x == 0) {
+    __threadfence();
+    last = atomicAdd(ticket, 1) == (int)gridDim.x - 1;
+    if (last) *ticket = 0;
+    __threadfence();
+  }
+  __syncthreads();
+  return last != 0;
 }
 
 // Reduces NQ compensated accumulators over the block; thread 0 gets the result.

@@ -18,38 +18,41 @@ using sgn_host::hip_fail;
 
 // Steps captured per graph replay.
 constexpr int RELAX_GRAPH_STEPS = 8;
+// Most blocks of relax_newton (c->partials holds their results).
+constexpr int RELAX_MERGE_BLOCKS = 256;
 
-// Device scalars of the relaxation: rs[0] = gam, rs[1] = t.  They live in the
-// context's result slots 4 and 5 (slots 0..3 serve the synchronizing totals).
-double* relax_scalars(const sgn_ctx* c) { return c->result + 4; }
+// The relaxation's device scalars lie in the context's result slots 4 .. 7 (slots
+// 0..3 serve the synchronizing totals).
+sgn::RelaxScalars* relax_scalars(const sgn_ctx* c) { return (sgn::RelaxScalars*)(c->result + 4); }
+static_assert(sizeof(sgn::RelaxScalars) == 4 * sizeof(double), "four result slots");
 
 int reduce_blocks(const sgn_ctx* c) { return c->p.ny < sgn::RED_MAX_BLOCKS ? c->p.ny : sgn::RED_MAX_BLOCKS; }
 
-// The Newton iterations for gam after an RK4 update base -> rk: the first from
-// the step kernel's per-tile sums (fused) or a pass of its own (pairs), the
-// second from a pass over (base, rk, b); rs[0] = gam, rs[1] += gam dt.
+// gam after an RK4 update base -> rk, and the time: from the step kernel's per-tile
+// sums (fused) or those of a pass (pairs), then where that was not enough from a pass.
 template <typename T>
 void enqueue_newton(const sgn_ctx* c, hipStream_t s, const void* base, const void* rk, bool fused, double dt) {
   const int nb = reduce_blocks(c);
-  double* rs = relax_scalars(c);
-  for (int it = 0; it < 2; ++it) {
-    if (it == 0 && fused) {
-      hipLaunchKernelGGL(sgn::relax_newton, dim3(1), dim3(sgn::RED_THREADS), 0, s, (const double*)c->tile_partials,
-                         sgn_host::step_parts(c, sgn::EPI_RELAX), rs, 1, 0, dt);
-      continue;
-    }
-    hipLaunchKernelGGL(sgn::relax_partial<T>, dim3(nb), dim3(sgn::RED_THREADS), 0, s, c->gc, (const T*)base,
-                       (const T*)rk, (const T*)c->b, (const double*)rs, it == 0 ? 1 : 0, c->partials);
-    hipLaunchKernelGGL(sgn::relax_newton, dim3(1), dim3(sgn::RED_THREADS), 0, s, (const double*)c->partials, nb,
-                       rs, it == 0 ? 1 : 0, it == 1 ? 1 : 0, dt);
-  }
+  sgn::RelaxScalars* rs = relax_scalars(c);
+  const dim3 block(sgn::RED_THREADS);
+  double* const sums = c->tile_partials;
+  const int n = fused ? sgn_host::step_parts(c, sgn::EPI_RELAX) : nb;
+  if (!fused)
+    hipLaunchKernelGGL(sgn::relax_sums<T>, dim3(nb), block, 0, s, c->gc, (const T*)base, (const T*)rk, (const T*)c->b,
+                       sums);
+  // a partial per thread: the merge is a chain of loads otherwise
+  const int per = std::max(sgn::RED_THREADS, (n + RELAX_MERGE_BLOCKS - 1) / RELAX_MERGE_BLOCKS);
+  hipLaunchKernelGGL(sgn::relax_newton, dim3((n + per - 1) / per), block, 0, s, (const double*)sums, n, per,
+                     c->partials, rs, dt);
+  hipLaunchKernelGGL(sgn::relax_second<T>, dim3(nb), block, 0, s, c->gc, (const T*)base, (const T*)rk, (const T*)c->b,
+                     rs, c->partials, dt);
 }
 
 template <typename T>
 hipError_t launch_update(const sgn_ctx* c, hipStream_t s, void* out, const void* base, const void* rk) {
   const size_t n5 = 5 * c->N;
   hipLaunchKernelGGL(sgn::relax_update<T>, dim3((unsigned)((n5 + 255) / 256)), dim3(256), 0, s, n5, (T*)out,
-                     (const T*)base, (const T*)rk, (const double*)relax_scalars(c));
+                     (const T*)base, (const T*)rk, (const sgn::RelaxScalars*)relax_scalars(c));
   return hipGetLastError();
 }
 
@@ -58,7 +61,7 @@ hipError_t launch_relax_step(const sgn_ctx* c, hipStream_t s, const void* qa, co
                              double dt) {
   constexpr int TX = sgn::StepGeom<TY>::TX;
   const int ntx = (c->p.nx + TX - 1) / TX, nty = (c->p.ny + TY - 1) / TY;
-  const sgn::RelaxIn<T> rx{(const T*)ra, relax_scalars(c), (T*)qbase};
+  const sgn::RelaxIn<T> rx{(const T*)ra, &relax_scalars(c)->gam, (T*)qbase};
   const dim3 grid((unsigned)(ntx * nty)), block(sgn::STAGE_THREADS);
 #define SGN_RLX(BX, BY)                                                                                             \
   hipLaunchKernelGGL((sgn::relax_step_kernel<T, BX, BY, TY>), grid, block, 0, s, c->gc, (const T*)qa, (const T*)c->b, \
@@ -75,7 +78,7 @@ hipError_t launch_relax_step(const sgn_ctx* c, hipStream_t s, const void* qa, co
 }
 
 // `steps` relaxed steps of q in place.  Pair path: per step the RK4 update into
-// acc, the two Newton iterations and the update pass.  Step-kernel paths: the
+// acc, gam and the update pass.  Step-kernel paths: the
 // first step updates q into acc; every later one stages the previous step's
 // relaxed state on the fly (relax_step_kernel), alternating between the buffer
 // pairs (q, acc) and (ya, yb); one update pass at the end writes q.
@@ -128,9 +131,9 @@ sgn_status sgn_step_relaxation(sgn_ctx* c, void* q, double dt, int64_t nsteps, d
   if (!std::isfinite(t0)) return fail(c, SGN_E_ARG, "t0 must be finite");
   if (c->p.source != SGN_SRC_NONE)
     return fail(c, SGN_E_UNSUPPORTED, "relaxation needs the energy-conserving semi-discretization (no source terms)");
-  if (c->step_path != SGN_PATH_PAIRS && (st = sgn_host::ensure_tile_partials(c))) return st;
+  if ((st = sgn_host::ensure_tile_partials(c))) return st;
   // the time accumulator starts at t0
-  hipLaunchKernelGGL(sgn::relax_set_time, dim3(1), dim3(64), 0, c->stream, relax_scalars(c), t0);
+  hipLaunchKernelGGL(sgn::relax_start, dim3(1), dim3(64), 0, c->stream, relax_scalars(c), t0);
   HIPCHK(c, hipGetLastError());
   int64_t left = nsteps;
   if (left >= RELAX_GRAPH_STEPS) {
@@ -164,7 +167,7 @@ sgn_status sgn_step_relaxation(sgn_ctx* c, void* q, double dt, int64_t nsteps, d
   }
   if (left > 0) HIPCHK(c, enqueue_relaxed_steps(c, c->stream, q, dt, (int)left));
   if (!t_end) return SGN_OK;
-  HIPCHK(c, hipMemcpyAsync(c->host_result + 5, relax_scalars(c) + 1, sizeof(double), hipMemcpyDeviceToHost,
+  HIPCHK(c, hipMemcpyAsync(c->host_result + 5, &relax_scalars(c)->t, sizeof(double), hipMemcpyDeviceToHost,
                            c->stream));
   if ((st = sgn_host::sync_results(c, 0))) return st;
   *t_end = c->host_result[5];

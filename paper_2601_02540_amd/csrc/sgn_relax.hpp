@@ -17,9 +17,16 @@
 //   lambda    (lam/6 (eta - h)^2 / h), A = eta - h, B = deta - dh:
 //                                  lam/6 [h (2AB + gam B^2) - dh A^2] / (h H)
 // with H = h + gam dh.  Their M-weighted sum s(gam) = (E(q_n + gam d) - E(q_n))/gam
-// has no root at gam = 0; two Newton iterations from gam = 1, with s'(gam) from
-// the same pass, find the relaxation root.  All of it in FP64 whatever the
-// storage type, with compensated, deterministic reductions.
+// has no root at gam = 0; two Newton iterations from gam = 1 find the relaxation
+// root.  All of it in FP64 whatever the storage type, with deterministic
+// reductions (s and s' compensated).
+//
+// The second iteration would take a pass over 11 values a node.  It takes s and s'
+// at its start gam_1 = 1 + delta from the series of s about 1 instead, whose
+// coefficients are summed along with s(1) and s'(1): the polynomial parts end with
+// delta^2, and the lambda term's coefficients fall by rho delta, rho = dh / (h + dh).
+// Where the terms from delta^5 on could move gam by more than 2^-56 (sum M |t_5|
+// bounds them), the pass runs.  2048^2 FP64 with walls: 71 + 5 us a step saved of 345.
 #pragma once
 
 #include "sgn_fused.hpp"
@@ -27,17 +34,120 @@
 
 namespace sgn {
 
-// Per-block partial sums of s(gam) and s'(gam) (compensated: 4 doubles per
-// block).  gam = 1 when `first`, else rs[0].
+// Device scalars of a relaxation run.
+struct RelaxScalars {
+  double gam, t;
+  double done;      // 1 when the second iteration has been made from the series
+  int ticket, pad;  // of last_block; zero between kernels
+};
+
+// One Newton update of gam from s and s' at gam.  A step without a usable root
+// (s' zero or not finite, or gam leaving [1/2, 3/2]) takes gam = 1.
+__device__ __forceinline__ double relax_next(double gam, double s, double ds) {
+  double next = gam;
+  if (ds != 0.0 && isfinite(s) && isfinite(ds)) next = gam - s / ds;
+  if (!(next >= 0.5 && next <= 1.5)) next = 1.0;
+  return next;
+}
+
+// Both iterations from the sums at gam = 1, the second one where its series is exact
+// enough (rs->done).
+static __device__ void relax_root(const RelaxSums& a, RelaxScalars* __restrict__ rs, double dt) {
+  const double s0 = a.s.s + a.s.c, s1 = a.ds.s + a.ds.c;
+  const bool root = s1 != 0.0 && isfinite(s0) && isfinite(s1);
+  const double d = root ? -s0 / s1 : 0.0;  // gam_1 - 1
+  double gam = relax_next(1.0, s0, s1);
+  double done = 1.0;  // without a usable root a second iteration repeats the first
+  if (root && 1.0 + d >= 0.5 && 1.0 + d <= 1.5) {
+    // s(1 + d) = s0 + s1 d + ..., the first two of which cancel
+    const double d2 = d * d;
+    const double s = d2 * (a.c2 + d * (a.c3 + d * a.c4));
+    const double ds = s1 + d * (2.0 * a.c2 + d * (3.0 * a.c3 + 4.0 * d * a.c4));
+    // sum_{k>=5} |t_k d^k| <= rem |d|^5 / (1 - |rho d|), and 5 rem |d|^4 / (1 - |rho d|)^2 for the derivative
+    const double x = 1.0 - a.rho * fabs(d);
+    const double es = a.rem * fabs(d) * d2 * d2 / x, eds = 5.0 * a.rem * d2 * d2 / (x * x);
+    const double lim = 0x1p-56 * fabs(ds);
+    if (x > 0.5 && es <= lim && eds * fabs(s) <= lim * fabs(ds) && isfinite(s) && isfinite(ds) && ds != 0.0) {
+      gam = (1.0 + d) - s / ds;
+      if (!(gam >= 0.5 && gam <= 1.5)) gam = 1.0;
+    } else {
+      done = 0.0;
+    }
+  }
+  rs->gam = gam;
+  rs->done = done;
+  if (done != 0.0) rs->t += gam * dt;
+}
+
+// The sums at gam = 1 of an RK4 update q -> qrk, per block (the pair path; the step
+// tile reduces them itself).
 template <typename T>
-__global__ __launch_bounds__(RED_THREADS) void relax_partial(const GridConst gc, const T* __restrict__ q,
-                                                             const T* __restrict__ qrk, const T* __restrict__ bplane,
-                                                             const double* __restrict__ rs, int first,
-                                                             double* __restrict__ partials) {
+__global__ __launch_bounds__(RED_THREADS) void relax_sums(const GridConst gc, const T* __restrict__ q,
+                                                          const T* __restrict__ qrk, const T* __restrict__ bplane,
+                                                          double* __restrict__ partials) {
   const int nx = gc.nx, ny = gc.ny;
   const size_t N = (size_t)nx * (size_t)ny;
-  const double g = gc.g, lam = gc.lam;
-  const double gam = first ? 1.0 : rs[0];
+  __shared__ double sh[RELAX_LDS];
+  RelaxSums a;
+  a.init();
+  for (int j = blockIdx.x; j < ny; j += gridDim.x) {
+    const double wy = axis_weight(j, ny, gc.bc_y, gc.dy);
+    for (int i = threadIdx.x; i < nx; i += RED_THREADS) {
+      const double M = axis_weight(i, nx, gc.bc_x, gc.dx) * wy;
+      const size_t o = (size_t)j * nx + i;
+      double x[5], dx[5];
+#pragma unroll
+      for (int f = 0; f < 5; ++f) {
+        x[f] = (double)q[f * N + o];
+        dx[f] = (double)qrk[f * N + o] - x[f];
+      }
+      a.add(M, relax_node_terms(x, dx, (double)bplane[o], gc.g, gc.lam, 1.0));
+    }
+  }
+  block_merge(a, sh);
+  if (threadIdx.x == 0) a.put(partials + RELAX_PART * blockIdx.x);
+}
+
+// gam from the partial sums at gam = 1: block b merges partials [b per, (b + 1) per),
+// the last block the blocks' results in order.
+static __global__ __launch_bounds__(RED_THREADS) void relax_newton(const double* __restrict__ in, int n, int per,
+                                                            double* __restrict__ out, RelaxScalars* __restrict__ rs,
+                                                            double dt) {
+  __shared__ double sh[RELAX_LDS];
+  RelaxSums a;
+  a.init();
+  const int lo = blockIdx.x * per, hi = lo + per < n ? lo + per : n;
+  for (int p = lo + threadIdx.x; p < hi; p += RED_THREADS) {
+    RelaxSums o;
+    o.get(in + (size_t)RELAX_PART * p);
+    a.merge(o);
+  }
+  block_merge(a, sh);
+  if (threadIdx.x == 0) a.put(out + RELAX_PART * blockIdx.x);
+  if (!last_block(&rs->ticket)) return;
+  a.init();
+  for (int p = threadIdx.x; p < (int)gridDim.x; p += RED_THREADS) {
+    RelaxSums o;
+    o.get(out + RELAX_PART * p);
+    a.merge(o);
+  }
+  __syncthreads();  // block_merge's LDS is used again
+  block_merge(a, sh);
+  if (threadIdx.x == 0) relax_root(a, rs, dt);
+}
+
+// The second iteration by a pass over the states, where the series was not enough:
+// per-block compensated sums of s and s' at rs->gam, the last block makes the
+// Newton update and advances the time by gam dt.
+template <typename T>
+__global__ __launch_bounds__(RED_THREADS) void relax_second(const GridConst gc, const T* __restrict__ q,
+                                                            const T* __restrict__ qrk, const T* __restrict__ bplane,
+                                                            RelaxScalars* __restrict__ rs,
+                                                            double* __restrict__ partials, double dt) {
+  if (rs->done != 0.0) return;
+  const int nx = gc.nx, ny = gc.ny;
+  const size_t N = (size_t)nx * (size_t)ny;
+  const double gam = rs->gam;
   CSum a[2];
   a[0].init();
   a[1].init();
@@ -52,10 +162,9 @@ __global__ __launch_bounds__(RED_THREADS) void relax_partial(const GridConst gc,
         x[f] = (double)q[f * N + o];
         dx[f] = (double)qrk[f * N + o] - x[f];
       }
-      double sv, dsv;
-      relax_node_terms(x, dx, (double)bplane[o], g, lam, gam, sv, dsv);
-      a[0].add(M * sv);
-      a[1].add(M * dsv);
+      const RelaxTerms t = relax_node_terms(x, dx, (double)bplane[o], gc.g, gc.lam, gam);
+      a[0].add(M * t.s);
+      a[1].add(M * t.ds);
     }
   }
   block_merge<2>(a);
@@ -65,70 +174,42 @@ __global__ __launch_bounds__(RED_THREADS) void relax_partial(const GridConst gc,
     partials[4 * blockIdx.x + 2] = a[1].s;
     partials[4 * blockIdx.x + 3] = a[1].c;
   }
-}
-
-// One block: s and s' from the partials (block order), one Newton update of
-// gam in rs[0] (from 1 when `first`).  A step without a usable root (s' zero or
-// not finite, or gam leaving [1/2, 3/2]) keeps gam = 1.  When `last`, the time
-// in rs[1] advances by gam dt.
-static __global__ __launch_bounds__(RED_THREADS) void relax_newton(const double* __restrict__ partials, int nparts,
-                                                            double* __restrict__ rs, int first, int last,
-                                                            double dt) {
-  CSum a[2];
+  if (!last_block(&rs->ticket)) return;
   a[0].init();
   a[1].init();
-  // Thread t merges partials t, t + 256, t + 512, ... in that order; the loads
-  // of eight of them are issued before the first merge (the step kernel leaves
-  // one partial per tile, tens of thousands of them).
-  constexpr int U = 8;
-  for (int p0 = threadIdx.x; p0 < nparts; p0 += U * RED_THREADS) {
-    double v[U][4];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int p = p0 + u * RED_THREADS;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[u][k] = p < nparts ? partials[4 * p + k] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (p0 + u * RED_THREADS >= nparts) break;
-      a[0].merge(v[u][0], v[u][1]);
-      a[1].merge(v[u][2], v[u][3]);
-    }
+  for (int p = threadIdx.x; p < (int)gridDim.x; p += RED_THREADS) {
+    a[0].merge(partials[4 * p + 0], partials[4 * p + 1]);
+    a[1].merge(partials[4 * p + 2], partials[4 * p + 3]);
   }
+  __syncthreads();
   block_merge<2>(a);
   if (threadIdx.x == 0) {
-    const double s = a[0].s + a[0].c, ds = a[1].s + a[1].c;
-    const double gam = first ? 1.0 : rs[0];
-    double next = gam;
-    if (ds != 0.0 && isfinite(s) && isfinite(ds)) next = gam - s / ds;
-    if (!(next >= 0.5 && next <= 1.5)) next = 1.0;
-    rs[0] = next;
-    if (last) rs[1] += next * dt;
+    const double next = relax_next(gam, a[0].s + a[0].c, a[1].s + a[1].c);
+    rs->gam = next;
+    rs->t += next * dt;
   }
 }
 
-// rs[1] = t0 (the time accumulator of a relaxation run).
-static __global__ void relax_set_time(double* __restrict__ rs, double t0) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) rs[1] = t0;
+// The scalars at the start of a relaxation run from time t0.
+static __global__ void relax_start(RelaxScalars* __restrict__ rs, double t0) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) *rs = RelaxScalars{1.0, t0, 0.0, 0, 0};
 }
 
 // out <- q + gam (q_RK4 - q), elementwise over the five planes (out may be q).
 template <typename T>
 __global__ __launch_bounds__(256) void relax_update(size_t n5, T* out, const T* q, const T* __restrict__ qrk,
-                                                    const double* __restrict__ rs) {
+                                                    const RelaxScalars* __restrict__ rs) {
   const size_t k = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (k >= n5) return;
-  const T gam = T(rs[0]);
+  const T gam = T(rs->gam);
   const T x = q[k];
   out[k] = fused(gam, qrk[k] - x, x);
 }
 
 // One RK4 step of a relaxation run after its first: the step tile stages the
 // relaxed state of the previous step, qa + gam (ra - qa), writes it out for
-// its owned nodes (qbase) beside the RK4 result (qout), and reduces the first
-// Newton iteration's sums per tile (EPI_RELAX), so no update pass runs between
-// the steps.
+// its owned nodes (qbase) beside the RK4 result (qout), and reduces the sums at
+// gam = 1 per tile (EPI_RELAX), so no update pass runs between the steps.
 template <typename T, int BCX, int BCY, int TY>
 __global__ __launch_bounds__(STAGE_THREADS) void relax_step_kernel(const GridConst gc, const T* __restrict__ qa,
                                                                    const T* __restrict__ bplane,
@@ -143,7 +224,7 @@ __global__ __launch_bounds__(STAGE_THREADS) void relax_step_kernel(const GridCon
   const int tile = xcd_tile(blockIdx.x, ntx * nty);
   step_tile<T, BCX, BCY, false, TY, false, 1, EPI_RELAX, RK_RELAXED>(
       s, gc, (tile % ntx) * TX, (tile / ntx) * TY, qa, bplane, qout, c6, c3, c2, c1, 0.0, dt, flag, nullptr,
-      rpart + 4 * tile, nullptr, &rx);
+      rpart + RELAX_PART * tile, nullptr, &rx);
 }
 
 }  // namespace sgn
