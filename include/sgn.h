@@ -91,7 +91,9 @@ typedef struct sgn_ctx sgn_ctx;
  * SGN_OPT_STEP_PATH: how sgn_step evaluates one RK4 step.
  *   SGN_PATH_FUSED (default): one kernel per step; the three intermediate
  *     stages stay in LDS (a four-node halo, evaluated redundantly in rings
- *     around each tile).  11 values of HBM traffic per node and step.
+ *     around each tile).  11 values of HBM traffic per node and step.  Small
+ *     grids (up to about 128 x 128) take two steps per kernel on 8 x 8 tiles
+ *     unless SGN_OPT_TILE_Y is set.
  *   SGN_PATH_PAIRS: two kernels, each fusing two stages; the intermediate
  *     stage stays in LDS.  37 values per node and step.
  *   SGN_PATH_STAGES: four kernels, one per stage.  84 values per node and step.

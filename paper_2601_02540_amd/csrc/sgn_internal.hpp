@@ -75,6 +75,7 @@ struct sgn_ctx {
   bool b_set = false;
   int step_path = SGN_PATH_FUSED;
   int tile_y = 8;     // stage and pair kernels
+  bool step_auto = true;  // the step kernel's shape is the size rule's (no height was set)
   int step_tile = 16;  // step kernel: 24 the march kernel's strips or 32 x 24 tiles, 16 32 x 16, 8 64 x 8
   sgn_host::GraphCache graphs[2];
   sgn_host::GraphCache relax_graph;   // relaxation steps (sgn_step_relaxation)
@@ -118,6 +119,16 @@ MarchPlan march_plan(const sgn_ctx* c);
 // mass and energy of the new state per task).
 hipError_t launch_march(const sgn_ctx* c, hipStream_t s, const MarchPlan& m, const void* qin, void* qout, double dt,
                         void* ysave, double* rpart);
+// Whether the small-grid kernel takes the steps (no stage saving, no totals): where
+// its 8 x 8 tiles are at most one per compute unit, in FP32 at most two.  A step
+// takes, tile kernel and this one, in us: FP64 64^2 9.4 and 5.1, 128^2 (one tile per
+// unit) 9.4 and 5.3, 192^2 (2.25) 9.6 and 10.3; FP32 7.9 and 4.0, 7.8 and 4.2, 8.0 and
+// 6.8, 256^2 (four) 8.0 and 9.0.
+bool small_pays(const sgn_ctx* c);
+// One or two steps by the small-grid kernel, qin into qout.
+hipError_t launch_small(const sgn_ctx* c, hipStream_t s, const void* qin, void* qout, double dt, int steps);
+// `steps` >= 1 steps by it of the state in q, which ends in q.
+hipError_t enqueue_small_steps(const sgn_ctx* c, hipStream_t s, void* q, double dt, int steps);
 // The tile shape a step kernel of this context runs (24: 32 x 24, ...).
 int tile_of(const sgn_ctx* c);
 

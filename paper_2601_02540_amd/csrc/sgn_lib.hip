@@ -227,6 +227,7 @@ hipError_t launch_fused_ty(const sgn_ctx* c, hipStream_t s, const void* qin, voi
 // every tile shape forms the same values.
 hipError_t launch_fused(const sgn_ctx* c, hipStream_t s, const void* qin, void* qout, double dt, double t0,
                         void* ysave = nullptr, double* rpart = nullptr, int epi = sgn::EPI_NONE) {
+  if (!ysave && !rpart && !c->prof_start && sgn_host::small_pays(c)) return sgn_host::launch_small(c, s, qin, qout, dt, 1);
   if (epi != sgn::EPI_RELAX) {
     const sgn_host::MarchPlan m = sgn_host::march_plan(c);
     if (m.tasks) return sgn_host::launch_march(c, s, m, qin, qout, dt, ysave, rpart);
@@ -305,6 +306,7 @@ hipError_t enqueue_single_step(const sgn_ctx* c, hipStream_t s, void* q, double 
 // pair and fused paths).
 hipError_t enqueue_steps(const sgn_ctx* c, hipStream_t s, void* q, double dt, int steps, double t0) {
   hipError_t e = hipSuccess;
+  if (sgn_host::small_pays(c)) return sgn_host::enqueue_small_steps(c, s, q, dt, steps);
   if (double_steps(c)) {
     for (int k = 0; k + 1 < steps && e == hipSuccess; k += 2) e = enqueue_double_step(c, s, q, dt, t0 + k * dt);
   } else {
@@ -313,10 +315,21 @@ hipError_t enqueue_steps(const sgn_ctx* c, hipStream_t s, void* q, double dt, in
   return e;
 }
 
+// Steps of `n` that the small-grid kernel takes outside the replays of GRAPH_STEPS
+// steps: the remainder, with one replay's steps where one or two are left (one step
+// ends in a copy, two are two launches).
+int64_t small_direct_steps(int64_t n) {
+  const int64_t r = n % GRAPH_STEPS;
+  return (r == 1 || r == 2) && n > GRAPH_STEPS ? r + GRAPH_STEPS : r;
+}
+
+// What of the step kernel's choice a captured graph depends on.
+int step_key(const sgn_ctx* c) { return sgn_host::small_pays(c) ? 0 : c->step_tile; }
+
 sgn_status get_graph(sgn_ctx* c, int slot, void* q, double dt, int steps, hipGraphExec_t* out) {
   GraphCache& g = c->graphs[slot];
   if (g.exec && g.q == q && g.dt == dt && g.steps == steps && g.path == c->step_path && g.tile_y == c->tile_y &&
-      g.step_tile == c->step_tile) {
+      g.step_tile == step_key(c)) {
     *out = g.exec;
     return SGN_OK;
   }
@@ -343,7 +356,7 @@ sgn_status get_graph(sgn_ctx* c, int slot, void* q, double dt, int steps, hipGra
   g.steps = steps;
   g.path = c->step_path;
   g.tile_y = c->tile_y;
-  g.step_tile = c->step_tile;
+  g.step_tile = step_key(c);
   *out = exec;
   return SGN_OK;
 }
@@ -650,7 +663,11 @@ sgn_status sgn_step(sgn_ctx* c, void* q, double dt, int64_t nsteps, double t0) {
     return SGN_OK;
   }
   int64_t left = nsteps;
-  if (c->step_path == SGN_PATH_FUSED && (left & 1)) {
+  if (sgn_host::small_pays(c)) {
+    const int64_t direct = small_direct_steps(left);
+    if (direct > 0) HIPCHK(c, sgn_host::enqueue_small_steps(c, c->stream, q, dt, (int)direct));
+    left -= direct;
+  } else if (c->step_path == SGN_PATH_FUSED && (left & 1)) {
     if (left == 1) {
       HIPCHK(c, enqueue_single_step(c, c->stream, q, dt, 0.0));
       return SGN_OK;
@@ -683,7 +700,8 @@ sgn_status sgn_prepare_step(sgn_ctx* c, void* q, double dt, int64_t nsteps) {
   if (nsteps == 0 || c->p.source != SGN_SRC_NONE) return SGN_OK;
   // the same split as sgn_step: an odd count of fused steps begins with three (or
   // is one) launched directly; 8-step replays, then 1- or 2-step replays
-  if (c->step_path == SGN_PATH_FUSED && (nsteps & 1)) nsteps -= nsteps == 1 ? 1 : 3;
+  if (sgn_host::small_pays(c)) nsteps -= small_direct_steps(nsteps);
+  else if (c->step_path == SGN_PATH_FUSED && (nsteps & 1)) nsteps -= nsteps == 1 ? 1 : 3;
   hipGraphExec_t ge;
   if (nsteps >= GRAPH_STEPS && (st = get_graph(c, 0, q, dt, GRAPH_STEPS, &ge))) return st;
   const int small = double_steps(c) ? 2 : 1;
@@ -700,6 +718,7 @@ sgn_status sgn_set_option(sgn_ctx* c, int32_t option, int64_t value) {
   } else if (option == SGN_OPT_TILE_Y) {
     if (value != 8 && value != 16 && value != 24) return fail(c, SGN_E_UNSUPPORTED, "tile height must be 8, 16 or 24");
     c->tile_y = value == 24 ? 16 : (int)value;
+    c->step_auto = false;
     c->step_tile = (int)value;
   } else if (option == SGN_OPT_ADJOINT_STORE) {
     if (value < 0) return fail(c, SGN_E_ARG, "adjoint storage must be >= 0 bytes");
