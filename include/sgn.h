@@ -384,7 +384,8 @@ sgn_status sgn_batch_cfl_dt(sgn_batch* batch, double cfl, double* dt);
  * 16 in SGN_F32). */
 sgn_status sgn_batch_set_step_path(sgn_batch* batch, int32_t path);
 /* Tile height (8 or 16, and 24 on the fused path; there 8 selects 64 x 8
- * tiles, 16 selects 32 x 16, and 24 selects 32 x 24 ones (FP64: 32 x 16) or, where
+ * tiles, 16 selects 32 x 16, and 24 selects 32 x 24 ones (FP64: 32 x 16 unless only
+ * 32 x 24 fit the compute units in one round) or, where
  * the ensemble holds 2^20 nodes and more and their shapes suit it, strips of 56
  * columns, one wave each) and persistent
  * workgroups per compute unit (1..16), or 0 for one workgroup per tile (the

@@ -38,6 +38,7 @@ struct sgn_batch {
   int nwork = 0;
   int work_key = 0;    // path and tiling the work list was built for
   bool march = false;  // its items are the march kernel's
+  int step_ty = 16;    // step tile height the work list was built for
   int* d_flags = nullptr;
   int* h_flags = nullptr;
   double* d_partials = nullptr;
@@ -116,10 +117,20 @@ std::vector<int> march_chunks(const sgn_batch* b) {
   return chunks;
 }
 
-// Tile height that the tile kernels run: FP64 32 x 24 tiles with a wall would need
-// more than 256 registers, so an FP64 ensemble runs 32 x 16 ones in their place.
+// Tile height that the tile kernels run.  FP64 32 x 24 tiles of all boundary pairs
+// take 278 registers, one workgroup per compute unit, so an FP64 ensemble at height 24
+// runs 32 x 16 ones, two per unit, unless only the 24 rows let its tiles fit the
+// units in one round: 21 instances of 36 .. 110 nodes a side 13.6 us a step on 32 x 24
+// tiles and 15.0 on 32 x 16, 60 of them 34.6 and 25.9, 8 of 32 .. 64 14.3 and 10.8.
 int tile_of(const sgn_batch* b) {
-  return b->path == SGN_PATH_FUSED && b->tile_y == 24 && b->dtype == SGN_F64 ? 16 : b->tile_y;
+  if (b->path != SGN_PATH_FUSED || b->tile_y != 24 || b->dtype != SGN_F64) return b->tile_y;
+  int64_t t16 = 0, t24 = 0;
+  for (const sgn_params& p : b->params) {
+    const int64_t nx = (p.nx + 31) / 32;
+    t16 += nx * ((p.ny + 15) / 16);
+    t24 += nx * ((p.ny + 23) / 24);
+  }
+  return t24 <= b->num_cus && t16 > b->num_cus ? 24 : 16;
 }
 
 int work_key(const sgn_batch* b) { return b->path * 100 + b->tile_y; }
@@ -149,6 +160,7 @@ sgn_status build_work(sgn_batch* b) {
   BCHK(b, hipMemcpy(b->d_work, work.data(), work.size() * sizeof(int), hipMemcpyHostToDevice));
   b->nwork = (int)work.size();
   b->march = !chunks.empty();
+  b->step_ty = tile_of(b);
   b->work_key = work_key(b);
   b->desc_dirty = true;
   drop_graph(b);
@@ -230,10 +242,11 @@ hipError_t enqueue_batch_step(const sgn_batch* b, hipStream_t s, int route) {
   if (b->path == SGN_PATH_FUSED) {
     if (b->march)
       return b->dtype == SGN_F64 ? launch_batch_march<double>(b, s, route) : launch_batch_march<float>(b, s, route);
-    const int ty = tile_of(b), bpc = b->tile_y == 24 ? 0 : b->blocks_per_cu;
+    const int ty = b->step_ty, bpc = b->tile_y == 24 ? 0 : b->blocks_per_cu;
     if (b->dtype == SGN_F64)
-      return ty == 16 ? launch_batch_step_t<double, 16>(b, s, route, bpc)
-                      : launch_batch_step_t<double, 8>(b, s, route, bpc);
+      return ty == 24   ? launch_batch_step_t<double, 24>(b, s, route, bpc)
+             : ty == 16 ? launch_batch_step_t<double, 16>(b, s, route, bpc)
+                        : launch_batch_step_t<double, 8>(b, s, route, bpc);
     return ty == 24   ? launch_batch_step_t<float, 24>(b, s, route, bpc)
            : ty == 16 ? launch_batch_step_t<float, 16>(b, s, route, bpc)
                       : launch_batch_step_t<float, 8>(b, s, route, bpc);
