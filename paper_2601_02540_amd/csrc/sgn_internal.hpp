@@ -153,6 +153,10 @@ hipError_t enqueue_step_into(const sgn_ctx* c, hipStream_t s, const void* cur, v
                              void* ysave, double* rpart = nullptr, int epi = 0);
 // Number of partial sums a step with epilogue `epi` leaves.
 int step_parts(const sgn_ctx* c, int epi);
+// Steps whose totals are merged in one launch: their partials are all kept, up to
+// 32 MB of them.
+constexpr int TOTALS_GROUP = 8;
+int totals_group(const sgn_ctx* c);
 // Makes c->tile_partials hold the epilogue sums of every shape
 // (synchronizes and drops the graphs that captured an older buffer).
 sgn_status ensure_tile_partials(sgn_ctx* c);

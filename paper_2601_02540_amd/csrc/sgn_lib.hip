@@ -419,13 +419,16 @@ int step_parts(const sgn_ctx* c, int epi) {
   return ((c->p.nx + tx - 1) / tx) * ((c->p.ny + ty - 1) / ty);
 }
 
+int totals_group(const sgn_ctx* c) { return step_parts(c, sgn::EPI_TOTALS) <= (1 << 17) ? TOTALS_GROUP : 1; }
+
 sgn_status ensure_tile_partials(sgn_ctx* c) {
   // room for the largest tile count of the tile shapes (32 x 24 has the fewest tiles),
   // for the march kernel's runs and for the blocks of a pass, at the size of the larger epilogue
   const size_t nx = (size_t)c->p.nx, ny = (size_t)c->p.ny;
   const size_t parts = std::max({((nx + 31) / 32) * ((ny + 15) / 16), ((nx + 63) / 64) * ((ny + 7) / 8),
                                  (size_t)step_parts(c, sgn::EPI_TOTALS), std::min(ny, (size_t)sgn::RED_MAX_BLOCKS)});
-  const size_t need = sgn::RELAX_PART * parts;
+  const size_t need = std::max((size_t)sgn::RELAX_PART * parts,
+                               4 * (size_t)totals_group(c) * (size_t)step_parts(c, sgn::EPI_TOTALS));
   if (c->tile_partials_cap >= need) return SGN_OK;
   SGN_HIPCHK(c, hipStreamSynchronize(c->stream));  // earlier steps may still write the old buffer
   if (c->tile_partials) (void)hipFree(c->tile_partials);

@@ -175,7 +175,7 @@ __device__ __forceinline__ bool last_block(int* __restrict__ ticket) {
   __shared__ int last;
   if (threadIdx.x == 0) {
     __threadfence();
-    last = atomicAdd(ticket, 1) == (int)gridDim.x - 1;
+    last = atomicAdd(ticket, 1) == (int)(gridDim.x * gridDim.y) - 1;
     if (last) *ticket = 0;
     __threadfence();
   }
@@ -252,14 +252,20 @@ __global__ __launch_bounds__(RED_THREADS) void totals_partial(const GridConst gc
   }
 }
 
-// Per-tile partials (4 doubles each: two compensated sums) of the step kernel's
-// epilogue, reduced in two deterministic levels.  Level 1: block b merges
-// partials [b per, min((b + 1) per, n)), thread t those at b per + t + 256 m.
-static __global__ __launch_bounds__(RED_THREADS) void partials_merge(const double* __restrict__ in, int n, int per,
-                                                              double* __restrict__ out) {
+// The recorded totals of gridDim.y steps from the partials (4 doubles each: two
+// compensated sums) of the step kernel's epilogue, step r's at in + 4 n r.
+// Block (b, r) merges partials [b per, min((b + 1) per, n)), thread t those at b per +
+// t + 256 m; the last block of all merges the blocks' results in block order and
+// writes them to series[2 k] and series[2 k + 1], k = counter[0] + r, which then
+// advances.  counter[1] is the ticket of last_block.
+static __global__ __launch_bounds__(RED_THREADS) void series_merge(const double* __restrict__ in, int n, int per,
+                                                            double* __restrict__ out, double* __restrict__ series,
+                                                            int* __restrict__ counter) {
   CSum a[2];
   a[0].init();
   a[1].init();
+  const int row = blockIdx.y, nb = gridDim.x;
+  in += (size_t)4 * n * row;
   const int lo = blockIdx.x * per;
   const int hi = lo + per < n ? lo + per : n;
   for (int p = lo + threadIdx.x; p < hi; p += RED_THREADS) {
@@ -268,36 +274,35 @@ static __global__ __launch_bounds__(RED_THREADS) void partials_merge(const doubl
   }
   block_merge<2>(a);
   if (threadIdx.x == 0) {
-    out[4 * blockIdx.x + 0] = a[0].s;
-    out[4 * blockIdx.x + 1] = a[0].c;
-    out[4 * blockIdx.x + 2] = a[1].s;
-    out[4 * blockIdx.x + 3] = a[1].c;
+    double* o = out + 4 * (row * nb + blockIdx.x);
+    o[0] = a[0].s;
+    o[1] = a[0].c;
+    o[2] = a[1].s;
+    o[3] = a[1].c;
   }
+  if (!last_block(counter + 1)) return;
+  const int k = counter[0];
+  for (int r = 0; r < (int)gridDim.y; ++r) {
+    a[0].init();
+    a[1].init();
+    for (int p = threadIdx.x; p < nb; p += RED_THREADS) {
+      const double* o = out + 4 * (r * nb + p);
+      a[0].merge(o[0], o[1]);
+      a[1].merge(o[2], o[3]);
+    }
+    __syncthreads();  // block_merge's LDS is used again
+    block_merge<2>(a);
+    if (threadIdx.x == 0) {
+      series[2 * (k + r)] = a[0].s + a[0].c;
+      series[2 * (k + r) + 1] = a[1].s + a[1].c;
+    }
+  }
+  if (threadIdx.x == 0) counter[0] = k + gridDim.y;
 }
 
-// Level 2 (one block): the two totals of the n level-1 partials go to
-// series[2 k] and series[2 k + 1], k = *counter, and the counter advances.
-static __global__ __launch_bounds__(RED_THREADS) void series_final(const double* __restrict__ in, int n,
-                                                            double* __restrict__ series, int* __restrict__ counter) {
-  CSum a[2];
-  a[0].init();
-  a[1].init();
-  for (int p = threadIdx.x; p < n; p += RED_THREADS) {
-    a[0].merge(in[4 * p + 0], in[4 * p + 1]);
-    a[1].merge(in[4 * p + 2], in[4 * p + 3]);
-  }
-  block_merge<2>(a);
-  if (threadIdx.x == 0) {
-    const int k = *counter;
-    series[2 * k] = a[0].s + a[0].c;
-    series[2 * k + 1] = a[1].s + a[1].c;
-    *counter = k + 1;
-  }
-}
-
-// *counter = 0 (start of a recorded series).
+// The counter and its ticket at the start of a recorded series.
 static __global__ void counter_reset(int* __restrict__ counter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0;
+  if (threadIdx.x < 2 && blockIdx.x == 0) counter[threadIdx.x] = 0;
 }
 
 // One block: combines nparts partials in block order; result[0..1] = totals.
