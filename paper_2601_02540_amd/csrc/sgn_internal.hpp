@@ -130,7 +130,7 @@ hipError_t launch_small(const sgn_ctx* c, hipStream_t s, const void* qin, void* 
 // `steps` >= 1 steps by it of the state in q, which ends in q.
 hipError_t enqueue_small_steps(const sgn_ctx* c, hipStream_t s, void* q, double dt, int steps);
 // The tile shape a step kernel of this context runs (24: 32 x 24, ...).
-int tile_of(const sgn_ctx* c);
+int tile_of(const sgn_ctx* c, int epi = 0);
 
 sgn_status fail(sgn_ctx* c, sgn_status st, const std::string& msg);
 sgn_status hip_fail(sgn_ctx* c, hipError_t e, const char* what);

@@ -67,9 +67,7 @@ hipError_t launch_relax_step(const sgn_ctx* c, hipStream_t s, const void* qa, co
   hipLaunchKernelGGL((sgn::relax_step_kernel<T, BX, BY, TY>), grid, block, 0, s, c->gc, (const T*)qa, (const T*)c->b, \
                      (T*)rk, rx, (T)(dt / 6.0), (T)(dt / 3.0), (T)(dt / 2.0), (T)dt, dt, c->flag, c->tile_partials)
   const int bx = c->p.bc_x, by = c->p.bc_y;
-  if constexpr (TY == 24 && sizeof(T) == 8) {  // periodic only (tile_of)
-    SGN_RLX(0, 0);
-  } else if (bx == 0 && by == 0) SGN_RLX(0, 0);
+  if (bx == 0 && by == 0) SGN_RLX(0, 0);
   else if (bx == 0 && by == 1) SGN_RLX(0, 1);
   else if (bx == 1 && by == 0) SGN_RLX(1, 0);
   else SGN_RLX(1, 1);
@@ -102,10 +100,12 @@ hipError_t enqueue_relaxed_steps_t(const sgn_ctx* c, hipStream_t s, void* q, dou
   enqueue_newton<T>(c, s, q, c->acc, true, dt);
   for (int k = 1; k < steps; ++k) {
     const int a = (k - 1) & 1, b = k & 1;
-    const int ty = sgn_host::tile_of(c);
-    e = ty == 24   ? launch_relax_step<T, 24>(c, s, base[a], rk[a], base[b], rk[b], dt)
-        : ty == 16 ? launch_relax_step<T, 16>(c, s, base[a], rk[a], base[b], rk[b], dt)
-                   : launch_relax_step<T, 8>(c, s, base[a], rk[a], base[b], rk[b], dt);
+    const int ty = sgn_host::tile_of(c, sgn::EPI_RELAX);
+    if constexpr (sizeof(T) == 4) {
+      if (ty == 24) e = launch_relax_step<T, 24>(c, s, base[a], rk[a], base[b], rk[b], dt);
+    }
+    if (ty == 16) e = launch_relax_step<T, 16>(c, s, base[a], rk[a], base[b], rk[b], dt);
+    if (ty == 8) e = launch_relax_step<T, 8>(c, s, base[a], rk[a], base[b], rk[b], dt);
     if (e) return e;
     enqueue_newton<T>(c, s, base[b], rk[b], true, dt);
   }
