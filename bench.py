@@ -52,13 +52,12 @@ HBM_PEAK_GBS = 8000.0
 #  fused:  the step kernel reads q, b and writes q_new -> 11 values, 1 launch
 PATHS = {"pairs": (37, 2), "stages": (84, 4), "fused": (11, 1)}
 # Arithmetic of one node and step as the kernels implement it, excluding the
-# step kernel's redundant ring evaluations: 4 right-hand sides of 178 flops
-# (56 for the 24 differences and the products they need, 12 for the node's own
-# products and constants, 9 for h_t, 33 each for the u and v rows, 17 for the
-# w-row fluxes, 5 for dividing the u, v, w rows by h, 12 for eta_t, 1 for the
-# reciprocal of h) and the stage updates (3 x 20 + 10).  Each add, multiply or
-# reciprocal counts 1, a fused multiply-add 2.
-FLOPS_PER_NODE_STEP = 4 * 178 + 70
+# step kernels' redundant evaluations: 4 right-hand sides of 133 flops (48 for
+# each axis' sums, 9 for the node's own products, 24 for joining the axes into the
+# five rates, 4 for e = (eta - h)^2/h and the reciprocal of h) and the stage
+# updates (3 x 20 + 10).  Each add, multiply or reciprocal counts 1, a fused
+# multiply-add 2.
+FLOPS_PER_NODE_STEP = 4 * 133 + 70
 FP64_VECTOR_PEAK_TFLOPS = 78.6
 # Untimed steps before the variants' timed runs (on a copy of the state): after an
 # idle spell of a few tens of ms the GPU runs the next ~30 launches up to 30%
@@ -67,21 +66,19 @@ SETTLE_STEPS = 64
 # Device memory the adjoint variant may fill with the stage states of the rollout's last
 # steps (beside its run that recomputes every step).
 ADJOINT_STORE_CAP_BYTES = 240 * 2**30
-# HBM traffic of the step kernel on the default workload (4096^2 periodic FP64,
-# its default 32 x 24 tiles), from the FETCH_SIZE and WRITE_SIZE passes
-# summarized in profiles/step_kernel_random_phase_4096_periodic_f64.md
-# (FETCH_SIZE scaled by 1.99992 and WRITE_SIZE by 1.0, the factors a plain
-# 1 GiB copy reads): bytes per node and launch.  Reported only while the kernel
-# sources hash to the value they had when the counters were taken (or to a later
-# version whose step kernel assembles to the same instructions: the relaxed-input
-# mode of the step tile added other instantiations only).
-STEP_TRAFFIC_BYTES_PER_NODE = (1082889614.0 + 671088640.0) / 16777216
+# HBM traffic of the step kernel on the default workload (4096^2 periodic FP64: the
+# march kernel), from the FETCH_SIZE and WRITE_SIZE passes summarized in
+# profiles/march_kernel_4096_periodic_f64.md (FETCH_SIZE scaled by 1.99992 and
+# WRITE_SIZE by 1.0, the factors a plain 1 GiB copy reads): bytes per node and
+# launch.  Reported only while the kernel sources hash to the value they had when
+# the counters were taken.
+STEP_TRAFFIC_BYTES_PER_NODE = (893248773.0 + 682858960.0) / 16777216
 STEP_KERNEL_SOURCES = ("sgn_common.hpp", "sgn_stage.hpp", "sgn_mms.hpp", "sgn_pair.hpp", "sgn_reduce.hpp",
-                       "sgn_fused.hpp")
-STEP_SOURCES_SHA256 = "4e8c6d844ce4d6910838e883f1ad1701f29b44e44029454f19aa51055cbf82fb"
+                       "sgn_fused.hpp", "sgn_march.hpp")
+STEP_SOURCES_SHA256 = "a3aaa151df40c0859d5d3b91d3a4f34303d79fbb2baaf2c02dcef9d4852766aa"
 KERNELS = {"pairs": "pair_kernel (two fused RK4 stages; mean over the 2 launches of a step)",
            "stages": "stage_kernel (fused RHS + RK4 stage; mean over the 4 launches of a step)",
-           "fused": "step_kernel (one whole RK4 step per launch)"}
+           "fused": "march_kernel (one whole RK4 step per launch)"}
 ALL_VARIANTS = {"f32", "reflecting", "ensemble", "small", "adjoint", "paths", "paper", "relaxation", "totals",
                 "adaptive", "longdrift"}
 
