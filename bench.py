@@ -75,7 +75,7 @@ ADJOINT_STORE_CAP_BYTES = 240 * 2**30
 STEP_TRAFFIC_BYTES_PER_NODE = (893248773.0 + 682858960.0) / 16777216
 STEP_KERNEL_SOURCES = ("sgn_common.hpp", "sgn_stage.hpp", "sgn_mms.hpp", "sgn_pair.hpp", "sgn_reduce.hpp",
                        "sgn_fused.hpp", "sgn_march.hpp")
-STEP_SOURCES_SHA256 = "a3aaa151df40c0859d5d3b91d3a4f34303d79fbb2baaf2c02dcef9d4852766aa"
+STEP_SOURCES_SHA256 = "7ba964abcd04071846f10f73d129251debf5a70258a5a2120a7fcc531226b929"
 KERNELS = {"pairs": "pair_kernel (two fused RK4 stages; mean over the 2 launches of a step)",
            "stages": "stage_kernel (fused RHS + RK4 stage; mean over the 4 launches of a step)",
            "fused": "march_kernel (one whole RK4 step per launch)"}

@@ -1,11 +1,11 @@
 // sgn_batch.hpp -- an ensemble of independent problems in one launch per RK4
-// step (step tiles) or per stage pair (pair tiles).
+// step (step tiles, or the march kernel's strips) or per stage pair (pair tiles).
 //
 // Every instance has its own grid size, boundary types, spacing, g, lambda and
 // time step.  The tiles of all instances form one work list (instance-major,
 // row-major tiles within an instance), cut into eight contiguous ranges, one per
 // XCD, so tiles of the same instance (and their shared halo rows) stay in one
-// L2.  Each work item runs the same tile code as the single-problem kernels,
+// L2.  Each work item runs the same tile or strip code as the single-problem kernels,
 // with the boundary variant chosen per instance at run time (uniform per
 // workgroup).  A launch has either one workgroup per work item or a persistent
 // grid of workgroups that walks the list.
