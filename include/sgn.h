@@ -318,7 +318,10 @@ sgn_status sgn_step_vjp(sgn_ctx* ctx, const void* q_n, double dt, void* qbar, vo
  * advance nsteps RK4 steps of size dt and record zeta = h + b at the gauge
  * nodes gauge_idx[g] (device int64 row-major node indices, 1..4096 gauges)
  * after every step into series[n * ngauges + g] (device doubles, n = 0 is the
- * state after the first step).  Synchronizes. */
+ * state after the first step).  In SGN_F64 the rollouts of this call and of
+ * sgn_gauge_loss_grad form the right-hand side term by term as printed, so their
+ * states agree with those of sgn_step to rounding (in SGN_F32 bit for bit); the
+ * step path changes no bit.  Synchronizes. */
 sgn_status sgn_gauge_series(sgn_ctx* ctx, const void* zeta0, int64_t nsteps, double dt, const int64_t* gauge_idx,
                             int32_t ngauges, double* series);
 
@@ -338,7 +341,11 @@ sgn_status sgn_gauge_series(sgn_ctx* ctx, const void* zeta0, int64_t nsteps, dou
  * afterwards), the reverse sweep reverses those without recomputing them, and
  * the checkpoints and segments cover the first nsteps - F steps only
  * (checkpoint_every 0: ceil(sqrt(nsteps - F))).  Loss and gradients are the
- * same bit for bit whatever B.  *loss is a host double.  Synchronizes.
+ * same bit for bit whatever B.  Conditioning: grad_b is the difference of the
+ * bottom's own cotangent and grad_zeta0.  Around gauges in water at rest the two
+ * cancel (the surface there does not depend on the bottom), so what is left of grad_b
+ * has an absolute error of rounding times grad_zeta0 and few or no digits of its own.
+ * *loss is a host double.  Synchronizes.
  * Errors: SGN_E_ALLOC when the storage cannot be allocated. */
 sgn_status sgn_gauge_loss_grad(sgn_ctx* ctx, const void* zeta0, int64_t nsteps, double dt, const int64_t* gauge_idx,
                                int32_t ngauges, const double* target, int64_t checkpoint_every, double* loss,

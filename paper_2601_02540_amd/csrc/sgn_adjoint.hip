@@ -11,6 +11,7 @@
 #include "sgn_reduce.hpp"
 #include "sgn_pair.hpp"
 #include "sgn_vjp.hpp"
+#include "sgn_vjp_terms.hpp"
 
 namespace {
 
@@ -20,7 +21,7 @@ using sgn_host::hip_fail;
 
 constexpr int VJP_TY = 8;
 
-template <typename T, int ROLE>
+template <typename T, int ROLE, int FORM>
 hipError_t launch_vjp_t(const sgn_ctx* c, hipStream_t s, const void* Y, const void* Kin, void* Qb, void* Kout,
                         void* Acc, void* Bb, double a_in, double cq, double cy) {
   const int ntx = (c->p.nx + sgn::TILE_X - 1) / sgn::TILE_X;
@@ -29,9 +30,15 @@ hipError_t launch_vjp_t(const sgn_ctx* c, hipStream_t s, const void* Y, const vo
   const T* Yp = (const T*)Y;
   const T* bp = (const T*)c->b;
   const T* kp = (const T*)Kin;
-#define SGN_VJP(BX, BY)                                                                                       \
-  hipLaunchKernelGGL((sgn::vjp_kernel<T, BX, BY, ROLE, VJP_TY>), grid, block, 0, s, c->gc, Yp, bp, kp, (T*)Qb, \
-                     (T*)Kout, (T*)Acc, (T*)Bb, (T)a_in, (T)cq, (T)cy)
+#define SGN_VJP(BX, BY)                                                                                         \
+  do {                                                                                                          \
+    if constexpr (FORM == sgn::FORM_TERMS)                                                                      \
+      hipLaunchKernelGGL((sgn::terms::vjp_kernel<T, BX, BY, ROLE, VJP_TY>), grid, block, 0, s, c->gc, Yp, bp, kp, \
+                         (T*)Qb, (T*)Kout, (T*)Acc, (T*)Bb, (T)a_in, (T)cq, (T)cy);                             \
+    else                                                                                                        \
+      hipLaunchKernelGGL((sgn::vjp_kernel<T, BX, BY, ROLE, VJP_TY>), grid, block, 0, s, c->gc, Yp, bp, kp, (T*)Qb, \
+                         (T*)Kout, (T*)Acc, (T*)Bb, (T)a_in, (T)cq, (T)cy);                                     \
+  } while (0)
   const int bx = c->p.bc_x, by = c->p.bc_y;
   if (bx == 0 && by == 0) SGN_VJP(0, 0);
   else if (bx == 0 && by == 1) SGN_VJP(0, 1);
@@ -41,14 +48,19 @@ hipError_t launch_vjp_t(const sgn_ctx* c, hipStream_t s, const void* Y, const vo
   return hipGetLastError();
 }
 
+// A reverse stage; `terms`: in the form of the FP64 gauge rollouts (sgn::FORM_TERMS).
 template <int ROLE>
 hipError_t launch_vjp(const sgn_ctx* c, hipStream_t s, const void* Y, const void* Kin, void* Qb, void* Kout,
-                      void* Acc, void* Bb, double a_in, double cq, double cy) {
-  if (c->p.dtype == SGN_F64) return launch_vjp_t<double, ROLE>(c, s, Y, Kin, Qb, Kout, Acc, Bb, a_in, cq, cy);
-  return launch_vjp_t<float, ROLE>(c, s, Y, Kin, Qb, Kout, Acc, Bb, a_in, cq, cy);
+                      void* Acc, void* Bb, double a_in, double cq, double cy, bool terms = false) {
+  if constexpr (ROLE != sgn::VJP_PLAIN) {
+    if (terms) return launch_vjp_t<double, ROLE, sgn::FORM_TERMS>(c, s, Y, Kin, Qb, Kout, Acc, Bb, a_in, cq, cy);
+  }
+  if (c->p.dtype == SGN_F64)
+    return launch_vjp_t<double, ROLE, sgn::FORM_SHARED>(c, s, Y, Kin, Qb, Kout, Acc, Bb, a_in, cq, cy);
+  return launch_vjp_t<float, ROLE, sgn::FORM_SHARED>(c, s, Y, Kin, Qb, Kout, Acc, Bb, a_in, cq, cy);
 }
 
-template <typename T, int PAIR, int TX>
+template <typename T, int PAIR, int TX, int FORM>
 hipError_t launch_vjp_pair_t(const sgn_ctx* c, hipStream_t s, const void* YA, const void* YB, const void* KinA,
                              const void* Qb, void* QbOut, void* Kout, void* Acc, void* Bb, double aA, double cqA,
                              double cyA, double cqB, double cyB) {
@@ -56,16 +68,21 @@ hipError_t launch_vjp_pair_t(const sgn_ctx* c, hipStream_t s, const void* YA, co
   const int ntx = (c->p.nx + TX - 1) / TX;
   const int nty = (c->p.ny + TY - 1) / TY;
   const dim3 grid((unsigned)(ntx * nty)), block(sgn::STAGE_THREADS);
-#define SGN_VJPP(BX, BY)                                                                                         \
-  hipLaunchKernelGGL((sgn::vjp_pair_kernel<T, BX, BY, PAIR, TX>), grid, block, 0, s, c->gc, (const T*)YA,        \
-                     (const T*)YB, (const T*)c->b, (const T*)KinA, (const T*)Qb, (T*)QbOut, (T*)Kout, (T*)Acc,   \
-                     (T*)Bb, (T)aA, (T)cqA, (T)cyA, (T)cqB, (T)cyB)
+#define SGN_VJPP_K(KERNEL)                                                                                      \
+  hipLaunchKernelGGL(KERNEL, grid, block, 0, s, c->gc, (const T*)YA, (const T*)YB, (const T*)c->b, (const T*)KinA, \
+                     (const T*)Qb, (T*)QbOut, (T*)Kout, (T*)Acc, (T*)Bb, (T)aA, (T)cqA, (T)cyA, (T)cqB, (T)cyB)
+#define SGN_VJPP(BX, BY)                                                                                        \
+  do {                                                                                                          \
+    if constexpr (FORM == sgn::FORM_TERMS) SGN_VJPP_K((sgn::terms::vjp_pair_kernel<T, BX, BY, PAIR, TX>));      \
+    else SGN_VJPP_K((sgn::vjp_pair_kernel<T, BX, BY, PAIR, TX>));                                               \
+  } while (0)
   const int bx = c->p.bc_x, by = c->p.bc_y;
   if (bx == 0 && by == 0) SGN_VJPP(0, 0);
   else if (bx == 0 && by == 1) SGN_VJPP(0, 1);
   else if (bx == 1 && by == 0) SGN_VJPP(1, 0);
   else SGN_VJPP(1, 1);
 #undef SGN_VJPP
+#undef SGN_VJPP_K
   return hipGetLastError();
 }
 
@@ -74,15 +91,14 @@ hipError_t launch_vjp_pair_t(const sgn_ctx* c, hipStream_t s, const void* YA, co
 template <int PAIR>
 hipError_t launch_vjp_pair(const sgn_ctx* c, hipStream_t s, const void* YA, const void* YB, const void* KinA,
                            const void* Qb, void* QbOut, void* Kout, void* Acc, void* Bb, double aA, double cqA,
-                           double cyA, double cqB, double cyB) {
-  if (c->p.dtype == SGN_F64) {
-    if (c->step_tile != 8)
-      return launch_vjp_pair_t<double, PAIR, 32>(c, s, YA, YB, KinA, Qb, QbOut, Kout, Acc, Bb, aA, cqA, cyA, cqB, cyB);
-    return launch_vjp_pair_t<double, PAIR, 64>(c, s, YA, YB, KinA, Qb, QbOut, Kout, Acc, Bb, aA, cqA, cyA, cqB, cyB);
-  }
-  if (c->step_tile != 8)
-    return launch_vjp_pair_t<float, PAIR, 32>(c, s, YA, YB, KinA, Qb, QbOut, Kout, Acc, Bb, aA, cqA, cyA, cqB, cyB);
-  return launch_vjp_pair_t<float, PAIR, 64>(c, s, YA, YB, KinA, Qb, QbOut, Kout, Acc, Bb, aA, cqA, cyA, cqB, cyB);
+                           double cyA, double cqB, double cyB, bool terms) {
+#define SGN_VP(T, TX, FORM) \
+  launch_vjp_pair_t<T, PAIR, TX, sgn::FORM>(c, s, YA, YB, KinA, Qb, QbOut, Kout, Acc, Bb, aA, cqA, cyA, cqB, cyB)
+  const bool wide = c->step_tile == 8;
+  if (terms) return wide ? SGN_VP(double, 64, FORM_TERMS) : SGN_VP(double, 32, FORM_TERMS);
+  if (c->p.dtype == SGN_F64) return wide ? SGN_VP(double, 64, FORM_SHARED) : SGN_VP(double, 32, FORM_SHARED);
+  return wide ? SGN_VP(float, 64, FORM_SHARED) : SGN_VP(float, 32, FORM_SHARED);
+#undef SGN_VP
 }
 
 size_t state_bytes(const sgn_ctx* c) { return 5 * c->N * c->esize; }
@@ -115,7 +131,7 @@ sgn_status ensure_stage_slots(sgn_ctx* c, size_t slots) {
   return SGN_OK;
 }
 
-template <typename T, int PAIR, int TY>
+template <typename T, int PAIR, int TY, int FORM>
 hipError_t launch_pair_save_t(const sgn_ctx* c, hipStream_t s, const void* Yin, const void* qn, void* acc,
                               void* yb, void* ysave, void* qout, double c1_acc, double c1_y, double c2_acc,
                               double c2_y) {
@@ -123,7 +139,7 @@ hipError_t launch_pair_save_t(const sgn_ctx* c, hipStream_t s, const void* Yin, 
   const int nty = (c->p.ny + TY - 1) / TY;
   const dim3 grid((unsigned)(ntx * nty)), block(sgn::STAGE_THREADS);
 #define SGN_PS(BX, BY)                                                                                         \
-  hipLaunchKernelGGL((sgn::pair_save_kernel<T, BX, BY, PAIR, TY>), grid, block, 0, s, c->gc, (const T*)Yin,      \
+  hipLaunchKernelGGL((sgn::pair_save_kernel<T, BX, BY, PAIR, TY, FORM>), grid, block, 0, s, c->gc, (const T*)Yin,      \
                      (const T*)c->b, (const T*)qn, (T*)acc, (T*)yb, (T*)ysave, (T*)qout, (T)c1_acc, (T)c1_y, \
                      (T)c2_acc, (T)c2_y, c->flag)
   const int bx = c->p.bc_x, by = c->p.bc_y;
@@ -137,16 +153,76 @@ hipError_t launch_pair_save_t(const sgn_ctx* c, hipStream_t s, const void* Yin, 
 
 template <int PAIR>
 hipError_t launch_pair_save(const sgn_ctx* c, hipStream_t s, const void* Yin, const void* qn, void* acc, void* yb,
-                            void* ysave, void* qout, double c1_acc, double c1_y, double c2_acc, double c2_y) {
-  if (c->p.dtype == SGN_F64) {
-    if (c->tile_y == 16)
-      return launch_pair_save_t<double, PAIR, 16>(c, s, Yin, qn, acc, yb, ysave, qout, c1_acc, c1_y, c2_acc, c2_y);
-    return launch_pair_save_t<double, PAIR, 8>(c, s, Yin, qn, acc, yb, ysave, qout, c1_acc, c1_y, c2_acc, c2_y);
-  }
-  if (c->tile_y == 16)
-    return launch_pair_save_t<float, PAIR, 16>(c, s, Yin, qn, acc, yb, ysave, qout, c1_acc, c1_y, c2_acc, c2_y);
-  return launch_pair_save_t<float, PAIR, 8>(c, s, Yin, qn, acc, yb, ysave, qout, c1_acc, c1_y, c2_acc, c2_y);
+                            void* ysave, void* qout, double c1_acc, double c1_y, double c2_acc, double c2_y,
+                            bool terms) {
+#define SGN_PSV(T, TY, FORM) \
+  launch_pair_save_t<T, PAIR, TY, sgn::FORM>(c, s, Yin, qn, acc, yb, ysave, qout, c1_acc, c1_y, c2_acc, c2_y)
+  const bool tall = c->tile_y == 16;
+  if (terms) return tall ? SGN_PSV(double, 16, FORM_TERMS) : SGN_PSV(double, 8, FORM_TERMS);
+  if (c->p.dtype == SGN_F64) return tall ? SGN_PSV(double, 16, FORM_SHARED) : SGN_PSV(double, 8, FORM_SHARED);
+  return tall ? SGN_PSV(float, 16, FORM_SHARED) : SGN_PSV(float, 8, FORM_SHARED);
+#undef SGN_PSV
 }
+
+// The step kernel in FORM_TERMS (FP64 gauge rollouts), on the context's step tile; with
+// stage saving on 32 x 16 ones where that is 32 x 24.
+template <int TY, bool SAVE>
+hipError_t launch_terms_step_ty(const sgn_ctx* c, hipStream_t s, const void* qin, void* qout, double dt, void* ysave) {
+  constexpr int TX = sgn::StepGeom<TY>::TX;
+  const int ntx = (c->p.nx + TX - 1) / TX, nty = (c->p.ny + TY - 1) / TY;
+  const dim3 grid((unsigned)(ntx * nty)), block(sgn::STAGE_THREADS);
+#define SGN_TERMS(BX, BY)                                                                                        \
+  hipLaunchKernelGGL((sgn::terms::rollout_kernel<BX, BY, TY, SAVE>), grid, block, 0, s, c->gc, (const double*)qin, \
+                     (const double*)c->b, (double*)qout, dt / 6.0, dt / 3.0, dt / 2.0, dt, c->flag, (double*)ysave)
+  const int bx = c->p.bc_x, by = c->p.bc_y;
+  if (bx == 0 && by == 0) SGN_TERMS(0, 0);
+  else if (bx == 0 && by == 1) SGN_TERMS(0, 1);
+  else if (bx == 1 && by == 0) SGN_TERMS(1, 0);
+  else SGN_TERMS(1, 1);
+#undef SGN_TERMS
+  return hipGetLastError();
+}
+
+hipError_t launch_terms_step(const sgn_ctx* c, hipStream_t s, const void* qin, void* qout, double dt, void* ysave) {
+  if (c->step_tile == 8)
+    return ysave ? launch_terms_step_ty<8, true>(c, s, qin, qout, dt, ysave)
+                 : launch_terms_step_ty<8, false>(c, s, qin, qout, dt, nullptr);
+  if (c->step_tile == 24 && !ysave) return launch_terms_step_ty<24, false>(c, s, qin, qout, dt, nullptr);
+  return ysave ? launch_terms_step_ty<16, true>(c, s, qin, qout, dt, ysave)
+               : launch_terms_step_ty<16, false>(c, s, qin, qout, dt, nullptr);
+}
+
+// The pair kernels in FORM_TERMS: one RK4 step from `cur` into `oth`.
+template <int PAIR, int TY>
+hipError_t launch_terms_pair_ty(const sgn_ctx* c, hipStream_t s, const void* Yin, const void* qn, void* acc, void* yb,
+                                double c1_acc, double c1_y, double c2_acc, double c2_y) {
+  const int ntx = (c->p.nx + sgn::TILE_X - 1) / sgn::TILE_X, nty = (c->p.ny + TY - 1) / TY;
+  const dim3 grid((unsigned)(ntx * nty)), block(sgn::STAGE_THREADS);
+#define SGN_TERMS(BX, BY)                                                                                             \
+  hipLaunchKernelGGL((sgn::pair_kernel<double, BX, BY, PAIR, false, TY, sgn::FORM_TERMS>), grid, block, 0, s, c->gc,     \
+                     (const double*)Yin, (const double*)c->b, (const double*)qn, (double*)acc, (double*)yb, c1_acc, c1_y, \
+                     c2_acc, c2_y, 0.0, 0.0, c->flag)
+  const int bx = c->p.bc_x, by = c->p.bc_y;
+  if (bx == 0 && by == 0) SGN_TERMS(0, 0);
+  else if (bx == 0 && by == 1) SGN_TERMS(0, 1);
+  else if (bx == 1 && by == 0) SGN_TERMS(1, 0);
+  else SGN_TERMS(1, 1);
+#undef SGN_TERMS
+  return hipGetLastError();
+}
+
+hipError_t enqueue_terms_pair_step(const sgn_ctx* c, hipStream_t s, void* cur, void* oth, double dt) {
+  const double d6 = dt / 6.0, d3 = dt / 3.0, d2 = dt / 2.0;
+  if (c->tile_y == 16) {
+    hipError_t e = launch_terms_pair_ty<1, 16>(c, s, cur, nullptr, oth, c->yb, d6, d2, d3, d2);
+    return e ? e : launch_terms_pair_ty<2, 16>(c, s, c->yb, cur, oth, nullptr, d3, dt, d6, 0.0);
+  }
+  hipError_t e = launch_terms_pair_ty<1, 8>(c, s, cur, nullptr, oth, c->yb, d6, d2, d3, d2);
+  return e ? e : launch_terms_pair_ty<2, 8>(c, s, c->yb, cur, oth, nullptr, d3, dt, d6, 0.0);
+}
+
+// Whether the gauge rollouts of this context run in FORM_TERMS.
+bool rollout_terms(const sgn_ctx* c) { return c->p.dtype == SGN_F64; }
 
 // Forward RK4 step from `qn` into `qout`, keeping the stage states Y2, Y3, Y4
 // in `ys` (three consecutive state slots).  On the pair path:
@@ -154,20 +230,27 @@ hipError_t launch_pair_save(const sgn_ctx* c, hipStream_t s, const void* Yin, co
 //   pair 2: k3 = f(Y3), Y4 = qn + dt k3 (saved), k4 = f(Y4), qout = acc + dt/3 k3 + dt/6 k4
 // (47 values of traffic per node); otherwise the step kernel writes the stage
 // states as it forms them (26 values).  Both give the same values bit for bit.
-hipError_t forward_step_keep(const sgn_ctx* c, hipStream_t s, const void* qn, void* ys, void* qout, double dt) {
-  if (c->step_path != SGN_PATH_PAIRS) return sgn_host::enqueue_step_into(c, s, qn, qout, dt, 0.0, ys);
+// `terms`: FORM_TERMS (gauge rollouts in FP64).
+hipError_t forward_step_keep(const sgn_ctx* c, hipStream_t s, const void* qn, void* ys, void* qout, double dt,
+                             bool terms) {
+  if (c->step_path != SGN_PATH_PAIRS)
+    return terms ? launch_terms_step(c, s, qn, qout, dt, ys)
+                 : sgn_host::enqueue_step_into(c, s, qn, qout, dt, 0.0, ys);
   void* y2 = slot(ys, 0, c);
   void* y3 = slot(ys, 1, c);
   void* y4 = slot(ys, 2, c);
   hipError_t e = launch_pair_save<1>(c, s, qn, nullptr, c->acc, y3, y2, nullptr, dt / 6.0, dt / 2.0, dt / 3.0,
-                                     dt / 2.0);
+                                     dt / 2.0, terms);
   if (e) return e;
-  return launch_pair_save<2>(c, s, y3, qn, c->acc, nullptr, y4, qout, dt / 3.0, dt, dt / 6.0, 0.0);
+  return launch_pair_save<2>(c, s, y3, qn, c->acc, nullptr, y4, qout, dt / 3.0, dt, dt / 6.0, 0.0, terms);
 }
 
 // One RK4 step of a rollout from `cur` into `oth`: the pair kernels on the pair
 // path, the step kernel otherwise.
 hipError_t rollout_step(const sgn_ctx* c, hipStream_t s, void* cur, void* oth, double dt) {
+  if (rollout_terms(c))
+    return c->step_path == SGN_PATH_PAIRS ? enqueue_terms_pair_step(c, s, cur, oth, dt)
+                                          : launch_terms_step(c, s, cur, oth, dt, nullptr);
   if (c->step_path == SGN_PATH_PAIRS) return sgn_host::enqueue_pair_step(c, s, cur, oth, dt, 0.0);
   return sgn_host::enqueue_step_into(c, s, cur, oth, dt, 0.0, nullptr);
 }
@@ -177,9 +260,9 @@ hipError_t rollout_step(const sgn_ctx* c, hipStream_t s, void* cur, void* oth, d
 // qbar itself on the pair and four-stage paths (four role kernels, qbar
 // updated in place), the context's kb_b on the fused path (two launches of the
 // two-stage kernel, whose second one cannot write the qbar it reads on the
-// rings of its tiles).  bbar accumulates.
+// rings of its tiles).  bbar accumulates.  `terms` as for forward_step_keep.
 hipError_t reverse_step(const sgn_ctx* c, hipStream_t s, const void* qn, const void* ys, void* qbar, void* bbar,
-                        double dt, void** qbar_out) {
+                        double dt, bool terms, void** qbar_out) {
   const auto& a = c->adj;
   const void* y2 = slot((void*)ys, 0, c);
   const void* y3 = slot((void*)ys, 1, c);
@@ -188,22 +271,22 @@ hipError_t reverse_step(const sgn_ctx* c, hipStream_t s, const void* qn, const v
   if (c->step_path == SGN_PATH_FUSED) {
     // S4 + S3: kb4 = dt/6 qb, kb3 = dt/3 qb + dt Yb4 (LDS); kb2 = dt/3 qb + dt/2 Yb3, acc = Yb4 + Yb3
     if ((e = launch_vjp_pair<2>(c, s, y4, y3, qbar, qbar, nullptr, a.kb_a, a.accb, bbar, dt / 6.0, dt / 3.0, dt,
-                                dt / 3.0, dt / 2.0)))
+                                dt / 3.0, dt / 2.0, terms)))
       return e;
     // S2 + S1: kb1 = dt/6 qb + dt/2 Yb2 (LDS); qb_n = qb + (acc + Yb2) + Yb1
     *qbar_out = a.kb_b;
     return launch_vjp_pair<1>(c, s, y2, qn, a.kb_a, qbar, a.kb_b, nullptr, a.accb, bbar, 1.0, dt / 6.0, dt / 2.0,
-                              0.0, 0.0);
+                              0.0, 0.0, terms);
   }
   *qbar_out = qbar;
   // kb4 = dt/6 qb ; next kb3 = dt/3 qb + dt Yb4
-  if ((e = launch_vjp<sgn::VJP_S4>(c, s, y4, qbar, qbar, a.kb_a, a.accb, bbar, dt / 6.0, dt / 3.0, dt))) return e;
+  if ((e = launch_vjp<sgn::VJP_S4>(c, s, y4, qbar, qbar, a.kb_a, a.accb, bbar, dt / 6.0, dt / 3.0, dt, terms))) return e;
   // kb2 = dt/3 qb + dt/2 Yb3
-  if ((e = launch_vjp<sgn::VJP_S3>(c, s, y3, a.kb_a, qbar, a.kb_b, a.accb, bbar, 1.0, dt / 3.0, dt / 2.0))) return e;
+  if ((e = launch_vjp<sgn::VJP_S3>(c, s, y3, a.kb_a, qbar, a.kb_b, a.accb, bbar, 1.0, dt / 3.0, dt / 2.0, terms))) return e;
   // kb1 = dt/6 qb + dt/2 Yb2
-  if ((e = launch_vjp<sgn::VJP_S2>(c, s, y2, a.kb_b, qbar, a.kb_a, a.accb, bbar, 1.0, dt / 6.0, dt / 2.0))) return e;
+  if ((e = launch_vjp<sgn::VJP_S2>(c, s, y2, a.kb_b, qbar, a.kb_a, a.accb, bbar, 1.0, dt / 6.0, dt / 2.0, terms))) return e;
   // qb_n = qb + Yb4 + Yb3 + Yb2 + Yb1
-  return launch_vjp<sgn::VJP_S1>(c, s, qn, a.kb_a, qbar, nullptr, a.accb, bbar, 1.0, 0.0, 0.0);
+  return launch_vjp<sgn::VJP_S1>(c, s, qn, a.kb_a, qbar, nullptr, a.accb, bbar, 1.0, 0.0, 0.0, terms);
 }
 
 // h = zeta0 - b, u = v = w = 0, eta = h (w is then set by the initialization kernel).
@@ -409,9 +492,9 @@ sgn_status sgn_step_vjp(sgn_ctx* c, const void* q_n, double dt, void* qbar, void
   if ((st = ensure_vjp_buffers(c)) || (st = ensure_stage_slots(c, 4))) return st;
   void* ys = c->adj.stages;
   void* qnext = slot(c->adj.stages, 3, c);
-  HIPCHK(c, forward_step_keep(c, c->stream, q_n, ys, qnext, dt));
+  HIPCHK(c, forward_step_keep(c, c->stream, q_n, ys, qnext, dt, false));
   void* out = nullptr;
-  HIPCHK(c, reverse_step(c, c->stream, q_n, ys, qbar, bbar, dt, &out));
+  HIPCHK(c, reverse_step(c, c->stream, q_n, ys, qbar, bbar, dt, false, &out));
   if (out != qbar) HIPCHK(c, hipMemcpyAsync(qbar, out, state_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   return SGN_OK;
 }
@@ -489,6 +572,7 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
     return fail(c, SGN_E_ALLOC, "adjoint rollout storage");
   }
   hipStream_t s = c->stream;
+  const bool terms = rollout_terms(c);
   // 1. forward rollout: checkpoints every K steps over the first T0 steps, then
   //    the last F steps keeping every state and stage state (slot layout of a
   //    segment: states 0..F at slots [0, F], stage triples from slot F+1)
@@ -504,7 +588,7 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
       const int64_t k = n - T0;
       if (k == 0) HIPCHK(c, hipMemcpyAsync(slot(a.stages, 0, c), cur, sb, hipMemcpyDeviceToDevice, s));
       HIPCHK(c, forward_step_keep(c, s, slot(a.stages, (size_t)k, c), slot(a.stages, (size_t)(F + 1 + 3 * k), c),
-                                  slot(a.stages, (size_t)(k + 1), c), dt));
+                                  slot(a.stages, (size_t)(k + 1), c), dt, terms));
       cur = slot(a.stages, (size_t)(k + 1), c);
     }
   }
@@ -532,7 +616,7 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
     HIPCHK(c, hipGetLastError());
     void* out = nullptr;
     HIPCHK(c, reverse_step(c, s, slot(a.stages, (size_t)k, c), slot(a.stages, (size_t)(len + 1 + 3 * k), c), a.qbar,
-                           grad_b, dt, &out));
+                           grad_b, dt, terms, &out));
     if (out != a.qbar) std::swap(a.qbar, a.kb_b);  // both buffers belong to the context
     return SGN_OK;
   };
@@ -545,7 +629,7 @@ sgn_status sgn_gauge_loss_grad(sgn_ctx* c, const void* zeta0, int64_t nsteps, do
     HIPCHK(c, hipMemcpyAsync(slot(a.stages, 0, c), slot(a.ckpt, (size_t)seg, c), sb, hipMemcpyDeviceToDevice, s));
     for (int64_t k = 0; k < len; ++k)
       HIPCHK(c, forward_step_keep(c, s, slot(a.stages, (size_t)k, c), slot(a.stages, (size_t)(len + 1 + 3 * k), c),
-                                  slot(a.stages, (size_t)(k + 1), c), dt));
+                                  slot(a.stages, (size_t)(k + 1), c), dt, terms));
     HIPCHK(c, record_segment(n0, len));
     for (int64_t k = len - 1; k >= 0; --k)
       if ((st = reverse_from_slots(n0, len, k))) return st;

@@ -196,7 +196,7 @@ constexpr bool step_keeps() {
 // output; c6 .. c1, t0, dt and flag are unused (the health of y_{n+1} is
 // checked by the attempt's FSAL evaluation).
 template <typename T, int BCX, int BCY, bool SRC, int TY, bool SAVE, int PAD, int EPI = EPI_NONE,
-          int RK = RK_CLASSIC, bool KEEP = step_keeps<T, TY, BCX, BCY, RK>()>
+          int RK = RK_CLASSIC, bool KEEP = step_keeps<T, TY, BCX, BCY, RK>(), int FORM = FORM_SHARED>
 __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridConst& gc, int i0, int j0,
                                           const T* __restrict__ q, const T* __restrict__ bplane,
                                           T* __restrict__ qout, T c6, T c3, T c2, T c1, double t0, double dt,
@@ -264,7 +264,7 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
         }
         s.store_b(rr, cc, v[it][5]);
         const T y[5] = {v[it][0], v[it][1], v[it][2], v[it][3], v[it][4]};
-        s.store(rr, cc, y, RK == RK_FSAL ? T(0) : node_e(y[0], y[4], recip_staged(y[0])), v[it][5]);
+        s.store(rr, cc, y, RK == RK_FSAL ? T(0) : node_extra<FORM>(y[0], y[4], recip_staged(y[0])), v[it][5]);
       }
     }
     if constexpr (RK == RK_FSAL) {
@@ -386,13 +386,18 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
       const int j = j0 + ly0 + k;
       const bool run = st < 4 ? own_dom[k] : (i < nx && j < ny);
       if (!run) continue;
-      const int r = ly0 + k + STEP_HALO, c = lx + STEP_HALO;
+      int r = ly0 + k + STEP_HALO;
+      const int c = lx + STEP_HALO;
+      // the printed terms take more registers than sharing the column's nodes leaves
+      // them: each is read anew, at a row that the compiler cannot tell
+      constexpr bool ANEW = FORM == FORM_TERMS && !KEEP;
+      if (ANEW) asm volatile("" : "+v"(r));
       const AxisStencil<BCY> ay(j, ny, gc.inv2dy, gc.invdy);
-      const Node<T> cn = KEEP ? Y[k] : (k == 0 ? s.load(r, c) : above);
+      const Node<T> cn = KEEP ? Y[k] : (k == 0 || ANEW ? s.load(r, c) : above);
       const Node<T> xm = s.load(r, c + ax.om);
       const Node<T> xp = s.load(r, c + ax.op);
       Node<T> dn, up;
-      if (k == 0) {
+      if (k == 0 || ANEW) {
         dn = s.load(r + ay.om, c);
       } else {
         dn = below;  // j > 0 here
@@ -429,8 +434,8 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
           for (int f = 0; f < 5; ++f) k1o[f] = fx->k1[f * N + ow];
         }
       }
-      const Rates<T> kk = node_rates<T, BCX, BCY, SRC>(cn, KEEP ? ih[k] : recip_staged(cn.h), xm, xp, dn, up, ax, ay, i,
-                                                       j, gc, ts);
+      const Rates<T> kk = node_rates<T, BCX, BCY, SRC, FORM>(cn, KEEP ? ih[k] : recip_staged(cn.h), xm, xp, dn, up, ax,
+                                                             ay, i, j, gc, ts);
       const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
       if (st < 4) {
 #pragma unroll
@@ -449,7 +454,7 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
         Y[k].b = cn.b;
         if (KEEP) {
           ih[k] = recip_staged(Y[k].h);
-          Y[k].e = node_e(Y[k].h, Y[k].eta, ih[k]);
+          Y[k].e = node_extra<FORM>(Y[k].h, Y[k].eta, ih[k]);
         }
         if (SAVE && i < nx && j < ny) {
           T* ys = ysave + (size_t)(st - 1) * 5 * N + o;
@@ -518,14 +523,15 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
       const Node<T> xp = s.load(r, c + axr.op);
       const Node<T> dn = s.load(r + ayr.om, c);
       const Node<T> up = s.load(r + ayr.op, c);
-      const Rates<T> kk = node_rates<T, BCX, BCY, SRC>(cn, KEEP ? ihr[k] : recip_staged(cn.h), xm, xp, dn, up, axr,
-                                                       ayr, i0 + ring_c[k], j0 + ring_r[k], gc, ts);
+      const Rates<T> kk =
+          node_rates<T, BCX, BCY, SRC, FORM>(cn, KEEP ? ihr[k] : recip_staged(cn.h), xm, xp, dn, up, axr, ayr,
+                                             i0 + ring_c[k], j0 + ring_r[k], gc, ts);
       const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
 #pragma unroll
       for (int f = 0; f < 5; ++f) rr[k][f] = fused(cy, kv[f], qr[k][f]);
       if (KEEP) {
         ihr[k] = recip_staged(rr[k][0]);
-        re[k] = node_e(rr[k][0], rr[k][4], ihr[k]);
+        re[k] = node_extra<FORM>(rr[k][0], rr[k][4], ihr[k]);
       }
       rb[k] = cn.b;
     }
@@ -536,14 +542,14 @@ __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridCon
       if (!own_dom[k]) continue;
       const int r = ly0 + k + STEP_HALO, c = lx + STEP_HALO;
       const T y[5] = {Y[k].h, Y[k].u, Y[k].v, Y[k].w, Y[k].eta};
-      s.store(r, c, y, KEEP ? Y[k].e : node_e(y[0], y[4], recip_staged(y[0])), Y[k].b);
+      s.store(r, c, y, KEEP ? Y[k].e : node_extra<FORM>(y[0], y[4], recip_staged(y[0])), Y[k].b);
     }
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       const int m = tid + k * STAGE_THREADS;
       if (m >= ring_lim || !ring_ok[k]) continue;
       const int r = ring_r[k] + STEP_HALO, c = ring_c[k] + STEP_HALO;
-      s.store(r, c, rr[k], KEEP ? re[k] : node_e(rr[k][0], rr[k][4], recip_staged(rr[k][0])), rb[k]);
+      s.store(r, c, rr[k], KEEP ? re[k] : node_extra<FORM>(rr[k][0], rr[k][4], recip_staged(rr[k][0])), rb[k]);
     }
     __syncthreads();
   }

@@ -64,8 +64,8 @@ __device__ __forceinline__ Node<T> lds_load(const Smem& s, int r, int c) {
 
 // Right-hand side at node (i, j) (unwrapped indices) from its value, ih =
 // recip_staged of its depth and its four neighbours as the stencils ax, ay
-// select them (closure rows included).
-template <typename T, int BCX, int BCY, bool SRC>
+// select them (closure rows included).  FORM: FORM_SHARED or FORM_TERMS (ih unused).
+template <typename T, int BCX, int BCY, bool SRC, int FORM = FORM_SHARED>
 __device__ __forceinline__ Rates<T> node_rates(const Node<T>& center, T ih, const Node<T>& xm,
                                                const Node<T>& xp, const Node<T>& ym, const Node<T>& yp,
                                                const AxisStencil<BCX>& ax, const AxisStencil<BCY>& ay, int i, int j,
@@ -79,8 +79,12 @@ __device__ __forceinline__ Rates<T> node_rates(const Node<T>& center, T ih, cons
     if (j == 0) saty = T(-2.0 * gc.invdy);
     if (j == gc.ny - 1) saty = T(2.0 * gc.invdy);
   }
-  Rates<T> k = split_form_rates<T, BCX, BCY>(center, ih, xm, xp, ym, yp, T(ax.scale), T(ay.scale), T(gc.g),
-                                             T(gc.lam), satx, saty);
+  Rates<T> k;
+  if constexpr (FORM == FORM_TERMS)
+    k = term_rates<T, BCX, BCY>(center, xm, xp, ym, yp, T(ax.scale), T(ay.scale), T(gc.g), T(gc.lam), satx, saty);
+  else
+    k = split_form_rates<T, BCX, BCY>(center, ih, xm, xp, ym, yp, T(ax.scale), T(ay.scale), T(gc.g), T(gc.lam), satx,
+                                      saty);
   if (SRC) {
     const int gi = wrap_or_clamp<BCX>(i, gc.nx), gj = wrap_or_clamp<BCY>(j, gc.ny);
     double S[5];
@@ -95,7 +99,7 @@ __device__ __forceinline__ Rates<T> node_rates(const Node<T>& center, T ih, cons
 }
 
 // Right-hand side at LDS position (r, c) of node (i, j) (unwrapped indices).
-template <typename T, int BCX, int BCY, bool SRC, class Smem>
+template <typename T, int BCX, int BCY, bool SRC, int FORM, class Smem>
 __device__ __forceinline__ Rates<T> tile_eval(const Smem& s, int r, int c, int i, int j, const GridConst& gc, double t,
                                               Node<T>& center) {
   const AxisStencil<BCX> ax(i, gc.nx, gc.inv2dx, gc.invdx);
@@ -105,7 +109,7 @@ __device__ __forceinline__ Rates<T> tile_eval(const Smem& s, int r, int c, int i
   const Node<T> xp = lds_load<T>(s, r, c + ax.op);
   const Node<T> ym = lds_load<T>(s, r + ay.om, c);
   const Node<T> yp = lds_load<T>(s, r + ay.op, c);
-  return node_rates<T, BCX, BCY, SRC>(center, recip_staged(center.h), xm, xp, ym, yp, ax, ay, i, j, gc, t);
+  return node_rates<T, BCX, BCY, SRC, FORM>(center, recip_staged(center.h), xm, xp, ym, yp, ax, ay, i, j, gc, t);
 }
 
 // One tile (origin i0, j0) of a stage pair, executed by a whole workgroup.
@@ -115,7 +119,7 @@ __device__ __forceinline__ Rates<T> tile_eval(const Smem& s, int r, int c, int i
 // SAVE (adjoint recomputation): also write the intermediate stage of owned
 // nodes to ysave (pair 1: Y2 = q + dt/2 k1; pair 2: Y4 = q + dt k3), and in
 // pair 2 write q_new to qout instead of over acc.
-template <typename T, int BCX, int BCY, int PAIR, bool SRC, int TY, bool SAVE = false>
+template <typename T, int BCX, int BCY, int PAIR, bool SRC, int TY, bool SAVE = false, int FORM = FORM_SHARED>
 __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& gc, int i0, int j0,
                                           const T* __restrict__ Yin, const T* __restrict__ bplane,
                                           const T* __restrict__ qn, T* acc_io, T* __restrict__ yb_out, T c1_acc,
@@ -150,7 +154,7 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
     s.f[3][rr][cc] = Yin[3 * N + o];
     s.f[4][rr][cc] = eta;
     s.f[5][rr][cc] = bplane[o];
-    s.f[6][rr][cc] = node_e(h, eta, recip_staged(h));
+    s.f[6][rr][cc] = node_extra<FORM>(h, eta, recip_staged(h));
   }
 
   // Own-node operands fetched before the barrier.
@@ -224,7 +228,7 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
     in_dom[k] = on_axis<BCX>(i, nx) && on_axis<BCY>(j, ny);
     if (!in_dom[k]) continue;
     Node<T> cnode;
-    const Rates<T> kk = tile_eval<T, BCX, BCY, SRC>(s, lr + 2, tx + 2, i, j, gc, t1, cnode);
+    const Rates<T> kk = tile_eval<T, BCX, BCY, SRC, FORM>(s, lr + 2, tx + 2, i, j, gc, t1, cnode);
     const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
     if (PAIR == 1) {
       const T yv[5] = {cnode.h, cnode.u, cnode.v, cnode.w, cnode.eta};
@@ -246,7 +250,7 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
   __builtin_amdgcn_sched_barrier(0);
   if (ring_valid) {
     Node<T> cnode;
-    const Rates<T> kk = tile_eval<T, BCX, BCY, SRC>(s, ring_r, ring_c, ring_i, ring_j, gc, t1, cnode);
+    const Rates<T> kk = tile_eval<T, BCX, BCY, SRC, FORM>(s, ring_r, ring_c, ring_i, ring_j, gc, t1, cnode);
     const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
     const T yv[5] = {cnode.h, cnode.u, cnode.v, cnode.w, cnode.eta};
 #pragma unroll
@@ -266,12 +270,12 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
     }
 #pragma unroll
     for (int f = 0; f < 5; ++f) s.f[f][r][c] = mid[k][f];
-    s.f[6][r][c] = node_e(mid[k][0], mid[k][4], recip_staged(mid[k][0]));
+    s.f[6][r][c] = node_extra<FORM>(mid[k][0], mid[k][4], recip_staged(mid[k][0]));
   }
   if (ring_valid) {
 #pragma unroll
     for (int f = 0; f < 5; ++f) s.f[f][ring_r][ring_c] = ring_mid[f];
-    s.f[6][ring_r][ring_c] = node_e(ring_mid[0], ring_mid[4], recip_staged(ring_mid[0]));
+    s.f[6][ring_r][ring_c] = node_extra<FORM>(ring_mid[0], ring_mid[4], recip_staged(ring_mid[0]));
   }
   __syncthreads();
 
@@ -284,7 +288,7 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
     const int j = j0 + lr;
     if (i >= nx || j >= ny) continue;
     Node<T> cnode;
-    const Rates<T> kk = tile_eval<T, BCX, BCY, SRC>(s, lr + 2, tx + 2, i, j, gc, t2, cnode);
+    const Rates<T> kk = tile_eval<T, BCX, BCY, SRC, FORM>(s, lr + 2, tx + 2, i, j, gc, t2, cnode);
     const T kv[5] = {kk.h, kk.u, kk.v, kk.w, kk.eta};
     const size_t o = (size_t)j * nx + i;
     if (PAIR == 1) {
@@ -309,7 +313,7 @@ __device__ __forceinline__ void pair_tile(PairSmem<T, TY>& s, const GridConst& g
   if (PAIR == 2 && health) atomicOr(flag, health);
 }
 
-template <typename T, int BCX, int BCY, int PAIR, bool SRC, int TY>
+template <typename T, int BCX, int BCY, int PAIR, bool SRC, int TY, int FORM = FORM_SHARED>
 __global__ __launch_bounds__(STAGE_THREADS) void pair_kernel(const GridConst gc, const T* __restrict__ Yin,
                                                              const T* __restrict__ bplane, const T* __restrict__ qn,
                                                              T* acc_io, T* __restrict__ yb_out, T c1_acc, T c1_y,
@@ -319,13 +323,13 @@ __global__ __launch_bounds__(STAGE_THREADS) void pair_kernel(const GridConst gc,
   const int ntx = (gc.nx + TILE_X - 1) / TILE_X;
   const int nty = (gc.ny + TY - 1) / TY;
   const int tile = xcd_tile(blockIdx.x, ntx * nty);
-  pair_tile<T, BCX, BCY, PAIR, SRC, TY>(s, gc, (tile % ntx) * TILE_X, (tile / ntx) * TY, Yin, bplane, qn, acc_io,
-                                        yb_out, c1_acc, c1_y, c2_acc, c2_y, t1, t2, flag);
+  pair_tile<T, BCX, BCY, PAIR, SRC, TY, false, FORM>(s, gc, (tile % ntx) * TILE_X, (tile / ntx) * TY, Yin, bplane, qn,
+                                                     acc_io, yb_out, c1_acc, c1_y, c2_acc, c2_y, t1, t2, flag);
 }
 
 // Pair kernel of the adjoint's segment recomputation (no source terms): the
 // same tile code with the intermediate stages saved (see pair_tile, SAVE).
-template <typename T, int BCX, int BCY, int PAIR, int TY>
+template <typename T, int BCX, int BCY, int PAIR, int TY, int FORM = FORM_SHARED>
 __global__ __launch_bounds__(STAGE_THREADS) void pair_save_kernel(const GridConst gc, const T* __restrict__ Yin,
                                                                   const T* __restrict__ bplane,
                                                                   const T* __restrict__ qn, T* acc_io,
@@ -336,9 +340,9 @@ __global__ __launch_bounds__(STAGE_THREADS) void pair_save_kernel(const GridCons
   const int ntx = (gc.nx + TILE_X - 1) / TILE_X;
   const int nty = (gc.ny + TY - 1) / TY;
   const int tile = xcd_tile(blockIdx.x, ntx * nty);
-  pair_tile<T, BCX, BCY, PAIR, false, TY, true>(s, gc, (tile % ntx) * TILE_X, (tile / ntx) * TY, Yin, bplane, qn,
-                                                acc_io, yb_out, c1_acc, c1_y, c2_acc, c2_y, 0.0, 0.0, flag, ysave,
-                                                qout);
+  pair_tile<T, BCX, BCY, PAIR, false, TY, true, FORM>(s, gc, (tile % ntx) * TILE_X, (tile / ntx) * TY, Yin, bplane,
+                                                      qn, acc_io, yb_out, c1_acc, c1_y, c2_acc, c2_y, 0.0, 0.0, flag,
+                                                      ysave, qout);
 }
 
 }  // namespace sgn

@@ -60,6 +60,26 @@ __device__ __forceinline__ T node_e(T h, T eta, T ih) {
   return (d * d) * ih;
 }
 
+// The two forms in which the rates are evaluated, equal to rounding.  FORM_SHARED
+// (everything but the FP64 gauge rollouts): the split form gathered over the two
+// neighbours of an axis, products shared between the rates (axis_terms).
+// FORM_TERMS: the printed sums term by term (term_rates), Node::e holding 1/h.  The
+// FP64 rollouts and gradients of the gauge loss keep the second: the bottom's
+// gradient is the difference of two sums of the misfits' size (grad_b = bbar -
+// grad_zeta0) that cancel where the water rests, down to 1e-10 of them and less, so
+// its digits there are the rounding of every evaluation that went into the sums.
+// With this form they stay those of the gradients on record; the other moved
+// grad_b by 4e-10 of its norm and single nodes by 6e-8 (146 x 261, 24 steps), no
+// nearer to the exact value.  Its price: 48 steps of 640 x 512 take 6660 us with
+// their gradient (6930 on the tiles of the time before), 5330 in FORM_SHARED.
+enum : int { FORM_SHARED = 0, FORM_TERMS = 1 };
+
+// The seventh value of a staged node.
+template <int FORM, typename T>
+__device__ __forceinline__ T node_extra(T h, T eta, T ih) {
+  return FORM == FORM_TERMS ? ih : node_e(h, eta, ih);
+}
+
 template <typename T, int TY>
 struct StageSmem {
   T f[7][TY + 2][TILE_X + 2];  // h u v w eta b e
@@ -196,6 +216,79 @@ __device__ __forceinline__ Rates<T> split_form_rates(const Node<T>& c, T ih, con
   const AxisTerms<T> x = x_terms(c, t, xm, xp, g, lam);
   const AxisTerms<T> y = y_terms(c, t, ym, yp, g, lam);
   return join_rates<T, BCX, BCY>(c, ih, t, x, y, sx, sy, satx_coef, saty_coef);
+}
+
+// a b - x y, the first product unrounded.
+template <typename T>
+__device__ __forceinline__ T diff_of_products(T a, T b, T x, T y) {
+#pragma clang fp contract(off)
+  return fused(a, b, -(x * y));
+}
+
+// FORM_TERMS, one axis (n the velocity along it, t the one across): the differences
+// of the printed products, unscaled, and the sums of the rates' terms.  With
+// D(eta^2/h) = D(h) + D((eta - h)(eta + h)/h), whose second part is small (eta stays
+// close to h), lambda/6 (r^2 D h - D(eta^2/h)) is formed without cancellation.
+//   A1 = g (D(h(h+b)) - (h+b) D h) + lambda/6 ((r^2 - 1) D h - D((eta-h)(eta+h)/h))
+//        + lambda/3 (1 - r) D eta + lambda/2 (1 - r) D b
+//   A2 = h D(n^2) - n^2 D h + n D(h n) - h n D n,  T = D(h n t) - n t D h + h n D t - h t D n
+//   C  = the same with w for t,  R = n D h + h D n,  E = n D eta + 3/2 n D b
+template <typename T>
+struct AxisSums {
+  T A1, A2, Tt, C, R, E;
+};
+
+template <typename T>
+__device__ __forceinline__ AxisSums<T> axis_sums(T h, T n, T t, T w, T H, T hn, T ht, T hw, T uv, T r2m1, T omr, T g,
+                                                 T lam, const Node<T>& m, T mn, T mt, const Node<T>& p, T pn, T pt) {
+#pragma clang fp contract(off)
+  const T dh = p.h - m.h, dn = pn - mn, dt = pt - mt, dw = p.w - m.w, deta = p.eta - m.eta, db = p.b - m.b;
+  const T phn = p.h * pn, mhn = m.h * mn;
+  const T dhH = diff_of_products(p.h, p.h + p.b, m.h, m.h + m.b);
+  const T dn2 = diff_of_products(pn, pn, mn, mn);
+  const T dhn = diff_of_products(p.h, pn, m.h, mn);
+  const T dhnt = diff_of_products(phn, pt, mhn, mt);
+  const T de2 = diff_of_products((p.eta - p.h) * (p.eta + p.h), p.e, (m.eta - m.h) * (m.eta + m.h), m.e);
+  const T dhnw = diff_of_products(phn, p.w, mhn, m.w);
+  const T lam6 = lam * T(1.0 / 6.0), lam3 = lam * T(1.0 / 3.0), lam2 = lam * T(0.5);
+  AxisSums<T> o;
+  o.A1 = fused(lam2 * omr, db,
+               fused(lam3 * omr, deta, fused(g, fused(-H, dh, dhH), lam6 * fused(r2m1, dh, -de2))));
+  o.A2 = fused(-hn, dn, fused(n, dhn, diff_of_products(h, dn2, n * n, dh)));
+  o.Tt = fused(-ht, dn, fused(hn, dt, fused(-uv, dh, dhnt)));
+  o.C = fused(-hw, dn, fused(hn, dw, fused(-(n * w), dh, dhnw)));
+  o.R = fused(n, dh, h * dn);
+  o.E = fused(n, deta, (T(1.5) * n) * db);
+  return o;
+}
+
+// FORM_TERMS: rates at node c.  Every derivative along one axis at a node carries the
+// same scale, applied once per sum.  All multiply-adds are written out, as the
+// gradients on record were rounded.
+template <typename T, int BCX, int BCY>
+__device__ __forceinline__ Rates<T> term_rates(const Node<T>& c, const Node<T>& xm, const Node<T>& xp,
+                                               const Node<T>& ym, const Node<T>& yp, T sx, T sy, T g, T lam,
+                                               T satx_coef, T saty_coef) {
+#pragma clang fp contract(off)
+  const T h = c.h, u = c.u, v = c.v, w = c.w, ih = c.e;
+  // r - 1 = (eta - h)/h and r^2 - 1 = (r - 1)(r + 1), formed from eta - h, so
+  // that a state at rest (eta = h) gives exactly zero relaxation terms
+  const T rm1 = (c.eta - h) * ih;
+  const T omr = -rm1;
+  const T r2m1 = rm1 * (rm1 + T(2));
+  const T H = h + c.b, hu = h * u, hv = h * v, uv = u * v, hw = h * w;
+  const AxisSums<T> x = axis_sums<T>(h, u, v, w, H, hu, hv, hw, uv, r2m1, omr, g, lam, xm, xm.u, xm.v, xp, xp.u, xp.v);
+  const AxisSums<T> y = axis_sums<T>(h, v, u, w, H, hv, hu, hw, uv, r2m1, omr, g, lam, ym, ym.v, ym.u, yp, yp.v, yp.u);
+  const T hsx = T(0.5) * sx, hsy = T(0.5) * sy;
+  Rates<T> k;
+  k.h = -fused(sx, x.R, sy * y.R);
+  if (BCX == BC_REFLECTING) k.h = fused(satx_coef, hu, k.h);
+  if (BCY == BC_REFLECTING) k.h = fused(saty_coef, hv, k.h);
+  k.u = -fused(hsy, y.Tt, fused(hsx, x.A2, sx * x.A1)) * ih;
+  k.v = -fused(hsx, x.Tt, fused(hsy, y.A2, sy * y.A1)) * ih;
+  k.w = fused(lam, omr, -fused(hsx, x.C, hsy * y.C)) * ih;
+  k.eta = w - fused(sx, x.E, sy * y.E);
+  return k;
 }
 
 template <typename T, int BCX, int BCY, int MODE, bool SRC, int TY>
