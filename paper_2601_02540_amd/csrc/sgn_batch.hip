@@ -464,11 +464,11 @@ sgn_status sgn_batch_step(sgn_batch* b, const double* dt, int64_t nsteps) {
   if (b->path == SGN_PATH_FUSED && (left & 1)) {  // an odd count begins with three steps, or is one and a copy
     BCHK(b, enqueue_batch_step(b, b->stream, sgn::BATCH_Q_ACC));
     if (left == 1) {
-      const dim3 grid(64, (unsigned)b->n);
+      const dim3 grid(64, (unsigned)std::min(b->n, sgn::BATCH_COPY_ROWS));
       if (b->dtype == SGN_F64)
-        hipLaunchKernelGGL(sgn::batch_copy_kernel<double>, grid, dim3(256), 0, b->stream, b->d_desc);
+        hipLaunchKernelGGL(sgn::batch_copy_kernel<double>, grid, dim3(256), 0, b->stream, b->d_desc, b->n);
       else
-        hipLaunchKernelGGL(sgn::batch_copy_kernel<float>, grid, dim3(256), 0, b->stream, b->d_desc);
+        hipLaunchKernelGGL(sgn::batch_copy_kernel<float>, grid, dim3(256), 0, b->stream, b->d_desc, b->n);
       BCHK(b, hipGetLastError());
       return SGN_OK;
     }

@@ -178,14 +178,19 @@ __global__ __launch_bounds__(MARCH_LANES, march_waves<T>()) void batch_march_ker
   }
 }
 
-// q <- acc of every instance (after a single step of the fused path); blockIdx.y = instance.
+// q <- acc of the ninst instances (after a single step of the fused path); block row
+// blockIdx.y takes instances blockIdx.y, blockIdx.y + gridDim.y, ... (a launch has at
+// most 65536 rows, an ensemble may have more instances).
+constexpr int BATCH_COPY_ROWS = 16384;
 template <typename T>
-__global__ __launch_bounds__(256) void batch_copy_kernel(const InstDesc* __restrict__ desc) {
-  const InstDesc& d = desc[blockIdx.y];
-  const size_t n = 5 * (size_t)d.gc.nx * (size_t)d.gc.ny;
-  const T* src = (const T*)d.acc;
-  T* dst = (T*)d.q;
-  for (size_t k = (size_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (size_t)gridDim.x * 256) dst[k] = src[k];
+__global__ __launch_bounds__(256) void batch_copy_kernel(const InstDesc* __restrict__ desc, int ninst) {
+  for (int i = blockIdx.y; i < ninst; i += gridDim.y) {
+    const InstDesc& d = desc[i];
+    const size_t n = 5 * (size_t)d.gc.nx * (size_t)d.gc.ny;
+    const T* src = (const T*)d.acc;
+    T* dst = (T*)d.q;
+    for (size_t k = (size_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (size_t)gridDim.x * 256) dst[k] = src[k];
+  }
 }
 
 }  // namespace sgn
