@@ -304,56 +304,53 @@ __global__ __launch_bounds__(256) void surface_to_state(const T* __restrict__ ze
 }
 
 // zeta = h + b at the gauges, one row of the series.  Also the misfit against a
-// target row and the row's loss.  One block per row, the rows' states one after
-// the other in memory; thread t handles gauges t,
-// t + 256, ... and the loss increment is summed in a fixed tree order, so the
-// result is deterministic.
+// target row and the row's loss.  One block per row (blocks stride over rows beyond
+// MAX_RECORD_BLOCKS), the rows' states one after the other in memory; thread t
+// handles gauges t, t + 256, ... and the loss increment is summed in a fixed tree
+// order, so the result is deterministic.
 // Gauge indices come from the caller: an index outside [0, N) is skipped and
 // raises FLAG_BADINDEX (reported as SGN_E_ARG by the next synchronizing call).
 constexpr int GAUGE_THREADS = 256;
 constexpr int MAX_GAUGES = 4096;
+constexpr int64_t MAX_RECORD_BLOCKS = 4096;  // twice what the GPU holds at once; a launch of all rows may pass 2^32 threads
 
 template <typename T>
 __global__ __launch_bounds__(GAUGE_THREADS) void gauge_record(const T* __restrict__ q, const T* __restrict__ b,
                                                               const int64_t* __restrict__ idx, int ng, size_t N,
-                                                              double* __restrict__ series,
+                                                              int64_t rows, double* __restrict__ series,
                                                               const double* __restrict__ target,
                                                               double* __restrict__ misfit, double* __restrict__ loss,
                                                               int* __restrict__ flag) {
   __shared__ double part[GAUGE_THREADS];
-  const size_t row = blockIdx.x;
-  q += row * 5 * N;
-  if (series) series += row * ng;
-  if (target) {
-    target += row * ng;
-    misfit += row * ng;
-  }
   const int t = threadIdx.x;
-  double acc = 0.0;
-  for (int g = t; g < ng; g += GAUGE_THREADS) {
-    const int64_t k = idx[g];
-    if (k < 0 || (size_t)k >= N) {
-      atomicOr(flag, sgn::FLAG_BADINDEX);
-      if (series) series[g] = 0.0;
-      if (target) misfit[g] = 0.0;
-      continue;
+  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
+    const T* h = q + (size_t)row * 5 * N;
+    double acc = 0.0;
+    for (int g = t; g < ng; g += GAUGE_THREADS) {
+      const int64_t k = idx[g];
+      if (k < 0 || (size_t)k >= N) {
+        atomicOr(flag, sgn::FLAG_BADINDEX);
+        if (series) series[row * ng + g] = 0.0;
+        if (target) misfit[row * ng + g] = 0.0;
+        continue;
+      }
+      const double z = (double)h[k] + (double)b[k];
+      if (series) series[row * ng + g] = z;
+      if (target) {
+        const double m = z - target[row * ng + g];
+        misfit[row * ng + g] = m;
+        acc += 0.5 * m * m;
+      }
     }
-    const double z = (double)q[k] + (double)b[k];
-    if (series) series[g] = z;
-    if (target) {
-      const double m = z - target[g];
-      misfit[g] = m;
-      acc += 0.5 * m * m;
-    }
-  }
-  if (!loss) return;
-  part[t] = acc;
-  __syncthreads();
-  for (int w = GAUGE_THREADS / 2; w > 0; w >>= 1) {
-    if (t < w) part[t] += part[t + w];
+    if (!loss) continue;
+    part[t] = acc;
     __syncthreads();
+    for (int w = GAUGE_THREADS / 2; w > 0; w >>= 1) {
+      if (t < w) part[t] += part[t + w];
+      __syncthreads();
+    }
+    if (t == 0) loss[row] = part[0];
   }
-  if (t == 0) loss[row] = part[0];
 }
 
 // *loss = the rows' losses, added in row order.  One block.
@@ -437,12 +434,13 @@ hipError_t launch_surface(const sgn_ctx* c, const void* zeta0, void* q) {
 
 hipError_t launch_record(const sgn_ctx* c, const void* q, int64_t rows, const int64_t* idx, int ng, double* series,
                          const double* target, double* misfit, double* loss) {
+  const dim3 grid((unsigned)std::min(rows, MAX_RECORD_BLOCKS)), block(GAUGE_THREADS);
   if (c->p.dtype == SGN_F64)
-    hipLaunchKernelGGL(gauge_record<double>, dim3((unsigned)rows), dim3(GAUGE_THREADS), 0, c->stream, (const double*)q, (const double*)c->b, idx,
-                       ng, c->N, series, target, misfit, loss, c->flag);
+    hipLaunchKernelGGL(gauge_record<double>, grid, block, 0, c->stream, (const double*)q, (const double*)c->b, idx, ng,
+                       c->N, rows, series, target, misfit, loss, c->flag);
   else
-    hipLaunchKernelGGL(gauge_record<float>, dim3((unsigned)rows), dim3(GAUGE_THREADS), 0, c->stream, (const float*)q, (const float*)c->b, idx,
-                       ng, c->N, series, target, misfit, loss, c->flag);
+    hipLaunchKernelGGL(gauge_record<float>, grid, block, 0, c->stream, (const float*)q, (const float*)c->b, idx, ng,
+                       c->N, rows, series, target, misfit, loss, c->flag);
   return hipGetLastError();
 }
 
