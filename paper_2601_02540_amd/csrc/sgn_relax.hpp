@@ -55,20 +55,21 @@ __device__ __forceinline__ double relax_next(double gam, double s, double ds) {
 static __device__ void relax_root(const RelaxSums& a, RelaxScalars* __restrict__ rs, double dt) {
   const double s0 = a.s.s + a.s.c, s1 = a.ds.s + a.ds.c;
   const bool root = s1 != 0.0 && isfinite(s0) && isfinite(s1);
-  const double d = root ? -s0 / s1 : 0.0;  // gam_1 - 1
+  const double gam1 = root ? 1.0 - s0 / s1 : 1.0;
   double gam = relax_next(1.0, s0, s1);
   double done = 1.0;  // without a usable root a second iteration repeats the first
-  if (root && 1.0 + d >= 0.5 && 1.0 + d <= 1.5) {
-    // s(1 + d) = s0 + s1 d + ..., the first two of which cancel
+  if (root && gam1 >= 0.5 && gam1 <= 1.5) {
+    const double d = gam1 - 1.0;  // exact
+    // s(1 + d) = s0 + s1 d + ..., the first two of which cancel but for the rounding of gam_1
     const double d2 = d * d;
-    const double s = d2 * (a.c2 + d * (a.c3 + d * a.c4));
+    const double s = __builtin_fma(s1, d, s0) + d2 * (a.c2 + d * (a.c3 + d * a.c4));
     const double ds = s1 + d * (2.0 * a.c2 + d * (3.0 * a.c3 + 4.0 * d * a.c4));
     // sum_{k>=5} |t_k d^k| <= rem |d|^5 / (1 - |rho d|), and 5 rem |d|^4 / (1 - |rho d|)^2 for the derivative
     const double x = 1.0 - a.rho * fabs(d);
     const double es = a.rem * fabs(d) * d2 * d2 / x, eds = 5.0 * a.rem * d2 * d2 / (x * x);
     const double lim = 0x1p-56 * fabs(ds);
     if (x > 0.5 && es <= lim && eds * fabs(s) <= lim * fabs(ds) && isfinite(s) && isfinite(ds) && ds != 0.0) {
-      gam = (1.0 + d) - s / ds;
+      gam = gam1 - s / ds;
       if (!(gam >= 0.5 && gam <= 1.5)) gam = 1.0;
     } else {
       done = 0.0;
