@@ -108,12 +108,15 @@ std::vector<int> march_chunks(const sgn_batch* b) {
   // the ends of the instances leave a few runs short: grow the height until one round holds them
   for (int64_t top = 2 * h; h < top && tasks(h) > slots;) h += std::max<int64_t>(1, h / 32);
   int64_t march = 0, tile = 0;
+  bool rows_ok = true;
   for (int i = 0; i < b->n; ++i) {
     chunks.push_back((int)std::max<int64_t>(1, (b->params[i].ny + h - 1) / h));
     march += sgn_host::march_evals(strips[i], b->params[i].ny, chunks.back());
     tile += sgn_host::tile_evals(b->params[i].nx, b->params[i].ny);
+    rows_ok = rows_ok && sgn::march_least_rows(chunks.back(), b->params[i].ny, b->params[i].bc_y == SGN_REFLECTING) >=
+                             sgn::MARCH_LEAST_ROWS;
   }
-  if (!sgn_host::march_pays(march, tile)) chunks.clear();
+  if (!rows_ok || !sgn_host::march_pays(march, tile)) chunks.clear();
   return chunks;
 }
 

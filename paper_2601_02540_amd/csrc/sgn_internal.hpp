@@ -98,9 +98,10 @@ namespace sgn_host {
 struct MarchPlan {
   int strips = 0, chunks = 0, wall_chunks = 0, tasks = 0;
 };
-// One round of waves (as many as the GPU holds at once) covers the grid, in
-// runs of at least MARCH_MIN_HEIGHT rows (12 evaluations of the rows around a
-// run against 4 per row of it).  Below MARCH_MIN_NODES the strips are too few or
+// One round of waves (as many as the GPU holds at once) covers the grid, in runs of
+// MARCH_MIN_HEIGHT rows on average or more (12 evaluations of the rows around a
+// run against 4 per row of it; runs at walls in y are a fifth shorter, and the runs of
+// an ensemble's instance of a few rows have four or more).  Below MARCH_MIN_NODES the strips are too few or
 // too short: FP64 512^2 takes 31 us in runs of 8 rows and 14.5 us on tiles, 1024^2
 // 41 us against 43, 2048^2 136 against 155.
 constexpr int64_t MARCH_MIN_NODES = (int64_t)1 << 20;

@@ -193,7 +193,10 @@ __device__ __forceinline__ void march_strip(const MarchSmem<T>& s, const GridCon
   T acc[3][5] = {};       // accumulators of rows R - 2, R - 3, R - 4
   T pf[6];                // the row being loaded
   int health = 0;
-  // the lane's sums, kept in LDS where q of row R - 3 might have gone
+  // the lane's sums, kept in LDS where q of row R - 3 might have gone (FP32: both holds)
+  static_assert(EPI == EPI_NONE || sizeof(MarchHold<double>) <= (HOLD_A ? 1 : 2) * sizeof(MarchHold<T>),
+                "the sums fit the LDS they take over");
+  static_assert(alignof(MarchHold<T>) >= alignof(MarchHold<double>), "and its alignment");
   MarchHold<double>* const sums = (MarchHold<double>*)s.hold;
   if (EPI != EPI_NONE) sums->put(lane, {0.0, 0.0, 0.0, 0.0, 0.0});
   const auto fetch = [&](int row) {
@@ -448,6 +451,16 @@ __device__ __forceinline__ int march_row(int chunk, int nchunks, int ny, bool wa
   if (chunk >= nchunks) return ny;
   return walls ? (int)((long long)ny * (5 * chunk - 1) / (5 * nchunks - 2)) : (int)((long long)ny * chunk / nchunks);
 }
+
+// Rows of the shortest run of march_row's division: with walls the first one.
+inline long long march_least_rows(int nchunks, int ny, bool walls) {
+  if (nchunks <= 1) return ny;
+  return walls ? 4LL * ny / (5LL * nchunks - 2) : ny / nchunks;
+}
+// What a run holds at least: a run whose halo of four rows reaches a wall takes the
+// wall's variant (march_any), whose prelude and last steps are laid out for runs that
+// hold as many rows themselves.  Plans are checked for it.
+constexpr int MARCH_LEAST_ROWS = 4;
 
 // One wave per workgroup.  Tasks: with reflecting walls in x first those of the
 // first and the last strip, cut into wchunks runs of rows each (more than the
