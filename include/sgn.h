@@ -280,10 +280,11 @@ sgn_status sgn_cfl_dt(sgn_ctx* ctx, const void* q, double cfl, double* dt);
  * first, 1 and 2 = middle, 3 = last).  Pair path: likewise, ms[0] = pair 1,
  * ms[1] = pair 2, ms[2] = ms[3] = 0.  Fused path (one kernel per step): a start
  * and a stop event bound to each step kernel's own execution, nothing enqueued
- * between the launches; ms[0] = the step kernel (on small grids the tile kernel,
- * one step per launch), ms[1..3] = 0.  On
+ * between the launches; ms[0] = the step kernel (on small grids, which take two
+ * steps per launch, half a launch), ms[1..3] = 0.  On
  * the pair and fused paths an odd nsteps is rounded up; the means leave out
- * the first step (two on those paths) when there are more.  nsteps <= 1024
+ * the first step (two on those paths; on small grids the first launch) when there
+ * are more.  nsteps <= 1024
  * (SGN_E_ARG otherwise).  Milliseconds; synchronizes. */
 sgn_status sgn_profile_stages(sgn_ctx* ctx, void* q, double dt, int64_t nsteps, double* ms);
 

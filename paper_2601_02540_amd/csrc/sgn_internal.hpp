@@ -130,6 +130,9 @@ bool small_pays(const sgn_ctx* c);
 hipError_t launch_small(const sgn_ctx* c, hipStream_t s, const void* qin, void* qout, double dt, int steps);
 // `steps` >= 1 steps by it of the state in q, which ends in q.
 hipError_t enqueue_small_steps(const sgn_ctx* c, hipStream_t s, void* q, double dt, int steps);
+// The same launches (an even count of steps), each timed by events of its own;
+// *ms_per_step: mean over all launches but the first.  Waits for the last.
+hipError_t profile_small_steps(sgn_ctx* c, void* q, double dt, int steps, double* ms_per_step);
 // The tile shape a step kernel of this context runs (24: 32 x 24, ...).
 int tile_of(const sgn_ctx* c, int epi = 0);
 

@@ -226,7 +226,7 @@ hipError_t launch_fused_ty(const sgn_ctx* c, hipStream_t s, const void* qin, voi
 // every tile shape forms the same values.
 hipError_t launch_fused(const sgn_ctx* c, hipStream_t s, const void* qin, void* qout, double dt, double t0,
                         void* ysave = nullptr, double* rpart = nullptr, int epi = sgn::EPI_NONE) {
-  if (!ysave && !rpart && !c->prof_start && sgn_host::small_pays(c)) return sgn_host::launch_small(c, s, qin, qout, dt, 1);
+  if (!ysave && !rpart && sgn_host::small_pays(c)) return sgn_host::launch_small(c, s, qin, qout, dt, 1);
   if (epi != sgn::EPI_RELAX) {
     const sgn_host::MarchPlan m = sgn_host::march_plan(c);
     if (m.tasks) return sgn_host::launch_march(c, s, m, qin, qout, dt, ysave, rpart);
@@ -799,6 +799,11 @@ sgn_status sgn_profile_stages(sgn_ctx* c, void* q, double dt, int64_t nsteps, do
   const bool pairs = c->step_path == SGN_PATH_PAIRS;
   const bool fused = c->step_path == SGN_PATH_FUSED;
   if ((pairs || fused) && (nsteps & 1)) ++nsteps;  // whole double steps, so the state ends in q
+  if (sgn_host::small_pays(c)) {
+    HIPCHK(c, sgn_host::profile_small_steps(c, q, dt, (int)nsteps, ms));
+    ms[1] = ms[2] = ms[3] = 0.0;
+    return sync_results(c, 0);
+  }
   const int nk = fused ? 0 : 4;                      // events between the launches of a profiled unit
   const int64_t units = (pairs || fused) ? nsteps / 2 : nsteps;
   // Pair and four-stage paths: one event between consecutive launches.  Fused
