@@ -97,11 +97,6 @@ struct VjpSmem<double, H, W> {
     uv[r][c] = sgn_d2{a[1], a[2]};
     we[r][c] = sgn_d2{a[3], a[4]};
   }
-  __device__ __forceinline__ void copy_seed(int r, int c, int r2, int c2) {
-    ((double*)&bs[r][c])[1] = bs[r2][c2].y;
-    uv[r][c] = uv[r2][c2];
-    we[r][c] = we[r2][c2];
-  }
 };
 
 template <int H, int W>
@@ -119,10 +114,6 @@ struct VjpSmem<float, H, W> {
   __device__ __forceinline__ void store_seed(int r, int c, const float (&a)[5]) {
     ((float*)&eb[r][c])[3] = a[0];
     a4[r][c] = sgn_f4{a[1], a[2], a[3], a[4]};
-  }
-  __device__ __forceinline__ void copy_seed(int r, int c, int r2, int c2) {
-    ((float*)&eb[r][c])[3] = eb[r2][c2].w;
-    a4[r][c] = a4[r2][c2];
   }
 };
 
@@ -535,9 +526,9 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
   }
   __syncthreads();
 
-  // 3. YB and its 1/h over the one-node halo (b stays), the new seeds on the
-  //    tile and ring.  Positions outside a reflecting wall then take the seed
-  //    of the wall node they copy, as the role kernels stage them.
+  // 3. YB and its r over the one-node halo (b stays), the new seeds on the tile and
+  //    ring.  Positions outside a reflecting wall keep old seeds: a node's neighbours
+  //    are taken where its stencil names them, never beyond a wall.
 #pragma unroll
   for (int it = 0; it < ITB; ++it) {
     const int idx = tid + it * STAGE_THREADS;
@@ -551,17 +542,6 @@ __global__ __launch_bounds__(STAGE_THREADS, 2) void vjp_pair_kernel(const GridCo
   for (int q = 0; q < 3; ++q) {
     if (!ev[q]) continue;
     s.store_seed(pr[q] + H, pc[q] + H, kbB[q]);
-  }
-  if (BCX == BC_REFLECTING || BCY == BC_REFLECTING) {
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      if (!slot[q] || ev[q]) continue;
-      // the reflecting axis clamps; on a periodic axis the position is its own
-      const int ic = BCX == BC_REFLECTING ? wrap_or_clamp<BC_REFLECTING>(i0 + pc[q], nx) - i0 : pc[q];
-      const int jc = BCY == BC_REFLECTING ? wrap_or_clamp<BC_REFLECTING>(j0 + pr[q], ny) - j0 : pr[q];
-      s.copy_seed(pr[q] + H, pc[q] + H, jc + H, ic + H);
-    }
   }
   __syncthreads();
 
