@@ -107,12 +107,26 @@ struct MarchPlan {
 constexpr int64_t MARCH_MIN_NODES = (int64_t)1 << 20;
 constexpr int MARCH_MIN_HEIGHT = 8;
 // Evaluations per step in waves of 64: a strip's rows and those around its runs
-// against a tile's owned and ring nodes (32 x 24 tiles: 60 waves in four stages).
-// The march kernel runs one in 0.78 of the tile kernel's time (4096^2: FP64 466
-// against 602 us, FP32 257 against 324, about 1.31e6 of them either way), so it is
-// taken where it does not need 1.25 times as many: not where a last strip of a few
-// columns leaves most of its lanes idle.
-inline bool march_pays(int64_t march_evals, int64_t tile_evals) { return 4 * march_evals < 5 * tile_evals; }
+// against a 32 x 24 tile's owned and ring nodes (60 waves in four stages).  The march
+// kernel runs one in 0.78 of the tile kernel's time on large grids (4096^2: FP64 466
+// against 602 us, FP32 257 against 324, about 1.31e6 of them either way) and loses
+// some of that where its runs are short.  It is taken where it does not need 1.25
+// times as many: not where a last strip of a few columns leaves most of its lanes
+// idle.  In FP64 with walls on both axes the line is 1.2, as the runs in the corners
+// hold all others up and a last strip of up to four columns leaves its
+// neighbour at the wall too.  Strips and tiles in us, at the ratio given (five runs on
+// three GPUs; the tiles are 32 x 24 ones periodic and in FP32, 32 x 16 ones else):
+//   FP64 periodic  1.04 (1448^2) 71 and 80, 1.13 (1500 x 900) 51 and 51, 1.15 (1063 x
+//     1009) 46 and 46, 1.24 (1024^2) 46.7 and 47.3
+//   FP64, one axis with walls  1.15 (1063 x 1009) 45 .. 47 and 49 .. 50, 1.21 (1065 x
+//     1000) 46 and 49 .. 51, 1.24 (1024^2) 44 .. 47 and 45 .. 46
+//   FP64, both  1.04 (1448^2) 80 and 94, 1.19 (1200 x 900) 49 and 52, 1.21 (1065 x 1000)
+//     55 .. 58 and 52, 1.21 (300 x 3600) 53 and 52, 1.23 (1024^2) 50 and 47
+//   FP32  1.11 (1448^2) 42 .. 44 and 45 .. 48, 1.20 (1063 x 1009) 27 .. 28 and 26 .. 28, 1.25
+//     (1500 x 900) 30 .. 31 and 30 .. 32
+inline bool march_pays(int64_t march_evals, int64_t tile_evals, bool f64_walls = false) {
+  return f64_walls ? 5 * march_evals < 6 * tile_evals : 4 * march_evals < 5 * tile_evals;
+}
 inline int64_t march_evals(int64_t strips, int64_t ny, int64_t chunks) { return strips * (4 * ny + 12 * chunks); }
 inline int64_t tile_evals(int64_t nx, int64_t ny) { return 60 * ((nx + 31) / 32) * ((ny + 23) / 24); }
 MarchPlan march_plan(const sgn_ctx* c);

@@ -59,7 +59,8 @@ MarchPlan march_plan(const sgn_ctx* c) {
   const bool xw = c->p.bc_x == SGN_REFLECTING;
   if (xw && strips < 3) return m;
   const int chunks = std::max(1, std::min(xw ? 2 * slots / (2 * strips + 1) : slots / strips, most));
-  if (!march_pays(march_evals(strips, c->p.ny, chunks), tile_evals(c->p.nx, c->p.ny))) return m;
+  const bool f64_walls = xw && c->p.bc_y == SGN_REFLECTING && c->p.dtype == SGN_F64;
+  if (!march_pays(march_evals(strips, c->p.ny, chunks), tile_evals(c->p.nx, c->p.ny), f64_walls)) return m;
   const int wall_chunks = xw ? std::min(chunks + chunks / 4, most) : 0;
   const bool yw = c->p.bc_y == SGN_REFLECTING;
   if (sgn::march_least_rows(std::max(chunks, wall_chunks), c->p.ny, yw) < sgn::MARCH_LEAST_ROWS) return m;

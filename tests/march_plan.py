@@ -23,8 +23,8 @@ def tile_evals(nx, ny):
     return 60 * cdiv(nx, 32) * cdiv(ny, 24)
 
 
-def pays(march, tile):
-    return 4 * march < 5 * tile
+def pays(march, tile, f64_walls=False):
+    return 5 * march < 6 * tile if f64_walls else 4 * march < 5 * tile
 
 
 def slots(dtype_bytes, cus):
@@ -52,7 +52,7 @@ def plan(nx, ny, bc_x, bc_y, dtype_bytes, cus=256):
         return None
     k = slots(dtype_bytes, cus)
     chunks = max(1, min(2 * k // (2 * s + 1) if bc_x else k // s, most))
-    if not pays(march_evals(s, ny, chunks), tile_evals(nx, ny)):
+    if not pays(march_evals(s, ny, chunks), tile_evals(nx, ny), bc_x and bc_y and dtype_bytes == 8):
         return None
     wall = min(chunks + chunks // 4, most) if bc_x else 0
     if least_rows(max(chunks, wall), ny, bc_y) < MARCH_LEAST_ROWS:

@@ -1,5 +1,5 @@
-"""The march kernel's instances that a grid reaches only by the size rule: FP32 strips at
-walls, FP32 totals, FP32 ensembles of uneven instances, and stage saving in both
+"""The march kernel on grids that the size rule sends there: strips at walls, a last strip
+of one column, totals, ensembles of uneven instances and stage saving, in both
 types.  Every case first asserts, by the host's rule, that it steps by strips."""
 
 import numpy as np
@@ -32,21 +32,23 @@ def on_strips(g, dtype):
     return plan(g.nx, g.ny, g.bc_x, g.bc_y, dtype.itemsize, cus()) is not None
 
 
+@pytest.mark.parametrize("dtype", [F32, F64])
 @pytest.mark.parametrize("nx,ny,bx,by,steps", [
     (56 * 36 + 1, 2100, REF, REF, 3),
-    (56 * 18 + 55, 1009, REF, PER, 2),
-    (1600, 1604, PER, REF, 1),
-    (1500, 900, REF, REF, 4),
+    (56 * 36 + 1, 1700, PER, PER, 1),
+    (56 * 26 + 55, 1409, REF, PER, 2),
+    (1600, 1604, PER, REF, 5),
+    (8200, 300, REF, REF, 1),
 ])
-def test_f32_strips_equal_stage_path(nx, ny, bx, by, steps):
+def test_strips_equal_stage_path(nx, ny, bx, by, steps, dtype):
     g, q, b = problem(nx, ny, bx, by, nx + ny)
-    assert on_strips(g, F32)
+    assert on_strips(g, dtype)
     out = []
     for path in ("fused", "stages"):
-        s = solver(g, F32)
+        s = solver(g, dtype)
         s.set_step_path(path)
-        s.set_bathymetry(dev(b, F32))
-        qd = dev(q, F32)
+        s.set_bathymetry(dev(b, dtype))
+        qd = dev(q, dtype)
         s.step(qd, s.cfl_dt(qd, 0.25), steps)
         s.check()
         out.append(qd)
@@ -58,7 +60,7 @@ def test_f32_strips_equal_stage_path(nx, ny, bx, by, steps):
 def test_totals_on_strips(bx, by, dtype):
     """The series within rounding of the totals pass (compensated sums in another order:
     a few units in the last place), the state to the bit."""
-    g, q, b = problem(56 * 18 + 55, 1009, bx, by, 8)
+    g, q, b = problem(56 * 26 + 55, 1409, bx, by, 8)
     assert on_strips(g, dtype)
     s = solver(g, dtype)
     s.set_bathymetry(dev(b, dtype))
@@ -95,9 +97,10 @@ def test_f32_ensemble_on_strips(steps):
 
 @pytest.mark.parametrize("dtype", [F32, F64])
 @pytest.mark.parametrize("nx,ny,bx,by", [
-    (56 * 18 + 55, 1009, PER, PER),
-    (56 * 18 + 55, 1009, REF, PER),
+    (56 * 26 + 55, 1409, PER, PER),
+    (56 * 26 + 55, 1409, REF, PER),
     (1500, 900, REF, REF),
+    (56 * 36 + 1, 1700, REF, REF),
     (1600, 1604, PER, REF),
 ])
 def test_stage_saving_on_strips(nx, ny, bx, by, dtype):

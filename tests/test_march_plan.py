@@ -34,6 +34,14 @@ def test_runs_of_instances():
                 assert min(b - a for a, b in zip(rows, rows[1:])) == least_rows(n, ny, walls) >= MARCH_LEAST_ROWS
 
 
+def test_grids_that_step_faster_on_tiles():
+    """FP64 with walls on both axes: short runs, or a last strip of one column, step on tiles."""
+    for nx, ny in ((1065, 1000), (300, 3600), (1024, 1024)):
+        assert plan(nx, ny, 1, 1, 8) is None
+    for nx, ny, bc, size in ((1065, 1000, 0, 8), (1200, 900, 1, 8), (1448, 1448, 1, 8), (1500, 900, 1, 4)):
+        assert plan(nx, ny, bc, bc, size) is not None
+
+
 def test_small_instances_make_a_plan():
     assert batch_plan([(4, 4, 1)] * 65600, 4) is not None
     assert batch_plan([(120, 9, 1)] * 1000, 8) is not None
