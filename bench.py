@@ -70,15 +70,17 @@ ADJOINT_STORE_CAP_BYTES = 240 * 2**30
 # march kernel), from the FETCH_SIZE and WRITE_SIZE passes summarized in
 # profiles/march_kernel_4096_periodic_f64.md (FETCH_SIZE scaled by 1.99992 and
 # WRITE_SIZE by 1.0, the factors a plain 1 GiB copy reads): bytes per node and
-# launch.  Reported only while the kernel sources hash to the value they had when
-# the counters were taken.
+# launch.  Reported only while the kernel sources hash to the value below: that of the
+# counters' build, or of a later one whose march kernel for that workload assembles
+# to the same instructions (compared when the value is moved).
 STEP_TRAFFIC_BYTES_PER_NODE = (893248773.0 + 682858960.0) / 16777216
 STEP_KERNEL_SOURCES = ("sgn_common.hpp", "sgn_stage.hpp", "sgn_mms.hpp", "sgn_pair.hpp", "sgn_reduce.hpp",
                        "sgn_fused.hpp", "sgn_march.hpp")
-STEP_SOURCES_SHA256 = "7ba964abcd04071846f10f73d129251debf5a70258a5a2120a7fcc531226b929"
+STEP_SOURCES_SHA256 = "69e39125f55ab7ee3a6d32d90d04cefbb09618b3d5e6db0983abcf4f8d88d56e"
 KERNELS = {"pairs": "pair_kernel (two fused RK4 stages; mean over the 2 launches of a step)",
            "stages": "stage_kernel (fused RHS + RK4 stage; mean over the 4 launches of a step)",
-           "fused": "march_kernel (one whole RK4 step per launch)"}
+           "fused": "march_kernel, on grids and tile heights that step by tiles step_kernel (one whole RK4 step per "
+                    "launch)"}
 ALL_VARIANTS = {"f32", "reflecting", "ensemble", "small", "adjoint", "paths", "paper", "relaxation", "totals",
                 "adaptive", "longdrift"}
 

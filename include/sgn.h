@@ -93,7 +93,7 @@ typedef struct sgn_ctx sgn_ctx;
  *     stages stay in LDS (a four-node halo, evaluated redundantly in rings
  *     around each tile).  11 values of HBM traffic per node and step.  Small
  *     grids (up to about 128 x 128) take two steps per kernel on 8 x 8 tiles
- *     unless SGN_OPT_TILE_Y is set.
+ *     unless SGN_OPT_TILE_Y is set (to any value; a new context has the rule again).
  *   SGN_PATH_PAIRS: two kernels, each fusing two stages; the intermediate
  *     stage stays in LDS.  37 values per node and step.
  *   SGN_PATH_STAGES: four kernels, one per stage.  84 values per node and step.
@@ -403,7 +403,8 @@ sgn_status sgn_batch_set_step_path(sgn_batch* batch, int32_t path);
 sgn_status sgn_batch_set_tiling(sgn_batch* batch, int32_t tile_y, int32_t blocks_per_cu);
 /* Time every (tile height 8, 16 or 24 (fused path, one workgroup per tile),
  * 0..6 workgroups per CU) candidate of the
- * current step path on one step from the
+ * current step path (in SGN_F64 height 24 may run the kernel of height 16, see
+ * sgn_batch_set_tiling) on one step from the
  * registered states into scratch (the states are read, never written), keep
  * the fastest and report it (any output may be NULL; ms = time of one step).
  * Synchronizes. */

@@ -177,12 +177,13 @@ __device__ __forceinline__ void ring_node(int m, int& r, int& c) {
 // KEEP: the owned nodes' current stage Y and its 1/h stay in registers from stage
 // to stage, so that LDS gives them only the nodes around the column of NO (one
 // above, one below, two beside each), two thirds of the reads.  Without KEEP they
-// read their centres back: where the registers would pass 256 (FP64 32 x 24 tiles
-// with a wall: 900 us at 4096^2 instead of 640; the adaptive attempt; the ensemble
-// kernels, which hold all four boundary variants).
-template <typename T, int TY, int BCX, int BCY, int RK>
+// read their centres back: where the registers would pass 256 (the adaptive attempt;
+// and, by their callers' choice, the FP64 ensemble kernels, which hold all four
+// boundary variants, and gauge rollouts on 32 x 24 tiles with a wall; a 4096^2 step
+// on 32 x 24 tiles with walls took 900 us with KEEP and 640 without).
+template <typename T, int RK>
 constexpr bool step_keeps() {
-  return sizeof(T) == 4 || (RK != RK_FSAL && (TY != 24 || (BCX == BC_PERIODIC && BCY == BC_PERIODIC)));
+  return sizeof(T) == 4 || RK != RK_FSAL;
 }
 
 // One tile (origin i0, j0) of one RK4 step, executed by a whole workgroup.
@@ -196,7 +197,7 @@ constexpr bool step_keeps() {
 // output; c6 .. c1, t0, dt and flag are unused (the health of y_{n+1} is
 // checked by the attempt's FSAL evaluation).
 template <typename T, int BCX, int BCY, bool SRC, int TY, bool SAVE, int PAD, int EPI = EPI_NONE,
-          int RK = RK_CLASSIC, bool KEEP = step_keeps<T, TY, BCX, BCY, RK>(), int FORM = FORM_SHARED>
+          int RK = RK_CLASSIC, bool KEEP = step_keeps<T, RK>(), int FORM = FORM_SHARED>
 __device__ __forceinline__ void step_tile(StepSmem<T, TY, PAD>& s, const GridConst& gc, int i0, int j0,
                                           const T* __restrict__ q, const T* __restrict__ bplane,
                                           T* __restrict__ qout, T c6, T c3, T c2, T c1, double t0, double dt,

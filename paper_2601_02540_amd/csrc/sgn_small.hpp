@@ -5,7 +5,7 @@
 // idles.  This kernel makes the chain short.  A workgroup owns 8 x 8 nodes and
 // takes two steps: it stages the nodes with a halo of eight and evaluates the
 // eight stages on squares of 22^2, 20^2, ..., 8^2 nodes, one node per thread.  The
-// redundant evaluations (32 per owned node and two steps, against 10.5 on 32 x 16
+// redundant evaluations (31 per owned node and two steps, against 10.5 on 32 x 16
 // tiles) run on compute units that had nothing else to do.  Threads are numbered
 // from the owned square outwards, so that the nodes of a stage are the first ones
 // and whole waves fall idle as the squares shrink.  Two LDS buffers alternate

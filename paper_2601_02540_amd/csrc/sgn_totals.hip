@@ -3,10 +3,10 @@
 //
 // Each step runs the step kernel with its totals epilogue: every tile reduces
 // M h and M E of the state it writes, from the values it holds in registers,
-// so the series costs no pass over the state.  Two small kernels reduce the
-// per-tile partials (in a fixed order: deterministic) into the next slot of
-// the caller's series, whose index lives in device memory, so that the steps
-// replay from one captured graph.
+// so the series costs no pass over the state.  One small kernel per group of up to
+// eight steps reduces their partials (in a fixed order: deterministic) into the next
+// slots of the caller's series, whose index lives in device memory, so that the
+// steps replay from one captured graph.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
