@@ -79,8 +79,8 @@ STEP_KERNEL_SOURCES = ("sgn_common.hpp", "sgn_stage.hpp", "sgn_mms.hpp", "sgn_pa
 STEP_SOURCES_SHA256 = "69e39125f55ab7ee3a6d32d90d04cefbb09618b3d5e6db0983abcf4f8d88d56e"
 KERNELS = {"pairs": "pair_kernel (two fused RK4 stages; mean over the 2 launches of a step)",
            "stages": "stage_kernel (fused RHS + RK4 stage; mean over the 4 launches of a step)",
-           "fused": "march_kernel, on grids and tile heights that step by tiles step_kernel (one whole RK4 step per "
-                    "launch)"}
+           "fused": "step_kernel (one whole RK4 step per launch)",
+           "strips": "march_kernel (one whole RK4 step per launch)"}
 ALL_VARIANTS = {"f32", "reflecting", "ensemble", "small", "adjoint", "paths", "paper", "relaxation", "totals",
                 "adaptive", "longdrift"}
 
@@ -783,8 +783,10 @@ def roofline(path, res, cells, esize=8):
     if path == "fused" and esize == 8 and cells == 4096 * 4096 and res["tile_y"] in (None, 24) and \
             step_sources_unchanged():
         traffic = STEP_TRAFFIC_BYTES_PER_NODE * cells
+    # the main run's periodic n x n grids step by strips from 1024 x 1024 on (ragged widths just above may not)
+    strips = path == "fused" and res["tile_y"] in (None, 24) and cells >= 1024 * 1024
     out = dict(bound="hbm", achieved=res["achieved_GBs"], peak=HBM_PEAK_GBS, unit="GB/s", frac=res["frac"],
-               traffic=traffic, kernel=KERNELS[path], traffic_unit="bytes per launch",
+               traffic=traffic, kernel=KERNELS["strips" if strips else path], traffic_unit="bytes per launch",
                launch_us=res["stage_launch_us"],
                algorithmic_bytes_per_launch_per_node=values / launches * esize,
                algorithmic_bytes_per_step_per_node=values * esize)
