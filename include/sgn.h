@@ -320,9 +320,10 @@ sgn_status sgn_step_vjp(sgn_ctx* ctx, const void* q_n, double dt, void* qbar, vo
  * nodes gauge_idx[g] (device int64 row-major node indices, 1..4096 gauges)
  * after every step into series[n * ngauges + g] (device doubles, n = 0 is the
  * state after the first step).  In SGN_F64 the rollouts of this call and of
- * sgn_gauge_loss_grad form the right-hand side term by term as printed, so their
- * states agree with those of sgn_step to rounding (in SGN_F32 bit for bit); the
- * step path changes no bit.  Synchronizes. */
+ * sgn_gauge_loss_grad form the right-hand side (and its reverse) term by term as
+ * printed, so their states agree with those of sgn_step, and the reverse with
+ * sgn_step_vjp, to rounding (in SGN_F32 bit for bit); the step path changes no bit
+ * of the states.  Synchronizes. */
 sgn_status sgn_gauge_series(sgn_ctx* ctx, const void* zeta0, int64_t nsteps, double dt, const int64_t* gauge_idx,
                             int32_t ngauges, double* series);
 
